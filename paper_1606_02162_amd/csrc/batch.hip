@@ -1330,10 +1330,12 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
 
     PhaseTimer pt("batch_build", s);
     DevTmp<GraphSrc> d_src(s);
-    DevTmp<int32_t> d_flag(s), d_ci32(s), d_k(s), d_nact(s);
+    DevTmp<CsrCheck> d_check(s);
+    DevTmp<int32_t> d_bfs_work(s), d_ci32(s), d_k(s), d_nact(s);
     DevTmp<int64_t> d_vb(s), d_counts(s), d_bounds(s);
     GILA_TRY(dalloc_t(&d_src.p, std::max(count, 1)));
-    GILA_TRY(dalloc_t(&d_flag.p, 2));
+    GILA_TRY(dalloc_t(&d_check.p, 1));
+    GILA_TRY(dalloc_t(&d_bfs_work.p, 1));
     GILA_TRY(dalloc_t(&b->rp, (size_t)b->nv + 1));
     GILA_TRY(dalloc_t(&d_ci32.p, (size_t)b->nnz));
     GILA_TRY(dalloc_t(&b->ci16, (size_t)b->nnz));
@@ -1341,7 +1343,7 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
     GILA_TRY(dalloc_t(&d_k.p, std::max(count, 1)));
     GILA_TRY(dalloc_t(&d_nact.p, std::max(count, 1)));
     GILA_TRY(dalloc_t(&b->d_work, 1));
-    GILA_HIP(hipMemsetAsync(d_flag.p, 0, 2 * sizeof(int32_t), s));
+    GILA_HIP(hipMemsetAsync(d_check.p, 0, sizeof(CsrCheck), s));
     GILA_HIP(hipMemsetAsync(b->rp, 0, sizeof(int64_t), s));
     GILA_HIP(hipMemcpyAsync(d_vb.p, b->vbase.data(), sizeof(int64_t) * (count + 1),
                             hipMemcpyHostToDevice, s));
@@ -1351,18 +1353,14 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
         GILA_HIP(hipMemcpyAsync(d_k.p, b->k.data(), sizeof(int32_t) * count,
                                 hipMemcpyHostToDevice, s));
         hipLaunchKernelGGL(gather_csr_kernel, dim3(count), dim3(kBlock), 0, s, d_src.p, b->rp,
-                           d_ci32.p, d_flag.p);
+                           d_ci32.p, &d_check.p->flag);
         GILA_HIP(hipGetLastError());
-        GILA_TRY(launch_validate_csr((int32_t)b->nv, b->nnz, b->rp, d_ci32.p, d_flag.p, s));
+        GILA_TRY(launch_validate_csr((int32_t)b->nv, b->nnz, b->rp, d_ci32.p, d_check.p, s));
     }
-    int32_t flag = 0;
-    GILA_HIP(hipMemcpyAsync(&flag, d_flag.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    CsrCheck checked;
+    GILA_HIP(hipMemcpyAsync(&checked, d_check.p, sizeof(checked), hipMemcpyDeviceToHost, s));
     GILA_HIP(hipStreamSynchronize(s));
-    if (flag)
-        return fail(GILA_EINVAL, "malformed CSR in batch:%s%s%s%s%s",
-                    (flag & 16) ? " bad row_ptr" : "", (flag & 1) ? " column out of range" : "",
-                    (flag & 2) ? " self-loop" : "", (flag & 4) ? " row not strictly ascending" : "",
-                    (flag & 8) ? " not symmetric" : "");
+    GILA_TRY(entries_status(checked, " in batch"));
 
     pt.mark("gather+validate");
     // k-hop rows as 16-bit local ids, each padded to whole quads with the
@@ -1436,7 +1434,7 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
         ga.kstart = b->kstart;
         ga.klen = b->klen;
         ga.kidx = b->kidx;
-        ga.work = d_flag.p + 1;
+        ga.work = d_bfs_work.p;
         ga.nmax = b->nmax;
         ga.nnzmax = nnzmax;
         GILA_TRY(run_batch_bfs(ga, bfs_lds, bfs_bs, dev, s));
@@ -1451,7 +1449,7 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
         a.rp = b->rp;
         a.ci = d_ci32.p;
         a.counts = d_counts.p;
-        a.work = d_flag.p + 1;
+        a.work = d_bfs_work.p;
         a.gvbase = d_vb.p;
         a.gk = d_k.p;
         a.ngraphs = count;

@@ -1,11 +1,17 @@
 // Connected components, each laid out on its own, and packing of their
 // drawings (Sections 4.6 and 5.1).
 //
-// Labels: every vertex starts as its own root; each pass hooks, for every
-// edge whose ends have different roots, the larger root under the smaller
-// one (atomic minimum), then compresses every path to its root.  Parent ids
-// only ever decrease, and the loop ends after a pass that hooked nothing:
-// then every edge joins vertices of one tree, whose root is its smallest id.
+// Labels: a forest of parent ids, every parent at most its child's id, so a
+// tree's root is its smallest id.  Every vertex starts under its smallest
+// neighbour; two rounds over the first two neighbours of every vertex hook
+// each tree under a smaller one it touches.  Most vertices are then in one
+// tree (found by a sample), and only those outside it link their whole rows,
+// exactly: the ends' roots are joined with a compare-and-swap, retried from
+// the value found there when another link came first.  An edge with one end
+// outside is linked from that end, one inside joins nothing, so the trees are
+// then the components.  (Exact links of the first neighbours of all vertices
+// at once took 0.64 ms on R-MAT 18: each retry climbs one hop of a long chain
+// of fresh hooks.)
 //
 // Order: a stable sort of the vertices by label groups each component
 // (ascending ids inside); a stable sort of the components by decreasing size
@@ -20,10 +26,12 @@
 // one batched launch (FR model), larger ones one after another on the whole
 // GPU.  Singletons never move.
 //
-// Packing: ranks fill a matrix of ceil(sqrt(C)) columns row by row; a column
-// is as wide as its widest drawing, a row as tall as its tallest, with the
-// gap between consecutive ones; each drawing is translated so that its
-// bounding box's lower-left corner is its cell's.
+// Packing: component sizes and bounding boxes are reduced per label (no
+// sorting of vertices); components, sorted by decreasing size (ties: smaller
+// label), fill a matrix of ceil(sqrt(C)) columns row by row; a column is as
+// wide as its widest drawing, a row as tall as its tallest, with the gap
+// between consecutive ones; each drawing is translated so that its bounding
+// box's lower-left corner is its cell's.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -35,8 +43,6 @@
 namespace gila {
 
 constexpr int32_t kSmallComponent = 2048;
-constexpr int kDigitBits = 11;
-constexpr int kDigits = 1 << kDigitBits;
 
 namespace {
 // Device scratch released into the block cache when its stream is done.
@@ -61,167 +67,209 @@ int grid_for(int64_t items) {
 }  // namespace
 
 // ------------------------------------------------------------------ labels
-__global__ __launch_bounds__(kBlock) void cc_init_kernel(int32_t n, int32_t* parent) {
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock)
-        parent[v] = (int32_t)v;
-}
-
-__device__ __forceinline__ int32_t cc_root(const int32_t* parent, int32_t x) {
+// Root of x, as far as this thread can see; every vertex walked is moved up
+// to its grandparent.  Other workgroups link and move at the same time, and
+// the caches of different XCDs are not coherent within a launch: a value read
+// may be old, but an old parent is still an ancestor (or, of a vertex hooked
+// meanwhile, the vertex itself), and a move written over a newer one too.
+// (Reads through the coherence point instead put every walk's last hops on
+// the one address of the largest tree's root: 1.35 ms on R-MAT 18.)
+__device__ __forceinline__ int32_t cc_root(int32_t* parent, int32_t x) {
     int32_t p = parent[x];
     while (p != x) {
+        const int32_t q = parent[p];
+        if (q != p) parent[x] = q;
         x = p;
-        p = parent[x];
+        p = q;
     }
     return x;
 }
 
-// Wavefront per vertex v; every edge {u, v} with u < v once.
+// Joins the trees of u and v.  Only a root is ever hooked (the atomic compare
+// sees the true parent); where it fails it gives that parent, from which the
+// walk goes on, and ids fall on every retry, so it ends.
+__device__ __forceinline__ void cc_link(int32_t* parent, int32_t u, int32_t v) {
+    int32_t a = cc_root(parent, u), b = cc_root(parent, v);
+    while (a != b) {
+        const int32_t hi = a > b ? a : b, lo = a > b ? b : a;
+        const int32_t was = atomicCAS(&parent[hi], hi, lo);
+        if (was == hi || was == lo) break;
+        a = cc_root(parent, was);  // hooked meanwhile: go on from its parent
+        b = cc_root(parent, lo);
+    }
+}
+
+constexpr int kHookFirst = 2;   // neighbours of every vertex the first rounds look at
+constexpr int kHookRounds = 2;
+
+// Every vertex under its smallest neighbour where that is smaller: a forest
+// without any atomic.
+__global__ __launch_bounds__(kBlock) void cc_init_kernel(int32_t n, const int64_t* __restrict__ rp,
+                                                         const int32_t* __restrict__ ci,
+                                                         int32_t* __restrict__ parent) {
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
+         v += (int64_t)gridDim.x * kBlock) {
+        int32_t p = (int32_t)v;
+        if (rp[v + 1] > rp[v]) p = min(p, ci[rp[v]]);
+        parent[v] = p;
+    }
+}
+
+// One round: every tree (paths compressed, so a parent is a root) goes under
+// the smallest of the roots its vertices' first neighbours have, if smaller.
+// Where it loses a race it loses only that round's edge.  Lanes with the
+// wavefront's first lane's two trees share one atomic: few trees are left
+// soon, and atomics on one address go one after another.
 __global__ __launch_bounds__(kBlock) void cc_hook_kernel(int32_t n, const int64_t* __restrict__ rp,
                                                          const int32_t* __restrict__ ci,
-                                                         int32_t* parent, int32_t* changed) {
-    const int lane = lane64();
-    const int64_t waves = (int64_t)gridDim.x * kWaves;
-    bool hooked = false;
-    for (int64_t v = (int64_t)blockIdx.x * kWaves + wave_id(); v < n; v += waves) {
-        const int64_t re = rp[v + 1];
-        for (int64_t e = rp[v] + lane; e < re; e += 64) {
-            const int32_t u = ci[e];
-            if (u >= v) break;  // rows ascend: the rest of this lane's entries are larger
-            const int32_t ru = cc_root(parent, u), rv = cc_root(parent, (int32_t)v);
-            if (ru != rv) {
-                atomicMin(&parent[ru > rv ? ru : rv], ru < rv ? ru : rv);
-                hooked = true;
-            }
+                                                         int32_t* parent) {
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
+         v += (int64_t)gridDim.x * kBlock) {
+        const int64_t b = rp[v], e = rp[v + 1];
+        for (int64_t j = b; j < e && j < b + kHookFirst; ++j) {
+            const int32_t x = parent[v], y = parent[ci[j]];
+            const int32_t hi = x > y ? x : y, lo = x > y ? y : x;
+            if (hi == lo || parent[hi] <= lo) continue;
+            const bool shared = hi == __builtin_amdgcn_readfirstlane(hi) &&
+                                lo == __builtin_amdgcn_readfirstlane(lo);
+            const uint64_t same = __ballot(shared);
+            if (!shared || (same & ((1ull << lane64()) - 1ull)) == 0ull) atomicMin(&parent[hi], lo);
         }
     }
-    if (__ballot(hooked) && lane == 0) atomicOr(changed, 1);
 }
 
+// label[v] = v's root; nothing is being hooked.  Each thread moves only its
+// own vertex up (a move of another thread's vertex could undo its last one),
+// and all climbing together halves the paths.
 __global__ __launch_bounds__(kBlock) void cc_compress_kernel(int32_t n, int32_t* parent) {
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock)
-        parent[v] = cc_root(parent, (int32_t)v);
+         v += (int64_t)gridDim.x * kBlock) {
+        int32_t p = parent[v];
+        for (;;) {
+            const int32_t q = parent[p];
+            if (q == p) break;  // (roots do not change in this launch)
+            parent[v] = q;
+            p = q;
+        }
+    }
 }
 
-// Labels of a validated graph into label (device, [n]).  Synchronises `s`
-// after every pass (to read whether anything was hooked).
-static int label_components(const gila_csr* g, int32_t* label, hipStream_t s) {
+// The most frequent label of 256 evenly spaced vertices (the smallest such
+// label).  One workgroup; any choice is correct, the best one lets the most
+// rows be skipped.
+constexpr int kSample = 256;
+__global__ __launch_bounds__(kSample) void cc_sample_kernel(int32_t n, const int32_t* __restrict__ label,
+                                                            int32_t* __restrict__ most) {
+    __shared__ int32_t s_label[kSample];
+    __shared__ unsigned long long s_best;
+    const int count = n < kSample ? n : kSample;
+    const int t = threadIdx.x;
+    if (t == 0) s_best = 0ull;
+    if (t < count) s_label[t] = label[(int64_t)t * n / count];
+    __syncthreads();
+    if (t < count) {
+        const int32_t l = s_label[t];
+        unsigned int same = 0;
+        for (int i = 0; i < count; ++i) same += s_label[i] == l ? 1u : 0u;
+        atomicMax(&s_best, ((unsigned long long)same << 32) | (unsigned int)~(unsigned int)l);
+    }
+    __syncthreads();
+    if (t == 0) *most = (int32_t)~(unsigned int)(s_best & 0xFFFFFFFFull);
+}
+
+// Wavefront per 64 vertices: rows outside the component `most` are linked,
+// the wavefront's lanes sharing each longer one.
+__global__ __launch_bounds__(kBlock) void cc_rest_kernel(int32_t n, const int64_t* __restrict__ rp,
+                                                         const int32_t* __restrict__ ci,
+                                                         int32_t* parent,
+                                                         const int32_t* __restrict__ most) {
+    const int lane = lane64();
+    const int32_t skip = *most;
+    const int64_t waves = (int64_t)gridDim.x * kWaves;
+    const int64_t groups = ((int64_t)n + 63) >> 6;
+    for (int64_t g = (int64_t)blockIdx.x * kWaves + wave_id(); g < groups; g += waves) {
+        const int64_t v = g * 64 + lane;
+        int64_t b = 0, e = 0;
+        if (v < n && parent[v] != skip) {
+            b = rp[v];
+            e = rp[v + 1];
+        }
+        // short rows by their own lane, long ones by the whole wavefront
+        constexpr int64_t kOwn = 8;
+        if (e - b <= kOwn)
+            for (int64_t j = b; j < e; ++j) cc_link(parent, (int32_t)v, ci[j]);
+        uint64_t left = __ballot(e - b > kOwn);
+        while (left) {
+            const int l = __builtin_ctzll(left);
+            left &= left - 1ull;
+            const int64_t lb = __shfl(b, l, 64), le = __shfl(e, l, 64);
+            const int32_t lv = (int32_t)(g * 64 + l);
+            for (int64_t j = lb + lane; j < le; j += 64) cc_link(parent, lv, ci[j]);
+        }
+    }
+}
+
+// Roots (label[v] == v) counted per workgroup into partial[blockIdx.x].
+__global__ __launch_bounds__(kBlock) void count_roots_kernel(int32_t n,
+                                                             const int32_t* __restrict__ label,
+                                                             unsigned long long* __restrict__ partial) {
+    __shared__ int64_t s_red[kWaves];
+    int64_t c = 0;
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
+         v += (int64_t)gridDim.x * kBlock)
+        c += label[v] == (int32_t)v ? 1 : 0;
+    const int64_t tot = block_sum<int64_t>(c, s_red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = (unsigned long long)tot;
+}
+
+// total = partial[0] + ... + partial[count - 1] (one workgroup, fixed order).
+__global__ __launch_bounds__(kBlock) void sum_partials_kernel(const unsigned long long* __restrict__ partial,
+                                                              int count,
+                                                              unsigned long long* __restrict__ total) {
+    __shared__ int64_t s_red[kWaves];
+    int64_t c = 0;
+    for (int i = threadIdx.x; i < count; i += kBlock) c += (int64_t)partial[i];
+    const int64_t tot = block_sum<int64_t>(c, s_red);
+    if (threadIdx.x == 0) *total = (unsigned long long)tot;
+}
+
+// Enqueues the labels of a valid graph into label (device, [n]); `most` is one
+// word of scratch.  No synchronisation.
+static int enqueue_labels(const gila_csr* g, int32_t* label, int32_t* most, hipStream_t s) {
     const int32_t n = g->n;
     if (n == 0) return GILA_OK;
-    hipLaunchKernelGGL(cc_init_kernel, dim3(grid_for(n)), dim3(kBlock), 0, s, n, label);
+    const dim3 grid((unsigned)grid_for(n));
+    hipLaunchKernelGGL(cc_init_kernel, grid, dim3(kBlock), 0, s, n, g->row_ptr, g->col_idx, label);
     GILA_HIP(hipGetLastError());
     if (g->nnz == 0) return GILA_OK;
-    Buf flag(s);
-    GILA_TRY(flag.alloc<int32_t>(1));
-    const int hgrid = (int)std::max<int64_t>(1, std::min<int64_t>(16384, ((int64_t)n + kWaves - 1) / kWaves));
-    for (int pass = 0;; ++pass) {
-        if (pass > 4096) return fail(GILA_EDEVICE, "component labels did not settle");
-        GILA_HIP(hipMemsetAsync(flag.p, 0, sizeof(int32_t), s));
-        hipLaunchKernelGGL(cc_hook_kernel, dim3(hgrid), dim3(kBlock), 0, s, n, g->row_ptr,
-                           g->col_idx, label, flag.as<int32_t>());
-        hipLaunchKernelGGL(cc_compress_kernel, dim3(grid_for(n)), dim3(kBlock), 0, s, n, label);
-        GILA_HIP(hipGetLastError());
-        int32_t changed = 0;
-        GILA_HIP(hipMemcpyAsync(&changed, flag.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        GILA_HIP(hipStreamSynchronize(s));
-        if (!changed) break;
+    hipLaunchKernelGGL(cc_compress_kernel, grid, dim3(kBlock), 0, s, n, label);
+    for (int r = 0; r < kHookRounds; ++r) {
+        hipLaunchKernelGGL(cc_hook_kernel, grid, dim3(kBlock), 0, s, n, g->row_ptr, g->col_idx, label);
+        hipLaunchKernelGGL(cc_compress_kernel, grid, dim3(kBlock), 0, s, n, label);
     }
+    hipLaunchKernelGGL(cc_sample_kernel, dim3(1), dim3(kSample), 0, s, n, label, most);
+    hipLaunchKernelGGL(cc_rest_kernel, grid, dim3(kBlock), 0, s, n, g->row_ptr, g->col_idx, label,
+                       most);
+    hipLaunchKernelGGL(cc_compress_kernel, grid, dim3(kBlock), 0, s, n, label);
+    GILA_HIP(hipGetLastError());
     return GILA_OK;
 }
 
-// ------------------------------------------------------------------ stable sort by key
-__global__ __launch_bounds__(kBlock) void iota_kernel(int64_t count, int32_t* out) {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * kBlock)
-        out[i] = (int32_t)i;
+static int label_components(const gila_csr* g, int32_t* label, hipStream_t s) {
+    Buf most(s);
+    GILA_TRY(most.alloc<int32_t>(1));
+    return enqueue_labels(g, label, most.as<int32_t>(), s);
 }
 
-// Per-tile histogram of the digit (key >> shift) & (kDigits - 1) of the
-// elements perm[j], stored digit-major so that its exclusive prefix sum is
-// the first output position of every (digit, tile).
-__global__ __launch_bounds__(kBlock) void digit_hist_kernel(int64_t T, int64_t tj, int64_t ntiles,
-                                                            const int32_t* __restrict__ key,
-                                                            const int32_t* __restrict__ perm,
-                                                            int shift, int64_t* __restrict__ hist) {
-    __shared__ int32_t s_cnt[kDigits];
-    for (int s = threadIdx.x; s < kDigits; s += kBlock) s_cnt[s] = 0;
-    __syncthreads();
-    const int64_t j0 = (int64_t)blockIdx.x * tj;
-    const int64_t j1 = j0 + tj < T ? j0 + tj : T;
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += kBlock)
-        atomicAdd(&s_cnt[(key[perm[j]] >> shift) & (kDigits - 1)], 1);
-    __syncthreads();
-    for (int s = threadIdx.x; s < kDigits; s += kBlock) hist[(int64_t)s * ntiles + blockIdx.x] = s_cnt[s];
-}
-
-// One wavefront per tile walks it in order, 64 elements at a time; equal
-// digits within a step are ranked by lane, so equal keys keep their order.
-__global__ __launch_bounds__(64) void digit_scatter_kernel(int64_t T, int64_t tj, int64_t ntiles,
-                                                           const int32_t* __restrict__ key,
-                                                           const int32_t* __restrict__ perm,
-                                                           int shift, const int64_t* __restrict__ base,
-                                                           int32_t* __restrict__ out) {
-    __shared__ int64_t s_next[kDigits];
-    const int lane = threadIdx.x;
-    for (int s = lane; s < kDigits; s += 64) s_next[s] = base[(int64_t)s * ntiles + blockIdx.x];
-    __syncthreads();
-    const int64_t j0 = (int64_t)blockIdx.x * tj;
-    const int64_t j1 = j0 + tj < T ? j0 + tj : T;
-    for (int64_t c = j0; c < j1; c += 64) {
-        const int64_t j = c + lane;
-        const bool valid = j < j1;
-        const int32_t e = valid ? perm[j] : 0;
-        const int32_t dg = valid ? (key[e] >> shift) & (kDigits - 1) : -1;
-        int rank = 0, same = 0;
-        for (int l = 0; l < 64; ++l) {
-            const int32_t dl = __builtin_amdgcn_readlane(dg, l);
-            same += dl == dg ? 1 : 0;
-            rank += (dl == dg && l < lane) ? 1 : 0;
-        }
-        const int64_t at = valid ? s_next[dg] : 0;
-        __syncthreads();
-        if (valid) {
-            out[at + rank] = e;
-            if (rank == same - 1) s_next[dg] = at + same;
-        }
-        __syncthreads();
-    }
-}
-
-// perm_out[i] = the element at sorted position i of 0 .. T-1 ordered by
-// key[element] (0 <= key <= kmax), ties in element order.
-static int stable_sort_by_key(const int32_t* key, int64_t T, int32_t kmax, int32_t* perm_out,
-                              hipStream_t s) {
-    if (T == 0) return GILA_OK;
-    const int64_t tj = std::max<int64_t>(4096, (T * kDigits + (1 << 24) - 1) >> 24);
-    const int64_t ntiles = (T + tj - 1) / tj;
-    const int64_t H = ntiles * kDigits;
-    Buf tmp(s), hist(s), scan(s), ws(s);
-    GILA_TRY(tmp.alloc<int32_t>((size_t)T));
-    GILA_TRY(hist.alloc<int64_t>((size_t)H));
-    GILA_TRY(scan.alloc<int64_t>((size_t)H + 1));
-    GILA_TRY(ws.alloc<int64_t>((size_t)scan_workspace_count(H)));
-    int passes = 0;
-    for (int shift = 0; shift == 0 || (shift < 31 && (kmax >> shift) > 0); shift += kDigitBits) ++passes;
-    // the passes alternate between the two buffers and end in perm_out
-    int32_t* bufs[2] = {perm_out, tmp.as<int32_t>()};
-    int32_t* cur = bufs[passes & 1];
-    hipLaunchKernelGGL(iota_kernel, dim3(grid_for(T)), dim3(kBlock), 0, s, T, cur);
+// Enqueues the number of roots of label[n] into *total; partial: at least
+// min(kCountPartials, blocks of kBlock vertices) words.
+constexpr int kCountPartials = 2040;
+static int enqueue_count_roots(int32_t n, const int32_t* label, unsigned long long* partial,
+                               unsigned long long* total, hipStream_t s) {
+    const int grid = (int)std::min<int64_t>(kCountPartials, ((int64_t)n + kBlock - 1) / kBlock);
+    hipLaunchKernelGGL(count_roots_kernel, dim3(grid), dim3(kBlock), 0, s, n, label, partial);
+    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(kBlock), 0, s, partial, grid, total);
     GILA_HIP(hipGetLastError());
-    int pass = 0;
-    for (int shift = 0; shift == 0 || (shift < 31 && (kmax >> shift) > 0); shift += kDigitBits, ++pass) {
-        int32_t* nxt = bufs[(passes - pass - 1) & 1];
-        hipLaunchKernelGGL(digit_hist_kernel, dim3((unsigned)ntiles), dim3(kBlock), 0, s, T, tj,
-                           ntiles, key, cur, shift, hist.as<int64_t>());
-        GILA_HIP(hipGetLastError());
-        GILA_TRY(enqueue_exclusive_scan_i64(hist.as<int64_t>(), scan.as<int64_t>(), H,
-                                            ws.as<int64_t>(), s));
-        hipLaunchKernelGGL(digit_scatter_kernel, dim3((unsigned)ntiles), dim3(64), 0, s, T, tj,
-                           ntiles, key, cur, shift, scan.as<int64_t>(), nxt);
-        GILA_HIP(hipGetLastError());
-        cur = nxt;
-    }
     return GILA_OK;
 }
 
@@ -318,7 +366,8 @@ static int order_components(int32_t n, const int32_t* label, hipStream_t s, Comp
     GILA_TRY(gstart.alloc<int64_t>((size_t)n));
     GILA_TRY(gidx.alloc<int64_t>((size_t)n + 1));
     GILA_TRY(ws.alloc<int64_t>((size_t)scan_workspace_count(n)));
-    GILA_TRY(stable_sort_by_key(label, n, n - 1, bylabel.as<int32_t>(), s));
+    GILA_TRY(stable_order_by_key(n, reinterpret_cast<const uint32_t*>(label), (uint32_t)(n - 1),
+                                 bylabel.as<int32_t>(), s));
     hipLaunchKernelGGL(group_start_kernel, dim3(grid_for(n)), dim3(kBlock), 0, s, n, label,
                        bylabel.as<int32_t>(), gstart.as<int64_t>());
     GILA_HIP(hipGetLastError());
@@ -342,7 +391,8 @@ static int order_components(int32_t n, const int32_t* label, hipStream_t s, Comp
     hipLaunchKernelGGL(group_size_kernel, dim3(grid_for(C)), dim3(kBlock), 0, s, o.C, n,
                        gfirst.as<int64_t>(), gsize.as<int32_t>(), gkey.as<int32_t>());
     GILA_HIP(hipGetLastError());
-    GILA_TRY(stable_sort_by_key(gkey.as<int32_t>(), C, n - 1, byrank.as<int32_t>(), s));
+    GILA_TRY(stable_order_by_key((int32_t)C, gkey.as<uint32_t>(), (uint32_t)(n - 1),
+                                 byrank.as<int32_t>(), s));
     hipLaunchKernelGGL(rank_tables_kernel, dim3(grid_for(C)), dim3(kBlock), 0, s, o.C,
                        byrank.as<int32_t>(), gsize.as<int32_t>(), grank.as<int32_t>(),
                        rsize.as<int32_t>(), rsize64.as<int64_t>());
@@ -413,55 +463,6 @@ __global__ __launch_bounds__(kBlock) void rank_bbox_kernel(int32_t R, const int6
     }
 }
 
-// Column widths and row heights: the largest extent in each (extents are
-// non-negative, so their bit patterns order as the values; the arrays start
-// at zero).
-__global__ __launch_bounds__(kBlock) void pack_extent_kernel(int32_t C, int32_t cols,
-                                                             const double4* __restrict__ box,
-                                                             unsigned long long* __restrict__ colw,
-                                                             unsigned long long* __restrict__ rowh) {
-    for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < C;
-         r += (int64_t)gridDim.x * kBlock) {
-        const double w = box[r].z - box[r].x, h = box[r].w - box[r].y;
-        atomicMax(&colw[r % cols], (unsigned long long)__double_as_longlong(w + 0.0));
-        atomicMax(&rowh[r / cols], (unsigned long long)__double_as_longlong(h + 0.0));
-    }
-}
-
-// Cell corners: running sums of widths and heights plus the gap, in the
-// order of a plain loop (one thread; there are at most 46341 columns).
-__global__ void pack_cells_kernel(int32_t cols, int32_t rows, double gap,
-                                  const unsigned long long* __restrict__ colw,
-                                  const unsigned long long* __restrict__ rowh,
-                                  double* __restrict__ colx, double* __restrict__ rowy) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    colx[0] = 0.0;
-    rowy[0] = 0.0;
-    for (int32_t j = 0; j < cols; ++j) colx[j + 1] = colx[j] + __longlong_as_double((long long)colw[j]) + gap;
-    for (int32_t j = 0; j < rows; ++j) rowy[j + 1] = rowy[j] + __longlong_as_double((long long)rowh[j]) + gap;
-}
-
-// Translate (new order) and scatter back to the caller's ids.
-template <class V>
-__global__ __launch_bounds__(kBlock) void pack_move_kernel(int32_t n, int32_t cols,
-                                                           const int32_t* __restrict__ vrank,
-                                                           const int32_t* __restrict__ perm,
-                                                           const double4* __restrict__ box,
-                                                           const double* __restrict__ colx,
-                                                           const double* __restrict__ rowy,
-                                                           const V* __restrict__ src,
-                                                           V* __restrict__ dst) {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kBlock) {
-        const int32_t r = vrank[i];
-        const double4 b = box[r];
-        V p = src[i];
-        p.x = (decltype(p.x))((double)p.x + (colx[r % cols] - b.x));
-        p.y = (decltype(p.y))((double)p.y + (rowy[r / cols] - b.y));
-        dst[perm[i]] = p;
-    }
-}
-
 template <class V>
 __global__ __launch_bounds__(kBlock) void gather_new_kernel(int32_t n, const int32_t* __restrict__ perm,
                                                             const V* __restrict__ src,
@@ -471,57 +472,334 @@ __global__ __launch_bounds__(kBlock) void gather_new_kernel(int32_t n, const int
         dst[i] = src[perm[i]];
 }
 
-// Packing of positions held in new order (pos_new) into the caller's ids.
 template <class V>
-static int pack_new_order(int32_t n, const CompOrder& o, double gap, const V* pos_new, V* pos_out,
-                          hipStream_t s) {
-    if (n == 0) return GILA_OK;
-    int32_t cols = 1;
-    while ((int64_t)cols * cols < o.C) ++cols;
-    const int32_t rows = (o.C + cols - 1) / cols;
-    Buf box(s), colx(s), rowy(s), ext(s);
-    GILA_TRY(box.alloc<double4>((size_t)o.C));
-    GILA_TRY(colx.alloc<double>((size_t)cols + 1));
-    GILA_TRY(rowy.alloc<double>((size_t)rows + 1));
-    GILA_TRY(ext.alloc<unsigned long long>((size_t)cols + rows));
-    unsigned long long* colw = ext.as<unsigned long long>();
-    unsigned long long* rowh = colw + cols;
-    GILA_HIP(hipMemsetAsync(colw, 0, sizeof(unsigned long long) * (cols + rows), s));
-    hipLaunchKernelGGL(rank_bbox_kernel<V>, dim3((unsigned)std::min<int64_t>(65536, o.C)),
-                       dim3(kBlock), 0, s, o.C, o.roff.as<int64_t>(), pos_new, box.as<double4>());
-    hipLaunchKernelGGL(pack_extent_kernel, dim3(grid_for(o.C)), dim3(kBlock), 0, s, o.C, cols,
-                       box.as<double4>(), colw, rowh);
-    hipLaunchKernelGGL(pack_cells_kernel, dim3(1), dim3(64), 0, s, cols, rows, gap, colw, rowh,
-                       colx.as<double>(), rowy.as<double>());
-    hipLaunchKernelGGL(pack_move_kernel<V>, dim3(grid_for(n)), dim3(kBlock), 0, s, n, cols,
-                       o.vrank.as<int32_t>(), o.perm.as<int32_t>(), box.as<double4>(),
-                       colx.as<double>(), rowy.as<double>(), pos_new, pos_out);
-    GILA_HIP(hipGetLastError());
-    return GILA_OK;
+__global__ __launch_bounds__(kBlock) void scatter_old_kernel(int32_t n, const int32_t* __restrict__ perm,
+                                                             const V* __restrict__ src,
+                                                             V* __restrict__ dst) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kBlock)
+        dst[perm[i]] = src[i];
 }
 
-template <class V>
-static int pack_positions(int32_t n, const CompOrder& o, double gap, V* pos, hipStream_t s) {
-    Buf tmp(s);
-    GILA_TRY(tmp.alloc<V>((size_t)std::max(n, 1)));
-    hipLaunchKernelGGL(gather_new_kernel<V>, dim3(grid_for(n)), dim3(kBlock), 0, s, n,
-                       o.perm.as<int32_t>(), pos, tmp.as<V>());
-    GILA_HIP(hipGetLastError());
-    return pack_new_order<V>(n, o, gap, tmp.as<V>(), pos, s);
+// Order-preserving integer keys of coordinates, so that bounding boxes are
+// kept with integer atomics.
+template <class R>
+struct Key;
+template <>
+struct Key<float> {
+    using word = unsigned int;
+    static constexpr word kTop = 0x80000000u;
+    __device__ static word bits(float f) { return __float_as_uint(f); }
+    __device__ static float value(word u) { return __uint_as_float(u); }
+};
+template <>
+struct Key<double> {
+    using word = unsigned long long;
+    static constexpr word kTop = 0x8000000000000000ull;
+    __device__ static word bits(double f) { return (word)__double_as_longlong(f); }
+    __device__ static double value(word u) { return __longlong_as_double((long long)u); }
+};
+template <class R>
+__device__ __forceinline__ typename Key<R>::word to_key(R f) {
+    const auto u = Key<R>::bits(f);
+    return (u & Key<R>::kTop) ? ~u : (u | Key<R>::kTop);
+}
+template <class R>
+__device__ __forceinline__ R from_key(typename Key<R>::word k) {
+    return Key<R>::value((k & Key<R>::kTop) ? (k & ~Key<R>::kTop) : ~k);
 }
 
-// Component labels given by a caller: each in [0, n) and naming a vertex
-// labelled with itself.
-__global__ __launch_bounds__(kBlock) void check_labels_kernel(int32_t n, const int32_t* __restrict__ label,
-                                                              int32_t* __restrict__ bad) {
-    bool b = false;
+// Size and bounding box of the component with label l (entry l; the others
+// stay unused).  Boxes hold keys: xmin, ymin (minimum) and the keys of -xmax,
+// -ymax (minimum too).
+template <class R>
+struct LabelBox {
+    typename Key<R>::word k[4];
+};
+
+template <class R>
+__global__ __launch_bounds__(kBlock) void pack_init_kernel(int32_t n, int32_t* __restrict__ size,
+                                                           LabelBox<R>* __restrict__ box) {
+    using W = typename Key<R>::word;
+    const W inf = to_key((R)INFINITY);
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * kBlock) {
-        const int32_t l = label[v];
-        if (l < 0 || l >= n) b = true;
-        else if (label[l] != l) b = true;
+        size[v] = 0;
+        for (int c = 0; c < 4; ++c) box[v].k[c] = inf;
     }
-    if (__ballot(b) && lane64() == 0) atomicOr(bad, 1);
+}
+
+// Adds every vertex to its component.  Atomics on one address go one after
+// another, so the vertices of the most frequent label of a sample are
+// reduced per workgroup before one set of them, and of the others those that
+// share the label of a wavefront's first non-root vertex per wavefront.  Also
+// the check of the labels: each in [0, n) and naming a vertex labelled with
+// itself (*bad otherwise; such a vertex is left out).
+template <class V, class R>
+__global__ __launch_bounds__(kBlock) void pack_reduce_kernel(int32_t n, const int32_t* __restrict__ label,
+                                                             const int32_t* __restrict__ most_p,
+                                                             const V* __restrict__ pos,
+                                                             int32_t* __restrict__ size,
+                                                             LabelBox<R>* __restrict__ box,
+                                                             int32_t* __restrict__ bad) {
+    using W = typename Key<R>::word;
+    const W inf = to_key((R)INFINITY);
+    const int32_t most = *most_p;
+    const int lane = lane64();
+    const auto lower = [](W x, W y) { return x < y ? x : y; };
+    int32_t cnt = 0;
+    W mk[4] = {inf, inf, inf, inf};
+    bool wrong = false;
+    for (int64_t v0 = (int64_t)blockIdx.x * kBlock; v0 < n; v0 += (int64_t)gridDim.x * kBlock) {
+        const int64_t v = v0 + threadIdx.x;
+        int32_t l = -1;
+        W k[4] = {inf, inf, inf, inf};
+        if (v < n) {
+            l = label[v];
+            if (l < 0 || l >= n || label[l] != l) {
+                wrong = true;
+                l = -1;
+            } else {
+                const V p = pos[v];
+                // (a NaN coordinate takes no part in its box)
+                if (p.x == p.x) {
+                    k[0] = to_key((R)p.x);
+                    k[2] = to_key((R)-p.x);
+                }
+                if (p.y == p.y) {
+                    k[1] = to_key((R)p.y);
+                    k[3] = to_key((R)-p.y);
+                }
+            }
+        }
+        if (l >= 0 && l == most) {
+            ++cnt;
+            for (int c = 0; c < 4; ++c) mk[c] = lower(mk[c], k[c]);
+            l = -1;
+        }
+        // the wavefront's shared label: of its first vertex that is no root
+        const uint64_t member = __ballot(l >= 0 && l != (int32_t)v);
+        if (member) {
+            const int32_t lead = __shfl(l, __builtin_ctzll(member), 64);
+            const uint64_t mine = __ballot(l == lead);
+            W g[4];
+            for (int c = 0; c < 4; ++c) {
+                g[c] = l == lead ? k[c] : inf;
+                for (int off = 32; off >= 1; off >>= 1) g[c] = lower(g[c], __shfl_xor(g[c], off, 64));
+            }
+            if (lane == 0) {
+                atomicAdd(&size[lead], (int32_t)__popcll(mine));
+                for (int c = 0; c < 4; ++c) atomicMin(&box[lead].k[c], g[c]);
+            }
+            if (l == lead) l = -1;
+        }
+        if (l >= 0) {
+            atomicAdd(&size[l], 1);
+            for (int c = 0; c < 4; ++c) atomicMin(&box[l].k[c], k[c]);
+        }
+    }
+    __shared__ W s_k[4][kWaves];
+    __shared__ int32_t s_n[kWaves];
+    cnt = wave_sum(cnt);
+    for (int c = 0; c < 4; ++c)
+        for (int off = 32; off >= 1; off >>= 1) mk[c] = lower(mk[c], __shfl_xor(mk[c], off, 64));
+    if (lane == 0) {
+        s_n[wave_id()] = cnt;
+        for (int c = 0; c < 4; ++c) s_k[c][wave_id()] = mk[c];
+    }
+    if (__ballot(wrong) && lane == 0) atomicOr(bad, 1);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kWaves; ++q) {
+            cnt += s_n[q];
+            for (int c = 0; c < 4; ++c) mk[c] = lower(mk[c], s_k[c][q]);
+        }
+        if (cnt > 0) {
+            atomicAdd(&size[most], cnt);
+            for (int c = 0; c < 4; ++c) atomicMin(&box[most].k[c], mk[c]);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void root_flag_kernel(int32_t n, const int32_t* __restrict__ label,
+                                                           int64_t* __restrict__ flag) {
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
+         v += (int64_t)gridDim.x * kBlock)
+        flag[v] = label[v] == (int32_t)v ? 1 : 0;
+}
+
+// Components in ascending label order, with their sort keys (larger first).
+__global__ __launch_bounds__(kBlock) void root_list_kernel(int32_t n, const int32_t* __restrict__ label,
+                                                           const int64_t* __restrict__ at,
+                                                           const int32_t* __restrict__ size,
+                                                           int32_t* __restrict__ root,
+                                                           uint32_t* __restrict__ key) {
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
+         v += (int64_t)gridDim.x * kBlock)
+        if (label[v] == (int32_t)v) {
+            root[at[v]] = (int32_t)v;
+            key[at[v]] = (uint32_t)(n - size[v]);
+        }
+}
+
+// Rank r holds component byrank[r]: each root's rank, each rank's box.
+template <class R>
+__global__ __launch_bounds__(kBlock) void rank_box_kernel(int32_t C, const int32_t* __restrict__ byrank,
+                                                          const int32_t* __restrict__ root,
+                                                          const LabelBox<R>* __restrict__ lbox,
+                                                          int32_t* __restrict__ rank_of,
+                                                          double4* __restrict__ box) {
+    for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < C;
+         r += (int64_t)gridDim.x * kBlock) {
+        const int32_t v = root[byrank[r]];
+        const LabelBox<R> b = lbox[v];
+        rank_of[v] = (int32_t)r;
+        box[r] = make_double4((double)from_key<R>(b.k[0]), (double)from_key<R>(b.k[1]),
+                              -(double)from_key<R>(b.k[2]), -(double)from_key<R>(b.k[3]));
+    }
+}
+
+// Column widths and row heights, a wavefront for each: the largest extent
+// (at least zero) of its components.
+__global__ __launch_bounds__(kBlock) void pack_extent_kernel(int32_t C, int32_t cols, int32_t rows,
+                                                             const double4* __restrict__ box,
+                                                             double* __restrict__ colw,
+                                                             double* __restrict__ rowh) {
+    const int lane = lane64();
+    const int64_t j = (int64_t)blockIdx.x * kWaves + wave_id();
+    if (j >= (int64_t)cols + rows) return;
+    double m = 0.0;
+    if (j < cols) {
+        for (int64_t r = j + (int64_t)lane * cols; r < C; r += 64 * (int64_t)cols)
+            m = fmax(m, box[r].z - box[r].x);
+    } else {
+        const int64_t r0 = (j - cols) * cols, r1 = min(r0 + cols, (int64_t)C);
+        for (int64_t r = r0 + lane; r < r1; r += 64) m = fmax(m, box[r].w - box[r].y);
+    }
+    m = wave_max(m);
+    if (lane == 0) (j < cols ? colw[j] : rowh[j - cols]) = m;
+}
+
+// Cell corners: running sums of widths (workgroup 0) and heights (1) plus the
+// gap, added one after another as a plain loop does, the values staged in LDS
+// (there are at most 46341 of each).  The chain of additions is what it takes;
+// one thread reading its values from global memory took 56 us for 374.
+__global__ __launch_bounds__(kBlock) void pack_cells_kernel(int32_t cols, int32_t rows, double gap,
+                                                            const double* __restrict__ colw,
+                                                            const double* __restrict__ rowh,
+                                                            double* __restrict__ colx,
+                                                            double* __restrict__ rowy) {
+    constexpr int kStage = 1024;
+    __shared__ double s_in[kStage], s_out[kStage];
+    __shared__ double s_sum;
+    const int32_t count = blockIdx.x == 0 ? cols : rows;
+    const double* in = blockIdx.x == 0 ? colw : rowh;
+    double* out = blockIdx.x == 0 ? colx : rowy;
+    if (threadIdx.x == 0) {
+        s_sum = 0.0;
+        out[0] = 0.0;
+    }
+    for (int32_t j0 = 0; j0 < count; j0 += kStage) {
+        const int32_t c = min(kStage, count - j0);
+        for (int i = threadIdx.x; i < c; i += kBlock) s_in[i] = in[j0 + i];
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double a = s_sum;
+#pragma unroll 8
+            for (int i = 0; i < c; ++i) {
+                a = a + s_in[i] + gap;
+                s_out[i] = a;
+            }
+            s_sum = a;
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < c; i += kBlock) out[j0 + i + 1] = s_out[i];
+        __syncthreads();
+    }
+}
+
+template <class V>
+__global__ __launch_bounds__(kBlock) void pack_move_kernel(int32_t n, int32_t cols,
+                                                           const int32_t* __restrict__ label,
+                                                           const int32_t* __restrict__ rank_of,
+                                                           const double4* __restrict__ box,
+                                                           const double* __restrict__ colx,
+                                                           const double* __restrict__ rowy,
+                                                           V* __restrict__ pos) {
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
+         v += (int64_t)gridDim.x * kBlock) {
+        const int32_t r = rank_of[label[v]];
+        const double bx = box[r].x, by = box[r].y;
+        V p = pos[v];
+        p.x = (decltype(p.x))((double)p.x + (colx[r % cols] - bx));
+        p.y = (decltype(p.y))((double)p.y + (rowy[r / cols] - by));
+        pos[v] = p;
+    }
+}
+
+// Packs the drawings of the labelled components in place (caller's ids).
+// EINVAL, with pos untouched, for labels out of range or not naming a vertex
+// labelled with itself.
+template <class V>
+static int pack_positions(int32_t n, const int32_t* label, double gap, V* pos, hipStream_t s) {
+    using R = decltype(V::x);
+    if (n == 0) return GILA_OK;
+    Buf size(s), lbox(s), flag(s), at(s), ws(s), small(s);
+    GILA_TRY(size.alloc<int32_t>((size_t)n));
+    GILA_TRY(lbox.alloc<LabelBox<R>>((size_t)n));
+    GILA_TRY(flag.alloc<int64_t>((size_t)n));
+    GILA_TRY(at.alloc<int64_t>((size_t)n + 1));
+    GILA_TRY(ws.alloc<int64_t>((size_t)scan_workspace_count(n)));
+    GILA_TRY(small.alloc<int32_t>(2));
+    int32_t* most = small.as<int32_t>();
+    int32_t* bad = most + 1;
+    const dim3 grid((unsigned)grid_for(n));
+    GILA_HIP(hipMemsetAsync(bad, 0, sizeof(int32_t), s));
+    hipLaunchKernelGGL(cc_sample_kernel, dim3(1), dim3(kSample), 0, s, n, label, most);
+    hipLaunchKernelGGL(pack_init_kernel<R>, grid, dim3(kBlock), 0, s, n, size.as<int32_t>(),
+                       lbox.as<LabelBox<R>>());
+    // (few enough workgroups that each reduces many vertices of the largest component)
+    hipLaunchKernelGGL((pack_reduce_kernel<V, R>), dim3((unsigned)std::min(grid_for(n), 512)), dim3(kBlock),
+                       0, s, n, label, most, pos, size.as<int32_t>(), lbox.as<LabelBox<R>>(), bad);
+    hipLaunchKernelGGL(root_flag_kernel, grid, dim3(kBlock), 0, s, n, label, flag.as<int64_t>());
+    GILA_HIP(hipGetLastError());
+    GILA_TRY(enqueue_exclusive_scan_i64(flag.as<int64_t>(), at.as<int64_t>(), n, ws.as<int64_t>(), s));
+    int32_t hbad = 0;
+    int64_t C64 = 0;
+    GILA_HIP(hipMemcpyAsync(&hbad, bad, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    GILA_HIP(hipMemcpyAsync(&C64, at.as<int64_t>() + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    GILA_HIP(hipStreamSynchronize(s));
+    if (hbad) return fail(GILA_EINVAL, "labels must lie in [0, n) and name a vertex labelled with itself");
+    const int32_t C = (int32_t)C64;
+    int32_t cols = 1;
+    while ((int64_t)cols * cols < C) ++cols;
+    const int32_t rows = (C + cols - 1) / cols;
+    Buf root(s), key(s), byrank(s), rank_of(s), box(s), ext(s);
+    GILA_TRY(root.alloc<int32_t>((size_t)C));
+    GILA_TRY(key.alloc<uint32_t>((size_t)C));
+    GILA_TRY(byrank.alloc<int32_t>((size_t)C));
+    GILA_TRY(rank_of.alloc<int32_t>((size_t)n));
+    GILA_TRY(box.alloc<double4>((size_t)C));
+    GILA_TRY(ext.alloc<double>(2 * ((size_t)cols + rows) + 2));
+    double* colw = ext.as<double>();
+    double* rowh = colw + cols;
+    double* colx = rowh + rows;
+    double* rowy = colx + cols + 1;
+    hipLaunchKernelGGL(root_list_kernel, grid, dim3(kBlock), 0, s, n, label, at.as<int64_t>(),
+                       size.as<int32_t>(), root.as<int32_t>(), key.as<uint32_t>());
+    GILA_HIP(hipGetLastError());
+    GILA_TRY(stable_order_by_key(C, key.as<uint32_t>(), (uint32_t)(n - 1), byrank.as<int32_t>(), s));
+    hipLaunchKernelGGL(rank_box_kernel<R>, dim3((unsigned)grid_for(C)), dim3(kBlock), 0, s, C,
+                       byrank.as<int32_t>(), root.as<int32_t>(), lbox.as<LabelBox<R>>(),
+                       rank_of.as<int32_t>(), box.as<double4>());
+    hipLaunchKernelGGL(pack_extent_kernel, dim3((unsigned)((cols + rows + kWaves - 1) / kWaves)),
+                       dim3(kBlock), 0, s, C, cols, rows, box.as<double4>(), colw, rowh);
+    hipLaunchKernelGGL(pack_cells_kernel, dim3(2), dim3(kBlock), 0, s, cols, rows, gap, colw, rowh, colx,
+                       rowy);
+    hipLaunchKernelGGL(pack_move_kernel<V>, grid, dim3(kBlock), 0, s, n, cols, label,
+                       rank_of.as<int32_t>(), box.as<double4>(), colx, rowy, pos);
+    GILA_HIP(hipGetLastError());
+    return GILA_OK;
 }
 
 // ------------------------------------------------------------------ per-component CSRs
@@ -672,7 +950,10 @@ static int layout_components(const gila_csr* g, int32_t k, const gila_params* pa
         GILA_TRY(rc);
         for (int32_t j = 0; j < nsmall; ++j) runs[small_first + j] = st[j].iterations_run;
     }
-    GILA_TRY(pack_new_order<V>(n, o, d, npos.as<V>(), pos, s));
+    hipLaunchKernelGGL(scatter_old_kernel<V>, dim3(grid_for(n)), dim3(kBlock), 0, s, n,
+                       o.perm.as<int32_t>(), npos.as<V>(), pos);
+    GILA_HIP(hipGetLastError());
+    GILA_TRY(pack_positions<V>(n, label.as<int32_t>(), d, pos, s));
     if (iterations_host) {
         std::vector<int32_t> perm((size_t)n);
         GILA_HIP(hipMemcpyAsync(perm.data(), o.perm.p, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
@@ -687,13 +968,14 @@ static int layout_components(const gila_csr* g, int32_t k, const gila_params* pa
 // ------------------------------------------------------------------ labels without allocation
 // gila_components_noalloc keeps its scratch in a fixed array per device,
 // never in allocated memory.  Layout (64-bit words):
-//   [0] CSR flags (int32 in the low half), [1] hooked-this-pass flag (int32),
-//   [2] number of components, [8, 8 + kNoAllocPartials) per-workgroup root
+//   [0, 3) CSR checks (CsrCheck), [3] most frequent label (int32),
+//   [4] number of components, [8, 8 + kNoAllocPartials) per-workgroup root
 //   counts.  The counting grid never exceeds kNoAllocPartials workgroups, so
 //   no graph needs more than these 16 KiB.
 constexpr int kNoAllocHeader = 8;
-constexpr int kNoAllocPartials = 2040;
+constexpr int kNoAllocPartials = kCountPartials;
 constexpr int kNoAllocWords = kNoAllocHeader + kNoAllocPartials;
+static_assert(sizeof(CsrCheck) == 3 * sizeof(unsigned long long), "three words of scratch");
 static __device__ __align__(256) unsigned long long scratch[kNoAllocWords];
 
 constexpr int kMaxScratchDevices = 64;
@@ -726,54 +1008,6 @@ __global__ void clear_words_kernel(unsigned long long* w, int count) {
     for (int i = threadIdx.x; i < count; i += blockDim.x) w[i] = 0ull;
 }
 
-// row_ptr rules (0 first, nnz last, monotone, every offset in [0, nnz]) on the
-// device: flag bit 16.  The CSR checks of validate_csr_kernel read col_idx
-// through row_ptr and may run only once these hold.
-__global__ __launch_bounds__(kBlock) void rowptr_check_kernel(int32_t n, int64_t nnz,
-                                                              const int64_t* __restrict__ rp,
-                                                              int32_t* __restrict__ flag) {
-    int32_t bad = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i <= n;
-         i += (int64_t)gridDim.x * kBlock) {
-        const int64_t r = rp[i];
-        if ((i == 0 && r != 0) || (i == n && r != nnz) || r < 0 || r > nnz ||
-            (i > 0 && rp[i - 1] > r))
-            bad = 16;
-    }
-    if (bad) atomicOr(flag, bad);
-}
-
-// Roots (label[v] == v) counted per workgroup into partial[blockIdx.x].
-__global__ __launch_bounds__(kBlock) void count_roots_kernel(int32_t n,
-                                                             const int32_t* __restrict__ label,
-                                                             unsigned long long* __restrict__ partial) {
-    __shared__ int64_t s_red[kWaves];
-    int64_t c = 0;
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock)
-        c += label[v] == (int32_t)v ? 1 : 0;
-    const int64_t tot = block_sum<int64_t>(c, s_red);
-    if (threadIdx.x == 0) partial[blockIdx.x] = (unsigned long long)tot;
-}
-
-// total = partial[0] + ... + partial[count - 1] (one workgroup, fixed order).
-__global__ __launch_bounds__(kBlock) void sum_partials_kernel(const unsigned long long* __restrict__ partial,
-                                                              int count,
-                                                              unsigned long long* __restrict__ total) {
-    __shared__ int64_t s_red[kWaves];
-    int64_t c = 0;
-    for (int i = threadIdx.x; i < count; i += kBlock) c += (int64_t)partial[i];
-    const int64_t tot = block_sum<int64_t>(c, s_red);
-    if (threadIdx.x == 0) *total = (unsigned long long)tot;
-}
-
-// Reads an int32 flag word of the scratch (synchronises the stream).
-static int read_flag(const unsigned long long* word, hipStream_t s, int32_t* out) {
-    GILA_HIP(hipMemcpyAsync(out, word, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    GILA_HIP(hipStreamSynchronize(s));
-    return GILA_OK;
-}
-
 static int components_noalloc(const gila_csr* g, int32_t* label, int32_t* count_out,
                               hipStream_t s) {
     if (!g) return fail(GILA_EINVAL, "graph is NULL");
@@ -792,50 +1026,23 @@ static int components_noalloc(const gila_csr* g, int32_t* label, int32_t* count_
         if (count_out) *count_out = 0;
         return GILA_OK;
     }
-    int32_t* csr_flag = reinterpret_cast<int32_t*>(w);
-    int32_t* hooked = reinterpret_cast<int32_t*>(w + 1);
+    CsrCheck* check = reinterpret_cast<CsrCheck*>(w);
     unsigned long long* partial = w + kNoAllocHeader;
     hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(64), 0, s, w, kNoAllocHeader);
-    hipLaunchKernelGGL(rowptr_check_kernel, dim3(grid_for((int64_t)n + 1)), dim3(kBlock), 0, s, n,
-                       nnz, g->row_ptr, csr_flag);
-    GILA_HIP(hipGetLastError());
-    int32_t flag = 0;
-    GILA_TRY(read_flag(w, s, &flag));
-    if (flag) return fail(GILA_EINVAL, "row_ptr must run from 0 to nnz without decreasing");
-    if (nnz > 0) {
-        GILA_TRY(launch_validate_csr(n, nnz, g->row_ptr, g->col_idx, csr_flag, s));
-        GILA_TRY(read_flag(w, s, &flag));
-        if (flag)
-            return fail(GILA_EINVAL, "malformed CSR:%s%s%s%s", (flag & 1) ? " column out of range" : "",
-                        (flag & 2) ? " self-loop" : "", (flag & 4) ? " row not strictly ascending" : "",
-                        (flag & 8) ? " not symmetric" : "");
-    }
-    // the labelling passes of label_components, with the hooked flag in scratch
-    hipLaunchKernelGGL(cc_init_kernel, dim3(grid_for(n)), dim3(kBlock), 0, s, n, label);
-    GILA_HIP(hipGetLastError());
-    if (nnz > 0) {
-        const int hgrid =
-            (int)std::max<int64_t>(1, std::min<int64_t>(16384, ((int64_t)n + kWaves - 1) / kWaves));
-        for (int pass = 0;; ++pass) {
-            if (pass > 4096) return fail(GILA_EDEVICE, "component labels did not settle");
-            hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(64), 0, s, w + 1, 1);
-            hipLaunchKernelGGL(cc_hook_kernel, dim3(hgrid), dim3(kBlock), 0, s, n, g->row_ptr,
-                               g->col_idx, label, hooked);
-            hipLaunchKernelGGL(cc_compress_kernel, dim3(grid_for(n)), dim3(kBlock), 0, s, n, label);
-            GILA_HIP(hipGetLastError());
-            int32_t changed = 0;
-            GILA_TRY(read_flag(w + 1, s, &changed));
-            if (!changed) break;
-        }
-    }
+    GILA_TRY(launch_rowptr_check(n, nnz, g->row_ptr, check, s));
+    GILA_TRY(launch_validate_csr(n, nnz, g->row_ptr, g->col_idx, check, s));
+    CsrCheck found;
+    GILA_HIP(hipMemcpyAsync(&found, check, sizeof(found), hipMemcpyDeviceToHost, s));
+    GILA_HIP(hipStreamSynchronize(s));
+    if (found.flag & (16 | 32))
+        return fail(GILA_EINVAL, "row_ptr must run from 0 to nnz without decreasing");
+    GILA_TRY(entries_status(found, ""));
+    GILA_TRY(enqueue_labels(g, label, reinterpret_cast<int32_t*>(w + 3), s));
     if (count_out) {
         // every component has exactly one root (its smallest id)
-        const int cgrid = (int)std::min<int64_t>(kNoAllocPartials, ((int64_t)n + kBlock - 1) / kBlock);
-        hipLaunchKernelGGL(count_roots_kernel, dim3(cgrid), dim3(kBlock), 0, s, n, label, partial);
-        hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(kBlock), 0, s, partial, cgrid, w + 2);
-        GILA_HIP(hipGetLastError());
+        GILA_TRY(enqueue_count_roots(n, label, partial, w + 4, s));
         unsigned long long c = 0;
-        GILA_HIP(hipMemcpyAsync(&c, w + 2, sizeof(c), hipMemcpyDeviceToHost, s));
+        GILA_HIP(hipMemcpyAsync(&c, w + 4, sizeof(c), hipMemcpyDeviceToHost, s));
         GILA_HIP(hipStreamSynchronize(s));
         *count_out = (int32_t)c;
     }
@@ -863,9 +1070,17 @@ int gila_components(const gila_csr* g_dev, int32_t* label_dev, int32_t* count_ou
     if (g_dev->n > 0 && !label_dev) return fail(GILA_EINVAL, "label_dev is NULL");
     GILA_TRY(label_components(g_dev, label_dev, s));
     if (count_out) {
-        CompOrder o(s);
-        GILA_TRY(order_components(g_dev->n, label_dev, s, o));
-        *count_out = o.C;
+        *count_out = 0;
+        if (g_dev->n > 0) {
+            Buf partial(s);
+            GILA_TRY(partial.alloc<unsigned long long>(kCountPartials + 1));
+            unsigned long long* total = partial.as<unsigned long long>() + kCountPartials;
+            GILA_TRY(enqueue_count_roots(g_dev->n, label_dev, partial.as<unsigned long long>(), total, s));
+            unsigned long long c = 0;
+            GILA_HIP(hipMemcpyAsync(&c, total, sizeof(c), hipMemcpyDeviceToHost, s));
+            GILA_HIP(hipStreamSynchronize(s));
+            *count_out = (int32_t)c;
+        }
     }
     GILA_HIP(hipStreamSynchronize(s));
     return GILA_OK;
@@ -882,22 +1097,8 @@ int gila_pack_components(int32_t n, const int32_t* label_dev, double gap, int32_
         return fail(GILA_EINVAL, "unknown precision %d", precision);
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GILA_OK;
-    {
-        Buf bad(s);
-        GILA_TRY(bad.alloc<int32_t>(1));
-        GILA_HIP(hipMemsetAsync(bad.p, 0, sizeof(int32_t), s));
-        hipLaunchKernelGGL(check_labels_kernel, dim3(grid_for(n)), dim3(kBlock), 0, s, n, label_dev,
-                           bad.as<int32_t>());
-        GILA_HIP(hipGetLastError());
-        int32_t b = 0;
-        GILA_HIP(hipMemcpyAsync(&b, bad.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        GILA_HIP(hipStreamSynchronize(s));
-        if (b) return fail(GILA_EINVAL, "labels must lie in [0, n) and name a vertex labelled with itself");
-    }
-    CompOrder o(s);
-    GILA_TRY(order_components(n, label_dev, s, o));
-    if (precision == GILA_FP64) GILA_TRY(pack_positions<double2>(n, o, gap, (double2*)pos_dev, s));
-    else GILA_TRY(pack_positions<float2>(n, o, gap, (float2*)pos_dev, s));
+    if (precision == GILA_FP64) GILA_TRY(pack_positions<double2>(n, label_dev, gap, (double2*)pos_dev, s));
+    else GILA_TRY(pack_positions<float2>(n, label_dev, gap, (float2*)pos_dev, s));
     GILA_HIP(hipStreamSynchronize(s));
     return GILA_OK;
 }

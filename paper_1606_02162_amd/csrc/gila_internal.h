@@ -316,9 +316,21 @@ int plan_iteration(gila_khop* kh, const std::vector<int64_t>& counts_internal,
 int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out);
 void free_khop(gila_khop* kh, Release rel = Release{});
 int run_bfs(bool fill, int device, hipStream_t s, BfsArgs a);
-int launch_validate_csr(int32_t n, int64_t nnz, const int64_t* rp, const int32_t* ci, int32_t* flag,
-                        hipStream_t s);
-int validate_graph(const gila_csr* g, hipStream_t s);
+// What the checks of a CSR on the device found (zeroed before they run).
+struct CsrCheck {
+    int32_t flag;              // 1, 2, 4, 8: the entries' rules; 16, 32: the row pointers'
+    int32_t active;            // non-empty rows
+    unsigned long long near;   // entries shorter than the window asked for
+    int64_t balance;           // 0 when entries and mirrors pair up (see validate_csr_kernel)
+};
+// the row pointers' rules, then the entries' (which reads no row while the
+// former found the row pointers bad)
+int launch_rowptr_check(int32_t n, int64_t nnz, const int64_t* rp, CsrCheck* check, hipStream_t s);
+int launch_validate_csr(int32_t n, int64_t nnz, const int64_t* rp, const int32_t* ci,
+                        CsrCheck* check, hipStream_t s, int32_t window = 0);
+// GILA_EINVAL with a message naming what was found, or GILA_OK
+int entries_status(const CsrCheck& c, const char* where);
+int validate_graph(const gila_csr* g, hipStream_t s, int32_t window = 0, CsrCheck* out = nullptr);
 // implemented in util.hip: out[0] = 0, out[i + 1] = in[0] + ... + in[i]
 // (in != out).  The enqueue variant needs scan_workspace_count(n) int64 of
 // workspace and does not synchronise; the other allocates and synchronises.
@@ -326,14 +338,24 @@ int exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t s
 int64_t scan_workspace_count(int64_t n);
 int enqueue_exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* ws,
                                hipStream_t s);
-// implemented in segment.hip
-int build_segments(gila_khop* kh, int precision, hipStream_t s);
 // Stable sort of the ids 0 .. n-1 by key (ascending; equal keys keep
 // ascending ids) into out[n], ordered on `s`: LSD counting-sort passes of
 // 11-bit digits over the bits of max_key (every key <= max_key).  Scratch is
 // released into the block cache after the work on `s`.
 int stable_order_by_key(int32_t n, const uint32_t* key, uint32_t max_key, int32_t* out,
                         hipStream_t s);
+// One such pass: out = the elements perm[0 .. T) (0 .. T-1 when perm is null)
+// ordered by the digit (key[element] >> shift) & mask < nkeys, equal digits in
+// input order, in tiles of tj elements (a multiple of 64; counting_tile).
+// hist holds ceil(T / tj) * nkeys words, hscan one more -- afterwards the
+// first output position of (digit d, tile t) at d * ntiles + t -- and ws the
+// scan's workspace for that many.  Enqueued on `s`.
+int64_t counting_tile(int64_t T, int32_t nkeys);
+int stable_counting_pass(int64_t T, int64_t tj, int32_t nkeys, const uint32_t* key, int shift,
+                         uint32_t mask, const int32_t* perm, int32_t* out, int64_t* hist,
+                         int64_t* hscan, int64_t* ws, hipStream_t s);
+// implemented in segment.hip
+int build_segments(gila_khop* kh, int precision, hipStream_t s);
 void free_segments(gila_khop* kh, Release rel = Release{});
 // span: null, or where the force kernel records its start and end (SegArgs)
 int launch_segment_step(const gila_khop* kh, int precision, const StepArgs& a, hipStream_t s,

@@ -173,120 +173,6 @@ __global__ __launch_bounds__(kBlock) void slice_rows_kernel(SliceBuild b) {
     }
 }
 
-// Stable counting sort of a sequence of slices by an integer key in
-// [0, nkeys), in tiles of `tj` consecutive elements.  Element i of the input
-// is slice perm[i] (slice i when perm is null); its key is key[perm[i]].
-// Pass 1: per-tile histogram, stored key-major (hist[key * ntiles + tile]) so
-// that its exclusive prefix sum is the first output position of each
-// (key, tile).
-__device__ __forceinline__ int64_t sort_elem(const int32_t* perm, int64_t i) {
-    return perm ? perm[i] : i;
-}
-
-__global__ __launch_bounds__(kBlock) void slice_hist_kernel(int64_t T, int64_t tj, int64_t ntiles,
-                                                            int32_t nkeys,
-                                                            const int32_t* __restrict__ key,
-                                                            const int32_t* __restrict__ perm,
-                                                            int64_t* __restrict__ hist) {
-    extern __shared__ int32_t s_cnt[];
-    for (int s = threadIdx.x; s < nkeys; s += kBlock) s_cnt[s] = 0;
-    __syncthreads();
-    const int64_t j0 = (int64_t)blockIdx.x * tj;
-    const int64_t j1 = j0 + tj < T ? j0 + tj : T;
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += kBlock) atomicAdd(&s_cnt[key[sort_elem(perm, j)]], 1);
-    __syncthreads();
-    for (int s = threadIdx.x; s < nkeys; s += kBlock) hist[(int64_t)s * ntiles + blockIdx.x] = s_cnt[s];
-}
-
-// Pass 2 (one wavefront per tile): walk the tile in order, 64 elements at a
-// time; equal keys within a step are ranked by lane, so elements with equal
-// keys keep their input order.  out[position] = slice.
-__global__ __launch_bounds__(64) void slice_scatter_kernel(int64_t T, int64_t tj, int64_t ntiles,
-                                                           int32_t nkeys,
-                                                           const int32_t* __restrict__ key,
-                                                           const int32_t* __restrict__ perm,
-                                                           const int64_t* __restrict__ base,
-                                                           int32_t* __restrict__ out) {
-    extern __shared__ int32_t s_next[];
-    const int lane = threadIdx.x;
-    for (int s = lane; s < nkeys; s += 64) s_next[s] = (int32_t)base[(int64_t)s * ntiles + blockIdx.x];
-    __syncthreads();
-    const int64_t j0 = (int64_t)blockIdx.x * tj;
-    const int64_t j1 = j0 + tj < T ? j0 + tj : T;
-    for (int64_t c = j0; c < j1; c += 64) {
-        const int64_t j = c + lane;
-        const bool valid = j < j1;
-        const int64_t e = valid ? sort_elem(perm, j) : 0;
-        const int32_t s = valid ? key[e] : -1;
-        int rank = 0, same = 0;
-        for (int l = 0; l < 64; ++l) {
-            const int32_t sl = __builtin_amdgcn_readlane(s, l);
-            same += sl == s ? 1 : 0;
-            rank += (sl == s && l < lane) ? 1 : 0;
-        }
-        const int32_t at = valid ? s_next[s] : 0;
-        __syncthreads();
-        if (valid) {
-            out[at + rank] = (int32_t)e;
-            if (rank == same - 1) s_next[s] = at + same;
-        }
-        __syncthreads();
-    }
-}
-
-// One 11-bit digit of each element's key, for the LSD passes below.
-constexpr int kOrderDigitBits = 11;
-__global__ __launch_bounds__(kBlock) void key_digit_kernel(int32_t n, const uint32_t* __restrict__ key,
-                                                           int shift, int32_t* __restrict__ digit) {
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock)
-        digit[v] = (int32_t)((key[v] >> shift) & ((1u << kOrderDigitBits) - 1u));
-}
-
-int stable_order_by_key(int32_t n, const uint32_t* key, uint32_t max_key, int32_t* out,
-                        hipStream_t s) {
-    if (n <= 0) return GILA_OK;
-    int passes = 1;
-    while (passes * kOrderDigitBits < 32 && (max_key >> (passes * kOrderDigitBits)) > 0) ++passes;
-    const int32_t nkeys_max = 1 << kOrderDigitBits;
-    const int64_t tj = std::max<int64_t>(1024, ((int64_t)n * nkeys_max + (1 << 24) - 1) >> 24);
-    const int64_t ntiles = (n + tj - 1) / tj;
-    const int64_t H = ntiles * nkeys_max;
-    struct Tmp {
-        void* p = nullptr;
-        hipStream_t s;
-        ~Tmp() { dfree_on(p, s); }
-    } digit{nullptr, s}, buf{nullptr, s}, hist{nullptr, s}, hscan{nullptr, s}, ws{nullptr, s};
-    GILA_TRY(dalloc_t(reinterpret_cast<int32_t**>(&digit.p), (size_t)n));
-    GILA_TRY(dalloc_t(reinterpret_cast<int32_t**>(&buf.p), (size_t)n));
-    GILA_TRY(dalloc_t(reinterpret_cast<int64_t**>(&hist.p), (size_t)H));
-    GILA_TRY(dalloc_t(reinterpret_cast<int64_t**>(&hscan.p), (size_t)H + 1));
-    GILA_TRY(dalloc_t(reinterpret_cast<int64_t**>(&ws.p), (size_t)scan_workspace_count(H)));
-    const unsigned grid = (unsigned)std::min<int64_t>(4096, ((int64_t)n + kBlock - 1) / kBlock);
-    // the last pass writes `out`; earlier ones alternate so that it does
-    const int32_t* src = nullptr;
-    for (int p = 0; p < passes; ++p) {
-        const int shift = p * kOrderDigitBits;
-        const int32_t nkeys = (int32_t)std::min<uint64_t>((uint64_t)nkeys_max, ((uint64_t)max_key >> shift) + 1);
-        int32_t* dst = ((passes - 1 - p) & 1) ? static_cast<int32_t*>(buf.p) : out;
-        hipLaunchKernelGGL(key_digit_kernel, dim3(grid), dim3(kBlock), 0, s, n, key, shift,
-                           static_cast<int32_t*>(digit.p));
-        const size_t lds = sizeof(int32_t) * (size_t)nkeys;
-        hipLaunchKernelGGL(slice_hist_kernel, dim3((unsigned)ntiles), dim3(kBlock), lds, s, (int64_t)n,
-                           tj, ntiles, nkeys, static_cast<const int32_t*>(digit.p), src,
-                           static_cast<int64_t*>(hist.p));
-        GILA_HIP(hipGetLastError());
-        GILA_TRY(enqueue_exclusive_scan_i64(static_cast<int64_t*>(hist.p), static_cast<int64_t*>(hscan.p),
-                                            ntiles * nkeys, static_cast<int64_t*>(ws.p), s));
-        hipLaunchKernelGGL(slice_scatter_kernel, dim3((unsigned)ntiles), dim3(64), lds, s, (int64_t)n, tj,
-                           ntiles, nkeys, static_cast<const int32_t*>(digit.p), src,
-                           static_cast<const int64_t*>(hscan.p), dst);
-        GILA_HIP(hipGetLastError());
-        src = dst;
-    }
-    return GILA_OK;
-}
-
 // Length key of each slice: dense slices (at least dmin k-hop ids; dmin <= 0:
 // none) key 0, the others by their quads, more quads smaller keys (longest
 // first), clamped to keys 1 .. kLenKeys - 1.  Within a segment the dense
@@ -989,13 +875,8 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     // --- slices ordered by segment, then by length (longest first), then
     // row: two stable counting sorts (length, then segment).  Groups of
     // lanes in one wavefront then walk slices of about the same length.
-    auto tiling = [&](int32_t nkeys, int64_t& tj, int64_t& ntiles) {
-        tj = std::max<int64_t>(1024, (T * (int64_t)nkeys + (1 << 24) - 1) >> 24);
-        ntiles = (T + tj - 1) / tj;
-    };
-    int64_t tj1, nt1, tj2, nt2;
-    tiling(kLenKeys, tj1, nt1);
-    tiling(nseg, tj2, nt2);
+    const int64_t tj1 = counting_tile(T, kLenKeys), nt1 = (T + tj1 - 1) / tj1;
+    const int64_t tj2 = counting_tile(T, nseg), nt2 = (T + tj2 - 1) / tj2;
     const int64_t H = std::max(nt1 * kLenKeys, nt2 * nseg);
     const size_t ws = (size_t)std::max(scan_workspace_count(H), scan_workspace_count(T));
     // Dense slices (FP32 positions): a k-hop slice with at least
@@ -1053,26 +934,10 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     const unsigned tgrid = (unsigned)((T + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(slice_lenkey_kernel, dim3(tgrid), dim3(kBlock), 0, st, T, b.d_kn, dmin, lenkey);
     GILA_HIP(hipGetLastError());
-    auto counting_sort = [&](int32_t nkeys, int64_t tj, int64_t ntiles, const int32_t* key,
-                             const int32_t* perm, int32_t* out) -> int {
-        const size_t lds = sizeof(int32_t) * (size_t)nkeys;
-        if (lds > 48 * 1024) {
-            (void)quiet(hipFuncSetAttribute((const void*)slice_hist_kernel,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            (void)quiet(hipFuncSetAttribute((const void*)slice_scatter_kernel,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        }
-        hipLaunchKernelGGL(slice_hist_kernel, dim3((unsigned)ntiles), dim3(kBlock), lds, st, T, tj,
-                           ntiles, nkeys, key, perm, hist);
-        GILA_HIP(hipGetLastError());
-        GILA_TRY(enqueue_exclusive_scan_i64(hist, hscan, ntiles * nkeys, sws, st));
-        hipLaunchKernelGGL(slice_scatter_kernel, dim3((unsigned)ntiles), dim3(64), lds, st, T, tj,
-                           ntiles, nkeys, key, perm, hscan, out);
-        GILA_HIP(hipGetLastError());
-        return GILA_OK;
-    };
-    GILA_TRY(counting_sort(kLenKeys, tj1, nt1, lenkey, nullptr, order1));
-    GILA_TRY(counting_sort(nseg, tj2, nt2, b.d_seg, order1, order));
+    GILA_TRY(stable_counting_pass(T, tj1, kLenKeys, reinterpret_cast<const uint32_t*>(lenkey), 0,
+                                  ~0u, nullptr, order1, hist, hscan, sws, st));
+    GILA_TRY(stable_counting_pass(T, tj2, nseg, reinterpret_cast<const uint32_t*>(b.d_seg), 0, ~0u,
+                                  order1, order, hist, hscan, sws, st));
     const int64_t ntiles = nt2;  // hscan now holds the segment sort's offsets
     hipLaunchKernelGGL(slice_lengths_kernel, dim3((unsigned)((T + kBlock - 1) / kBlock)),
                        dim3(kBlock), 0, st, T, order, b.d_kn, b.d_an, dmin, wk, wa, dn);

@@ -94,6 +94,159 @@ int exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t s
     return GILA_OK;
 }
 
+// ------------------------------------------------------------------ stable counting pass
+// One pass of a stable counting sort by the digit (key >> shift) & mask in
+// [0, nkeys), in tiles of `tj` consecutive elements.  Element j of the input
+// is perm[j] (j itself when perm is null); key is indexed by element.
+// The per-tile histogram is stored digit-major (hist[digit * ntiles + tile]),
+// so that its exclusive prefix sum is the first output position of each
+// (digit, tile).
+__global__ __launch_bounds__(kBlock) void count_tiles_kernel(int64_t T, int64_t tj, int64_t ntiles,
+                                                             int32_t nkeys,
+                                                             const uint32_t* __restrict__ key,
+                                                             int shift, uint32_t mask,
+                                                             const int32_t* __restrict__ perm,
+                                                             int64_t* __restrict__ hist) {
+    extern __shared__ int32_t s_count[];
+    for (int s = threadIdx.x; s < nkeys; s += kBlock) s_count[s] = 0;
+    __syncthreads();
+    const int64_t j0 = (int64_t)blockIdx.x * tj;
+    const int64_t j1 = j0 + tj < T ? j0 + tj : T;
+    for (int64_t j = j0 + threadIdx.x; j < j1; j += kBlock)
+        atomicAdd(&s_count[(key[perm ? perm[j] : j] >> shift) & mask], 1);
+    __syncthreads();
+    for (int s = threadIdx.x; s < nkeys; s += kBlock) hist[(int64_t)s * ntiles + blockIdx.x] = s_count[s];
+}
+
+// W wavefronts per tile, each on a quarter (or all) of it in order, 64
+// elements a step.  Lanes with equal digits find each other by one ballot per
+// digit bit; an element's place is its digit's next one plus its rank among
+// the lower lanes.  Latency-bound (a tile is a chain of steps): one wavefront
+// per tile with a 64-step readlane ranking took 126 us a pass on 262144
+// elements (64 tiles), this 8 us (128 tiles of four wavefronts, 11 ballots
+// for 2048 digits).  W = 1 where W histograms of nkeys words do not fit in LDS.
+template <int W>
+__global__ __launch_bounds__(64 * W) void scatter_tiles_kernel(int64_t T, int64_t tj, int64_t ntiles,
+                                                               int32_t nkeys, int bits,
+                                                               const uint32_t* __restrict__ key,
+                                                               int shift, uint32_t mask,
+                                                               const int32_t* __restrict__ perm,
+                                                               const int64_t* __restrict__ base,
+                                                               int32_t* __restrict__ out) {
+    extern __shared__ int32_t s_next[];  // [W][nkeys]
+    const int lane = lane64(), w = wave_id();
+    const int64_t j0 = (int64_t)blockIdx.x * tj;
+    const int64_t j1 = j0 + tj < T ? j0 + tj : T;
+    const int64_t part = (tj / W + 63) / 64 * 64;  // W * part >= tj
+    const int64_t w0 = min(j0 + w * part, j1), w1 = min(w0 + part, j1);
+    int32_t* mine = s_next + (size_t)w * nkeys;
+    if constexpr (W > 1) {
+        for (int s = threadIdx.x; s < nkeys * W; s += 64 * W) s_next[s] = 0;
+        __syncthreads();
+        for (int64_t j = w0 + lane; j < w1; j += 64)
+            atomicAdd(&mine[(key[perm ? perm[j] : j] >> shift) & mask], 1);
+        __syncthreads();
+    }
+    // first place of each digit for each wavefront
+    for (int s = threadIdx.x; s < nkeys; s += 64 * W) {
+        int32_t at = (int32_t)base[(int64_t)s * ntiles + blockIdx.x];
+        for (int q = 0; q < W; ++q) {
+            const int32_t c = W > 1 ? s_next[(size_t)q * nkeys + s] : 0;
+            s_next[(size_t)q * nkeys + s] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+    const uint64_t below = (1ull << lane) - 1ull;
+    for (int64_t c = w0; c < w1; c += 64) {
+        const int64_t j = c + lane;
+        const bool valid = j < w1;
+        const int32_t e = valid ? (perm ? perm[j] : (int32_t)j) : 0;
+        const uint32_t d = valid ? (key[e] >> shift) & mask : 0u;
+        uint64_t same = __ballot(valid);
+        for (int b = 0; b < bits; ++b) {
+            const uint64_t on = __ballot((d >> b) & 1u);
+            same &= ((d >> b) & 1u) ? on : ~on;
+        }
+        if (valid) {
+            const int32_t at = mine[d];
+            out[at + __popcll(same & below)] = e;
+            // the last lane of each digit moves its next place
+            if ((same >> lane) == 1ull) mine[d] = at + __popcll(same);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+int64_t counting_tile(int64_t T, int32_t nkeys) {
+    // tiles of 2048, larger where the histogram would exceed 2^24 words
+    return std::max<int64_t>(2048, ((T * nkeys + (1 << 24) - 1) >> 24) + 63) / 64 * 64;
+}
+
+int stable_counting_pass(int64_t T, int64_t tj, int32_t nkeys, const uint32_t* key, int shift,
+                         uint32_t mask, const int32_t* perm, int32_t* out, int64_t* hist,
+                         int64_t* hscan, int64_t* ws, hipStream_t s) {
+    if (T <= 0) return GILA_OK;
+    const int64_t ntiles = (T + tj - 1) / tj;
+    const size_t one = sizeof(int32_t) * (size_t)nkeys;
+    constexpr size_t kPlain = 48 * 1024;  // more needs the kernel's limit raised
+    int bits = 0;
+    while ((1 << bits) < nkeys) ++bits;
+    if (one > kPlain) {
+        (void)quiet(hipFuncSetAttribute((const void*)count_tiles_kernel,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)one));
+        (void)quiet(hipFuncSetAttribute((const void*)scatter_tiles_kernel<1>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)one));
+    }
+    hipLaunchKernelGGL(count_tiles_kernel, dim3((unsigned)ntiles), dim3(kBlock), one, s, T, tj, ntiles,
+                       nkeys, key, shift, mask, perm, hist);
+    GILA_HIP(hipGetLastError());
+    GILA_TRY(enqueue_exclusive_scan_i64(hist, hscan, ntiles * nkeys, ws, s));
+    if (4 * one <= kPlain)
+        hipLaunchKernelGGL(scatter_tiles_kernel<4>, dim3((unsigned)ntiles), dim3(256), 4 * one, s, T, tj,
+                           ntiles, nkeys, bits, key, shift, mask, perm, hscan, out);
+    else
+        hipLaunchKernelGGL(scatter_tiles_kernel<1>, dim3((unsigned)ntiles), dim3(64), one, s, T, tj,
+                           ntiles, nkeys, bits, key, shift, mask, perm, hscan, out);
+    GILA_HIP(hipGetLastError());
+    return GILA_OK;
+}
+
+int stable_order_by_key(int32_t n, const uint32_t* key, uint32_t max_key, int32_t* out,
+                        hipStream_t s) {
+    if (n <= 0) return GILA_OK;
+    constexpr int kDigitBits = 11;
+    constexpr uint32_t kMask = (1u << kDigitBits) - 1u;
+    int passes = 1;
+    while (passes * kDigitBits < 32 && (max_key >> (passes * kDigitBits)) > 0) ++passes;
+    const int64_t tj = counting_tile(n, 1 << kDigitBits);
+    const int64_t H = (n + tj - 1) / tj * (1 << kDigitBits);
+    const size_t hb = ((size_t)H * 8 + 255) & ~(size_t)255;
+    const size_t sb = ((size_t)(H + 1) * 8 + 255) & ~(size_t)255;
+    const size_t wb = ((size_t)scan_workspace_count(H) * 8 + 255) & ~(size_t)255;
+    struct Tmp {
+        void* p = nullptr;
+        hipStream_t s;
+        ~Tmp() { dfree_on(p, s); }
+    } mem{nullptr, s};
+    GILA_TRY(dalloc(&mem.p, hb + sb + wb + sizeof(int32_t) * (size_t)n));
+    char* at = static_cast<char*>(mem.p);
+    int64_t* hist = reinterpret_cast<int64_t*>(at);
+    int64_t* hscan = reinterpret_cast<int64_t*>(at + hb);
+    int64_t* ws = reinterpret_cast<int64_t*>(at + hb + sb);
+    int32_t* buf = reinterpret_cast<int32_t*>(at + hb + sb + wb);
+    // the last pass writes `out`; earlier ones alternate so that it does
+    const int32_t* src = nullptr;
+    for (int p = 0; p < passes; ++p) {
+        const int shift = p * kDigitBits;
+        const int32_t nkeys = (int32_t)std::min<uint64_t>(1u << kDigitBits, ((uint64_t)max_key >> shift) + 1);
+        int32_t* dst = ((passes - 1 - p) & 1) ? buf : out;
+        GILA_TRY(stable_counting_pass(n, tj, nkeys, key, shift, kMask, src, dst, hist, hscan, ws, s));
+        src = dst;
+    }
+    return GILA_OK;
+}
+
 static double wall_s() {
     return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch())
         .count();

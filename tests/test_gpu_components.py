@@ -214,3 +214,32 @@ def test_empty_graph(G):
     assert c == 0 and len(runs) == 0
     m = G.drawing_metrics(rp, ci, G.FP64, pos)
     assert m.edges == 0 and m.crossings == 0 and m.similarity == 1.0 and m.gabriel_edges == 0
+
+
+def _edge_graphs():
+    """Shapes at the edges of the labelling and packing kernels: long parent
+    chains in id order, components of about one tile (2048) and one wavefront,
+    several large components (no single most frequent label), stars whose
+    rows are walked by whole wavefronts, and one vertex."""
+    return [inputs.to_csr(1, [], []),
+            inputs.path_graph(20011),
+            inputs.to_csr(4099, np.arange(4098)[::-1], np.arange(1, 4099)[::-1], name="path_back"),
+            _relabel(_union(*[inputs.cycle_graph(s) for s in (2047, 2048, 2049, 3, 63, 64, 65)]), 3),
+            _union(inputs.grid_graph(60, 60), inputs.grid_graph(60, 61), inputs.grid_graph(61, 60)),
+            _relabel(_union(*[inputs.star_graph(s) for s in (1, 2, 9, 10, 64, 700, 3000)]), 4)]
+
+
+@pytest.mark.parametrize("i", range(6))
+def test_labels_and_pack_at_kernel_edges(G, i):
+    import torch
+    g = _edge_graphs()[i]
+    print(f"edge graph {i} n={g.n}", flush=True)
+    rp, ci = G.to_device_csr(g)
+    label, count = G.components(rp, ci)
+    ol, oc = oracle.components(g.n, g.row_ptr, g.col_idx)
+    assert count == oc and np.array_equal(label.cpu().numpy(), ol)
+    x = inputs.uniform_positions(g.n, seed=8, width=700.0, height=400.0) - 350.0
+    pos = torch.from_numpy(x).cuda()
+    G.pack_components(label, 3.25, G.FP64, pos)
+    # the same comparisons and sums in the same order: the same bits
+    assert np.array_equal(pos.cpu().numpy(), oracle.pack(ol, 3.25, x))
