@@ -10,17 +10,22 @@
 //
 //   edge_list_kernel      edges {u, v}, u < v, in row order (the part of a
 //                         sorted row above v is a suffix found by bisection)
-//   crossings_kernel      an edge per thread against a chunk of edges
-//                         streamed through LDS (each entry: end points and
-//                         line coefficients); per pair four filtered signs
-//                         decided by wavefront lane masks on the scalar unit;
-//                         each pair once for the total, or both ways for
-//                         per-edge counts
+//   cross_*_kernel        edges sorted by the place of their two ends (on a
+//                         four-dimensional Hilbert curve) and cut into groups
+//                         of 64 with a box around the left ends and one
+//                         around the right ends
+//   crossings_kernel      wavefront per group, an edge per lane, against a
+//                         range of groups: boxes apart, nothing; else every
+//                         edge of the other group, one per lane, against this
+//                         group's boxes (no edge of it can be crossed, all of
+//                         them are, or neither is sure); and only the unsure
+//                         ones against each of the 64 edges, by filtered
+//                         signs
 //   lengths kernels       per-edge length, fixed-order sums (mean, then the
 //                         squared deviations)
 //   grid kernels          points binned into a uniform grid (about two per
 //                         cell)
-//   gabriel_degree_kernel thread per point u (in cell order): rings of cells
+//   gabriel_degree_kernel a few lanes per point u (in cell order): rings of cells
 //                         around u until each of the eight 45-degree octants
 //                         around u is settled: the nearest point w found in it
 //                         blocks everything at squared distance >= 2 |w - u|^2
@@ -63,8 +68,8 @@ int mgrid(int64_t items) {
 }
 }  // namespace
 
-constexpr int kCrossTile = 256;         // edges per LDS tile of the crossing kernel
-constexpr int64_t kGabrielBudget = 2048;  // cells and points one thread visits for a point
+constexpr int kGabrielLanes = 8;          // lanes that share one point's search
+constexpr int64_t kGabrielBudget = 512;   // cells and points one of them visits for a point
 
 // ------------------------------------------------------------------ points and edges
 template <class V>
@@ -145,43 +150,167 @@ __device__ __noinline__ int orient_exact(float ax, float ay, float bx, float by,
 }
 
 // ------------------------------------------------------------------ crossings
-// A segment's line in the form used by the sign filter: for a point x,
-// orient(p0, p1, x) = dx x.y - dy x.x - k, evaluated in double.  Its rounding
-// error is below 4u(|dx| |x.y| + |dy| |x.x|) + 2u(|x1 y0| + |y1 x0|) plus
+constexpr int kCrossGroup = 64;           // edges per group: one per lane
+constexpr int64_t kCrossSortMin = 4096;   // edges sorted by place from here on
+constexpr int64_t kCrossWaves = 262144;   // wavefronts to cut the group pairs into
+
+// A segment's line: for a point (x, y), orient(p0, p1, (x, y)) =
+// dx y - dy x - k, evaluated as fma(dx, y, fma(-dy, x, -k)).  Its rounding
+// error is below 2u |dx| |y| + 3u |dy| |x| + 3u (|x1 y0| + |y1 x0|) plus
 // second-order terms (u = 2^-53; coordinates are floats, so x1 y0 and y1 x0
 // are exact), hence below bnd = 8u((|dx| + |dy|) M + |x1 y0| + |y1 x0|) for
-// every point with coordinates of magnitude at most M.
+// every point with coordinates of magnitude at most M.  The line is scaled by
+// the power of two that brings bnd into [1/2, 1), which is exact, so a sign is
+// certain where the scaled value is at least 1 in magnitude.  A line with
+// bnd = 0 (all its values are 0) stays unscaled and is never certain.
 struct Line {
-    double dx, dy, k, bnd;
+    double dx, dy, k;
 };
 
-__device__ __forceinline__ Line make_line(float x0, float y0, float x1, float y1, double M) {
+__device__ __forceinline__ Line make_line(float4 z, double M) {
 #pragma clang fp contract(off)
     Line L;
-    L.dx = (double)x1 - (double)x0;
-    L.dy = (double)y1 - (double)y0;
-    const double s = (double)x1 * y0, t = (double)y1 * x0;
-    L.k = s - t;
-    L.bnd = ((fabs(L.dx) + fabs(L.dy)) * M + (fabs(s) + fabs(t))) * 0x1p-50;
+    L.dx = (double)z.z - (double)z.x;
+    L.dy = (double)z.w - (double)z.y;
+    const double s = (double)z.z * z.y, u = (double)z.w * z.x;
+    L.k = s - u;
+    const double bnd = ((fabs(L.dx) + fabs(L.dy)) * M + (fabs(s) + fabs(u))) * 0x1p-50;
+    if (bnd > 0.0) {
+        int ex = 0;
+        (void)frexp(bnd, &ex);
+        L.dx = ldexp(L.dx, -ex);
+        L.dy = ldexp(L.dy, -ex);
+        L.k = ldexp(L.k, -ex);
+    }
     return L;
 }
 
-// orient(p0, p1, (x, y)) up to rounding: its sign is certain where |d| > L.bnd
 __device__ __forceinline__ double side(const Line& L, double x, double y) {
-#pragma clang fp contract(off)
-    const double q = L.dy * x;
-    return fma(L.dx, y, -q) - L.k;
+    return fma(L.dx, y, fma(-L.dy, x, -L.k));
 }
 
-// One LDS entry: an edge's end points and line.
-struct alignas(16) CrossEntry {
-    double x0, y0, x1, y1;
-    Line L;
+// The unsure edges of the other group as the pair test reads them from LDS
+// (16-byte broadcasts: the ends, the direction, and two entries' k at once).
+struct CrossEntries {
+    double2 p0[kCrossGroup], p1[kCrossGroup], d[kCrossGroup];
+    alignas(16) double k[kCrossGroup];
+    int at[kCrossGroup];  // place in the group
 };
 
-constexpr int kCrossRows = 1;                         // edges per thread (64 VGPRs: 8 waves per SIMD)
-constexpr int kCrossBlock = kCrossRows * kCrossTile;  // edges per block
-constexpr int64_t kCrossChunk = 8192;                 // edges streamed per block (at least)
+// Filtered signs of one pair per lane: edge i of the lane, the entry's edge.
+// sure: all four signs are certain; cross: the ends of each lie on opposite
+// sides of the other's line (where sure).
+__device__ __forceinline__ void pair_masks(const Line& li, double ax, double ay, double bx, double by,
+                                           double2 p0, double2 p1, double2 d, double k,
+                                           uint64_t& sure, uint64_t& cross) {
+    const Line lc{d.x, d.y, k};
+    const double d1 = side(li, p0.x, p0.y);
+    const double d2 = side(li, p1.x, p1.y);
+    const double d3 = side(lc, ax, ay);
+    const double d4 = side(lc, bx, by);
+    const int w1 = __double2hiint(d1), w2 = __double2hiint(d2);
+    const int w3 = __double2hiint(d3), w4 = __double2hiint(d4);
+    // smallest magnitude, by the high words taken as floats (a double's high
+    // word orders as the double does)
+    float low;
+    asm("v_min3_f32 %0, |%1|, |%2|, |%3|" : "=v"(low) : "v"(w1), "v"(w2), "v"(w3));
+    asm("v_min_f32 %0, %1, |%2|" : "=v"(low) : "v"(low), "v"(w4));
+    constexpr float kOne = 1.875f;  // the high word of 1.0 as a float
+    sure = __builtin_amdgcn_ballot_w64(low >= kOne);
+    cross = __builtin_amdgcn_ballot_w64(((w1 ^ w2) & (w3 ^ w4)) < 0);
+}
+
+// A group's boxes: of its edges' left ends and of their right ends.
+struct alignas(32) CrossBox {
+    float px0, py0, px1, py1, qx0, qy0, qx1, qy1;
+};
+
+// bit b of an 8-bit value to bit 4 b
+__device__ __forceinline__ uint32_t spread4(uint32_t q) {
+    q = (q | (q << 12)) & 0x000F000Fu;
+    q = (q | (q << 6)) & 0x03030303u;
+    return (q | (q << 3)) & 0x11111111u;
+}
+
+// Place of a cell of the 256^4 grid on a four-dimensional Hilbert curve, by
+// the transposed form of J. Skilling, "Programming the Hilbert curve" (2004).
+// Consecutive places are neighbouring cells: boxes around 64 of them leave
+// 22% of R-MAT 17's pairs unsure, against 27% in Morton order.
+__device__ __forceinline__ uint32_t hilbert4(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3) {
+    uint32_t x[4] = {x0, x1, x2, x3};
+#pragma unroll
+    for (uint32_t q = 128u; q > 1u; q >>= 1) {
+        const uint32_t p = q - 1u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool on = x[i] & q;
+            const uint32_t t = on ? 0u : (x[0] ^ x[i]) & p;
+            x[0] ^= on ? p : t;
+            x[i] ^= t;
+        }
+    }
+#pragma unroll
+    for (int i = 1; i < 4; ++i) x[i] ^= x[i - 1];
+    uint32_t t = 0;
+#pragma unroll
+    for (uint32_t q = 128u; q > 1u; q >>= 1) t ^= (x[3] & q) ? q - 1u : 0u;
+    return (spread4(x[0] ^ t) << 3) | (spread4(x[1] ^ t) << 2) | (spread4(x[2] ^ t) << 1) | spread4(x[3] ^ t);
+}
+
+__device__ __forceinline__ bool left_first(float2 a, float2 b) {
+    return a.x < b.x || (a.x == b.x && a.y <= b.y);
+}
+
+// Place of (left end, right end) on the curve, eight bits per coordinate.
+__global__ __launch_bounds__(kBlock) void cross_key_kernel(int64_t m, const int2* __restrict__ ends,
+                                                           const float2* __restrict__ p, float2 lo,
+                                                           float2 scale, uint32_t* __restrict__ key) {
+    const auto cell = [](float x, float l, float s) {
+        const float c = (x - l) * s;  // (a NaN from an overflowing range lands in cell 0)
+        return c >= 255.f ? 255u : (c > 0.f ? (uint32_t)c : 0u);
+    };
+    for (int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x; e < m;
+         e += (int64_t)gridDim.x * kBlock) {
+        float2 a = p[ends[e].x], b = p[ends[e].y];
+        if (!left_first(a, b)) {
+            const float2 t = a;
+            a = b;
+            b = t;
+        }
+        key[e] = hilbert4(cell(a.x, lo.x, scale.x), cell(a.y, lo.y, scale.y), cell(b.x, lo.x, scale.x),
+                          cell(b.y, lo.y, scale.y));
+    }
+}
+
+// Wavefront per group: its edges' ends, left one (smaller x, then y) first,
+// and the group's boxes.  order: null for row order.
+__global__ __launch_bounds__(kBlock) void cross_prepare_kernel(int64_t m, int64_t groups,
+                                                               const int2* __restrict__ ends,
+                                                               const float2* __restrict__ p,
+                                                               const int32_t* __restrict__ order,
+                                                               float4* __restrict__ seg,
+                                                               CrossBox* __restrict__ box) {
+    const int64_t waves = (int64_t)gridDim.x * kWaves;
+    for (int64_t g = (int64_t)blockIdx.x * kWaves + wave_id(); g < groups; g += waves) {
+        const int64_t t = g * kCrossGroup + lane64();
+        const int64_t at = t < m ? t : m - 1;  // lanes past the end repeat the last edge in the box
+        const int2 e = ends[order ? (int64_t)order[at] : at];
+        float2 a = p[e.x], b = p[e.y];
+        if (!left_first(a, b)) {
+            const float2 q = a;
+            a = b;
+            b = q;
+        }
+        if (t < m) seg[t] = make_float4(a.x, a.y, b.x, b.y);
+        float lo[4] = {a.x, a.y, b.x, b.y}, hi[4] = {a.x, a.y, b.x, b.y};
+        for (int off = 32; off >= 1; off >>= 1)
+            for (int q = 0; q < 4; ++q) {
+                lo[q] = fminf(lo[q], __shfl_xor(lo[q], off, 64));
+                hi[q] = fmaxf(hi[q], __shfl_xor(hi[q], off, 64));
+            }
+        if (lane64() == 0) box[g] = CrossBox{lo[0], lo[1], hi[0], hi[1], lo[2], lo[3], hi[2], hi[3]};
+    }
+}
 
 // Exact crossing decision for a pair the filter could not settle.
 __device__ __forceinline__ int cross_exact(int2 ea, int2 ec, const float2* __restrict__ p) {
@@ -195,122 +324,190 @@ __device__ __forceinline__ int cross_exact(int2 ea, int2 ec, const float2* __res
     return o3 * o4 < 0 ? 1 : 0;
 }
 
-// The pairs (i, j) of one LDS tile for the edges a thread holds.  Lane
-// masks of the wavefront (one ballot per comparison, combined in scalar
-// registers) decide each pair: sure crossings of PAIRS_ONCE mode are counted
-// per wavefront (wcnt), other counts per lane (cnt).  DIAG: count j > i only.
-template <bool PAIRS_ONCE, bool DIAG>
-__device__ __forceinline__ void cross_tile(const CrossEntry* __restrict__ s_e, const int2* __restrict__ s_end,
-                                           int tn, int64_t t0, int64_t a0, const uint64_t (&live)[kCrossRows],
-                                           const double (&ax)[kCrossRows], const double (&ay)[kCrossRows],
-                                           const double (&bx)[kCrossRows], const double (&by)[kCrossRows],
-                                           const Line (&la)[kCrossRows], int (&cnt)[kCrossRows],
-                                           uint64_t& wcnt, const int2* __restrict__ ends,
-                                           const float2* __restrict__ p) {
-    const uint64_t me = 1ull << lane64();
-    for (int q = 0; q < tn; ++q) {
-        const CrossEntry c = s_e[q];
-#pragma unroll
-        for (int r = 0; r < kCrossRows; ++r) {
-            const int64_t i = a0 + r * kCrossTile + threadIdx.x;
-            const double d1 = side(la[r], c.x0, c.y0);
-            const double d2 = side(la[r], c.x1, c.y1);
-            const double d3 = side(c.L, ax[r], ay[r]);
-            const double d4 = side(c.L, bx[r], by[r]);
-            // the signs are certain where |d| > bnd; then |d| > bnd >= 2^-348
-            // (a float's nonzero difference or product is at least 2^-298 in
-            // magnitude), so the products below neither underflow nor overflow
-            const uint64_t sure = __builtin_amdgcn_ballot_w64(fabs(d1) > la[r].bnd) &
-                                  __builtin_amdgcn_ballot_w64(fabs(d2) > la[r].bnd) &
-                                  __builtin_amdgcn_ballot_w64(fabs(d3) > c.L.bnd) &
-                                  __builtin_amdgcn_ballot_w64(fabs(d4) > c.L.bnd);
-            const uint64_t cross = __builtin_amdgcn_ballot_w64(d1 * d2 < 0.0) &
-                                   __builtin_amdgcn_ballot_w64(d3 * d4 < 0.0);
-            const uint64_t keep = DIAG ? __builtin_amdgcn_ballot_w64(t0 + q > i) & live[r] : live[r];
-            if (PAIRS_ONCE)
-                wcnt += __popcll(sure & cross & keep);
-            else
-                cnt[r] += (sure & cross & keep & me) ? 1 : 0;
-            const uint64_t slow = ~sure & keep;
-            if (slow) [[unlikely]] {
-                if (slow & me) cnt[r] += cross_exact(ends[i], s_end[q], p);
+// Range of orient(p, q, z) over p in the box's left part, q in its right one:
+// (p - z) x (q - z), whose four factors vary independently, so the products'
+// ranges give it exactly (up to rounding).
+__device__ __forceinline__ void orient_range(const CrossBox& B, float zx, float zy, float& lo, float& hi) {
+    const float ux0 = B.px0 - zx, ux1 = B.px1 - zx, uy0 = B.py0 - zy, uy1 = B.py1 - zy;
+    const float wx0 = B.qx0 - zx, wx1 = B.qx1 - zx, wy0 = B.qy0 - zy, wy1 = B.qy1 - zy;
+    const float a0 = ux0 * wy0, a1 = ux0 * wy1, a2 = ux1 * wy0, a3 = ux1 * wy1;
+    const float b0 = uy0 * wx0, b1 = uy0 * wx1, b2 = uy1 * wx0, b3 = uy1 * wx1;
+    lo = fminf(fminf(fminf(a0, a1), a2), a3) - fmaxf(fmaxf(fmaxf(b0, b1), b2), b3);
+    hi = fmaxf(fmaxf(fmaxf(a0, a1), a2), a3) - fminf(fminf(fminf(b0, b1), b2), b3);
+}
+
+// What a group's boxes say of an edge (ends z0, z1): 0 it crosses none of the
+// group, 1 all of it, 2 unsure.  eps covers the rounding of every value
+// compared, so 0 and 1 are what the exact signs give for each edge of the
+// group: the values are sums of two products of coordinate differences, each
+// at most (2 M)^2, whose float evaluation errs by less than 2^-19 M^2.  (An
+// edge that shares an end with one of the group, or is one of it, is never
+// found to cross all: that orientation is 0.)
+__device__ __forceinline__ int group_verdict(const CrossBox& B, float4 z, float eps) {
+    if (fmaxf(z.x, z.z) < fminf(B.px0, B.qx0) || fminf(z.x, z.z) > fmaxf(B.px1, B.qx1) ||
+        fmaxf(z.y, z.w) < fminf(B.py0, B.qy0) || fminf(z.y, z.w) > fmaxf(B.py1, B.qy1))
+        return 0;
+    // the edge's line over the two boxes
+    const float dx = z.z - z.x, dy = z.w - z.y;
+    const auto side_range = [&](float x0, float x1, float y0, float y1, float& lo, float& hi) {
+        const float a0 = dx * (y0 - z.y), a1 = dx * (y1 - z.y);
+        const float b0 = dy * (x0 - z.x), b1 = dy * (x1 - z.x);
+        lo = fminf(a0, a1) - fmaxf(b0, b1);
+        hi = fmaxf(a0, a1) - fminf(b0, b1);
+    };
+    float pl, ph, ql, qh;
+    side_range(B.px0, B.px1, B.py0, B.py1, pl, ph);
+    side_range(B.qx0, B.qx1, B.qy0, B.qy1, ql, qh);
+    if ((pl > eps && ql > eps) || (ph < -eps && qh < -eps)) return 0;
+    float l0, h0, l1, h1;
+    orient_range(B, z.x, z.y, l0, h0);
+    orient_range(B, z.z, z.w, l1, h1);
+    if ((l0 > eps && l1 > eps) || (h0 < -eps && h1 < -eps)) return 0;
+    const bool apart = (pl > eps && qh < -eps) || (ph < -eps && ql > eps);
+    const bool across = (l0 > eps && h1 < -eps) || (h0 < -eps && l1 > eps);
+    return apart && across ? 1 : 2;
+}
+
+// Wavefront (group blockIdx.x * kWaves + wave, range blockIdx.y of `span`
+// groups): its 64 edges i, one per lane, against every edge j of the range.  A
+// crossing is a pair with no shared end whose ends lie strictly on opposite
+// sides of the other's line.  PAIRS_ONCE: only j > i in sorted order counts
+// (each crossing once, for the total); otherwise every j != i counts and
+// per_edge[] accumulates.
+//
+// Bound by the pair test (eight FMA, three operations on the high words for
+// certainty -- a double's high word orders as the double, and as a float
+// pattern -- and three for the signs, against 20 operations before, with four
+// conversions) and, about equally, by its three 16-byte LDS broadcasts; what
+// makes the difference is how few pairs reach it: a quarter on a smoothed
+// drawing of R-MAT 17 (groups' boxes apart for 56% of the pairs, 13% decided
+// by the boxes), 6% on a Watts-Strogatz graph's.  Reading the other edge
+// through the scalar cache instead of LDS left the loop waiting for its misses
+// (57 ms on R-MAT 17).
+template <bool PAIRS_ONCE>
+__global__ __launch_bounds__(kBlock, 6) void crossings_kernel(int64_t m, int64_t groups, int64_t span,
+                                                              double M, float eps,
+                                                              const float4* __restrict__ seg,
+                                                              const CrossBox* __restrict__ box,
+                                                              const int32_t* __restrict__ order,
+                                                              const int2* __restrict__ ends,
+                                                              const float2* __restrict__ p,
+                                                              unsigned long long* __restrict__ per_edge,
+                                                              unsigned long long* __restrict__ total) {
+    __shared__ CrossEntries s_entry[kWaves];
+    const int64_t g = (int64_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(wave_id());
+    int64_t h0 = (int64_t)blockIdx.y * span;
+    const int64_t h1 = min(h0 + span, groups);
+    if (g >= groups || (PAIRS_ONCE && h1 <= g)) return;
+    if (PAIRS_ONCE) h0 = max(h0, g);
+    const int lane = lane64();
+    CrossEntries& mine = s_entry[wave_id()];
+    const int64_t i = g * kCrossGroup + lane;
+    const uint64_t live = __ballot(i < m);
+    const float4 ei = seg[min(i, m - 1)];
+    const Line li = make_line(ei, M);
+    const double ax = ei.x, ay = ei.y, bx = ei.z, by = ei.w;
+    const auto id_of = [&](int64_t t) { return order ? (int64_t)order[t] : t; };
+    // the group's boxes are uniform: read through the scalar cache (written by
+    // an earlier launch)
+    typedef const __attribute__((address_space(4))) CrossBox* BoxPtr;
+    const BoxPtr bp = (BoxPtr)(box + g);
+    CrossBox B;
+    B.px0 = bp->px0;
+    B.py0 = bp->py0;
+    B.px1 = bp->px1;
+    B.py1 = bp->py1;
+    B.qx0 = bp->qx0;
+    B.qy0 = bp->qy0;
+    B.qx1 = bp->qx1;
+    B.qy1 = bp->qy1;
+    const float gx0 = fminf(B.px0, B.qx0), gx1 = fmaxf(B.px1, B.qx1);
+    const float gy0 = fminf(B.py0, B.qy0), gy1 = fmaxf(B.py1, B.qy1);
+    int64_t whole = 0;  // edges found to cross the whole group (uniform)
+    int64_t sure_cnt = 0;
+    int cnt = 0;
+    for (int64_t hb = h0; hb < h1; hb += 64) {
+        const int64_t h = hb + lane;
+        bool near = false;
+        if (h < h1) {
+            const CrossBox C = box[h];
+            near = fminf(C.px0, C.qx0) <= gx1 && fmaxf(C.px1, C.qx1) >= gx0 &&
+                   fminf(C.py0, C.qy0) <= gy1 && fmaxf(C.py1, C.qy1) >= gy0;
+        }
+        uint64_t todo = __ballot(near);
+        while (todo) {
+            const int64_t hj = hb + __builtin_ctzll(todo);
+            todo &= todo - 1ull;
+            const int64_t j0 = hj * kCrossGroup;
+            int verdict = 0;
+            float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (j0 + lane < m) {
+                z = seg[j0 + lane];
+                verdict = group_verdict(B, z, eps);
+            }
+            // (in its own group an edge is never found to cross all)
+            whole += __popcll(__ballot(verdict == 1));
+            const uint64_t open = __ballot(verdict == 2);
+            __builtin_amdgcn_wave_barrier();  // the previous group's entries have been read
+            if (verdict == 2) {
+                const Line lj = make_line(z, M);
+                const int at = __popcll(open & ((1ull << lane) - 1ull));
+                mine.p0[at] = make_double2(z.x, z.y);
+                mine.p1[at] = make_double2(z.z, z.w);
+                mine.d[at] = make_double2(lj.dx, lj.dy);
+                mine.k[at] = lj.k;
+                mine.at[at] = lane;
+            }
+            __builtin_amdgcn_wave_barrier();
+            const int count = __popcll(open);
+            const auto take = [&](uint64_t sure, uint64_t cross, uint64_t keep) {
+                const uint64_t yes = sure & cross & keep;
+                if (PAIRS_ONCE) sure_cnt += __popcll(yes);
+                else cnt += (int)((yes >> lane) & 1ull);
+            };
+            const auto settle = [&](uint64_t slow, int64_t at) {
+                if ((slow >> lane) & 1ull) cnt += cross_exact(ends[id_of(i)], ends[id_of(j0 + at)], p);
+            };
+            if (hj != g) {
+                // two entries a step: their reads and chains overlap
+                int q = 0;
+                for (; q + 1 < count; q += 2) {
+                    const double2 k = *reinterpret_cast<const double2*>(&mine.k[q]);
+                    uint64_t sure0, cross0, sure1, cross1;
+                    pair_masks(li, ax, ay, bx, by, mine.p0[q], mine.p1[q], mine.d[q], k.x, sure0, cross0);
+                    pair_masks(li, ax, ay, bx, by, mine.p0[q + 1], mine.p1[q + 1], mine.d[q + 1], k.y,
+                               sure1, cross1);
+                    take(sure0, cross0, live);
+                    take(sure1, cross1, live);
+                    if (~(sure0 & sure1) & live) [[unlikely]] {
+                        settle(~sure0 & live, mine.at[q]);
+                        settle(~sure1 & live, mine.at[q + 1]);
+                    }
+                }
+                if (q < count) {
+                    uint64_t sure, cross;
+                    pair_masks(li, ax, ay, bx, by, mine.p0[q], mine.p1[q], mine.d[q], mine.k[q], sure, cross);
+                    take(sure, cross, live);
+                    if (~sure & live) [[unlikely]] settle(~sure & live, mine.at[q]);
+                }
+            } else {
+                for (int q = 0; q < count; ++q) {  // i < j, or i != j
+                    const int at = __builtin_amdgcn_readfirstlane(mine.at[q]);
+                    const uint64_t keep = live & (PAIRS_ONCE ? (1ull << at) - 1ull : ~(1ull << at));
+                    uint64_t sure, cross;
+                    pair_masks(li, ax, ay, bx, by, mine.p0[q], mine.p1[q], mine.d[q], mine.k[q], sure, cross);
+                    take(sure, cross, keep);
+                    if (~sure & keep) [[unlikely]] settle(~sure & keep, at);
+                }
             }
         }
     }
-}
-
-// Block (blockIdx.x, blockIdx.y): edges i of A-block x (thread t holds
-// i = x * kCrossBlock + r * kCrossTile + t, r < kCrossRows) against edges j
-// of chunk y, streamed through LDS in tiles.  A crossing is a pair with no
-// shared end whose ends lie strictly on opposite sides of the other's line.
-// PAIRS_ONCE: only j > i counts (each crossing once, for the total);
-// otherwise every j != i counts and per_edge[i] accumulates.  M bounds the
-// magnitude of every coordinate.
-template <bool PAIRS_ONCE>
-__global__ __launch_bounds__(kCrossTile) void crossings_kernel(int64_t m, int64_t chunk, double M,
-                                                               const int2* __restrict__ ends,
-                                                               const float2* __restrict__ p,
-                                                               unsigned long long* __restrict__ per_edge,
-                                                               unsigned long long* __restrict__ total) {
-    __shared__ CrossEntry s_e[kCrossTile];
-    __shared__ int2 s_end[kCrossTile];
-    const int64_t a0 = (int64_t)blockIdx.x * kCrossBlock;
-    const int64_t c0 = (int64_t)blockIdx.y * chunk;
-    const int64_t c1 = min(c0 + chunk, m);
-    int64_t jbeg = c0;
-    if (PAIRS_ONCE) {
-        if (c1 <= a0 + 1) return;  // every j of the chunk is <= every i of the block
-        jbeg = max(c0, a0);        // a0 is a multiple of the tile size
+    if (!PAIRS_ONCE && i < m) {
+        const int64_t own = (int64_t)cnt + whole;
+        if (per_edge && own) atomicAdd(&per_edge[id_of(i)], (unsigned long long)own);
     }
-    double ax[kCrossRows], ay[kCrossRows], bx[kCrossRows], by[kCrossRows];
-    Line la[kCrossRows];
-    int cnt[kCrossRows];
-    uint64_t live[kCrossRows];
-    uint64_t wcnt = 0;
-#pragma unroll
-    for (int r = 0; r < kCrossRows; ++r) {
-        const int64_t i = a0 + r * kCrossTile + threadIdx.x;
-        cnt[r] = 0;
-        live[r] = __builtin_amdgcn_ballot_w64(i < m);
-        float2 pa = make_float2(0.f, 0.f), pb = pa;
-        if (i < m) {
-            const int2 e = ends[i];
-            pa = p[e.x];
-            pb = p[e.y];
-        }
-        ax[r] = pa.x;
-        ay[r] = pa.y;
-        bx[r] = pb.x;
-        by[r] = pb.y;
-        la[r] = make_line(pa.x, pa.y, pb.x, pb.y, M);
-    }
-    for (int64_t t0 = jbeg; t0 < c1; t0 += kCrossTile) {
-        const int64_t j = t0 + threadIdx.x;
-        if (j < c1) {
-            const int2 e = ends[j];
-            const float2 pc = p[e.x], pd = p[e.y];
-            s_e[threadIdx.x] = CrossEntry{pc.x, pc.y, pd.x, pd.y, make_line(pc.x, pc.y, pd.x, pd.y, M)};
-            s_end[threadIdx.x] = e;
-        }
-        __syncthreads();
-        const int tn = (int)min<int64_t>(kCrossTile, c1 - t0);
-        // in PAIRS_ONCE mode, tiles that reach into the block's own range count j > i only
-        if (PAIRS_ONCE && t0 < a0 + kCrossBlock)
-            cross_tile<PAIRS_ONCE, true>(s_e, s_end, tn, t0, a0, live, ax, ay, bx, by, la, cnt, wcnt, ends, p);
-        else
-            cross_tile<PAIRS_ONCE, false>(s_e, s_end, tn, t0, a0, live, ax, ay, bx, by, la, cnt, wcnt, ends, p);
-        __syncthreads();
-    }
-    int64_t sum = 0;
-#pragma unroll
-    for (int r = 0; r < kCrossRows; ++r) {
-        const int64_t i = a0 + r * kCrossTile + threadIdx.x;
-        sum += cnt[r];
-        if (!PAIRS_ONCE && per_edge && cnt[r] && i < m)
-            atomicAdd(&per_edge[i], (unsigned long long)cnt[r]);
-    }
-    const int64_t w = wave_sum(sum) + (int64_t)wcnt;
-    if (lane64() == 0 && w) atomicAdd(total, (unsigned long long)w);
+    const int64_t w = wave_sum((int64_t)(i < m ? cnt : 0)) + sure_cnt + whole * __popcll(live);
+    if (lane == 0 && w) atomicAdd(total, (unsigned long long)w);
 }
 
 // ------------------------------------------------------------------ edge lengths
@@ -570,25 +767,29 @@ __device__ __forceinline__ bool use_full_ring(int32_t k, unsigned open) {
     return k <= 3 || (int32_t)__popc(open) * (k + 5) >= 8 * k;
 }
 
-__device__ __forceinline__ double wave_min_d(double v) {
+// Minimum over aligned groups of G lanes, in every lane of the group.
+template <int G>
+__device__ __forceinline__ double group_min(double v) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
+    for (int off = G / 2; off >= 1; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
     return v;
 }
 
 // Gabriel degree of point iu.  Rings of cells around u find the nearest
 // point of each 45-degree octant until the octant is settled; a second walk
 // over the same rings (or sectors) tests every point of an octant that is
-// not blocked.  WAVE: the lanes of a wavefront take the cells of each ring in
-// turn (all lanes call this for the same point and get the same result);
-// otherwise one thread does it all and gives up (returns -1) once it has
-// visited more than `budget` cells and points.  box = (xmin, xmax, ymin, ymax).
-template <bool WAVE>
+// not blocked.  The G lanes of an aligned group take the cells of each ring in
+// turn (all of them call this for the same point and get the same result).
+// With G < 64 the group gives up (returns -1) once a lane has visited more
+// than `budget` cells and points.  box = (xmin, xmax, ymin, ymax).
+template <int G>
 __device__ int32_t gabriel_degree_of(int32_t iu, const Grid& g, const int64_t* __restrict__ start,
                                      const int32_t* __restrict__ pts, const float2* __restrict__ p,
                                      float cell, float4 box, int64_t budget) {
-    const int lane = WAVE ? lane64() : 0;
-    const int stride = WAVE ? 64 : 1;
+    const int lane = threadIdx.x % G;
+    constexpr int stride = G;
+    const uint64_t group = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull) << (lane64() / G * G);
+    const auto any = [&](bool b) { return (__ballot(b) & group) != 0ull; };
     Work work;
     const float2 u = p[iu];
     const int32_t cx = cell_x(g, u.x), cy = cell_y(g, u.y);
@@ -640,10 +841,8 @@ __device__ int32_t gabriel_degree_of(int32_t iu, const Grid& g, const int64_t* _
                 best[o] = r2 < best[o] ? r2 : best[o];
             }
         });
-        if (WAVE)
-            for (int o = 0; o < 8; ++o) best[o] = wave_min_d(best[o]);
-        else if (work.n > budget)
-            return -1;
+        for (int o = 0; o < 8; ++o) best[o] = group_min<G>(best[o]);
+        if (G < 64 && any(work.n > budget)) return -1;
         // every point of an octant visited so far within (k - 2) cells' width
         // of u has been seen (a cell index computed in float can be one off);
         // an octant is settled at ring ko once that covers twice its nearest
@@ -668,7 +867,7 @@ __device__ int32_t gabriel_degree_of(int32_t iu, const Grid& g, const int64_t* _
         unsigned live = 0;
         for (int o = 0; o < 8; ++o) live |= (ko[o] >= k ? 1u : 0u) << o;
         each_cell(k, live, [&](int64_t c, int only) {
-            if (!WAVE && (over = over || work.n > budget)) return;
+            if (G < 64 && (over = over || work.n > budget)) return;
             ++work.n;
             for (int64_t q = start[c]; q < start[c + 1]; ++q) {
                 ++work.n;
@@ -686,16 +885,16 @@ __device__ int32_t gabriel_degree_of(int32_t iu, const Grid& g, const int64_t* _
                 deg += gabriel_pair_dev(g, start, pts, p, iu, iv, work) ? 1 : 0;
             }
         });
+        if (G < 64) over = any(over);
     }
-    if (WAVE) return wave_sum(deg);
-    return over ? -1 : deg;
+    return over ? -1 : group_sum<G>(deg);
 }
 
-// Thread per point (in cell order: a wavefront's points are neighbours); a
-// point whose search exceeds the budget is listed in hard[] for
-// gabriel_wave_kernel instead.  At most 128 VGPRs, so that four waves per
-// SIMD hold every point of a 262k-point drawing at once (the walks are
-// latency-bound: 14.4 ms against 18.2 ms at 137 VGPRs and three waves).
+// kGabrielLanes lanes per point (in cell order: a wavefront's points are
+// neighbours); a point whose search exceeds the budget is listed in hard[] for
+// gabriel_wave_kernel instead.  The walks are latency-bound: with one lane per
+// point 131072 points are two wavefronts per SIMD, whose lanes also wait for
+// the longest of 64 walks (9.3 ms against 3.8 ms with eight).
 __global__ __launch_bounds__(kBlock, 4) void gabriel_degree_kernel(int32_t n, Grid g,
                                                                 const int64_t* __restrict__ start,
                                                                 const int32_t* __restrict__ pts,
@@ -704,10 +903,12 @@ __global__ __launch_bounds__(kBlock, 4) void gabriel_degree_kernel(int32_t n, Gr
                                                                 int32_t* __restrict__ gdeg,
                                                                 int32_t* __restrict__ hard,
                                                                 int32_t* __restrict__ hard_count) {
-    for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < n;
-         t += (int64_t)gridDim.x * kBlock) {
+    constexpr int L = kGabrielLanes;
+    for (int64_t t = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / L; t < n;
+         t += (int64_t)gridDim.x * (kBlock / L)) {
         const int32_t iu = pts[t];
-        const int32_t deg = gabriel_degree_of<false>(iu, g, start, pts, p, cell, box, budget);
+        const int32_t deg = gabriel_degree_of<L>(iu, g, start, pts, p, cell, box, budget);
+        if (threadIdx.x % L != 0) continue;
         if (deg >= 0)
             gdeg[iu] = deg;
         else
@@ -726,7 +927,7 @@ __global__ __launch_bounds__(kBlock, 4) void gabriel_wave_kernel(Grid g, const i
     const int64_t waves = (int64_t)gridDim.x * kWaves;
     for (int64_t i = (int64_t)blockIdx.x * kWaves + wave_id(); i < count; i += waves) {
         const int32_t iu = hard[i];
-        const int32_t deg = gabriel_degree_of<true>(iu, g, start, pts, p, cell, box, 0);
+        const int32_t deg = gabriel_degree_of<64>(iu, g, start, pts, p, cell, box, 0);
         if (lane64() == 0) gdeg[iu] = deg;
     }
 }
@@ -844,19 +1045,47 @@ static int drawing_metrics(const gila_csr* g, const V* pos, int32_t what, hipStr
         MBuf tot(s);
         GILA_TRY(tot.alloc<unsigned long long>(1));
         GILA_HIP(hipMemsetAsync(tot.p, 0, sizeof(unsigned long long), s));
-        // chunks of at least kCrossChunk edges, few enough for the grid's y extent
-        int64_t chunk = std::max<int64_t>(kCrossChunk, (m + 65534) / 65535);
-        chunk = (chunk + kCrossTile - 1) / kCrossTile * kCrossTile;
-        const dim3 grid((unsigned)((m + kCrossBlock - 1) / kCrossBlock), (unsigned)((m + chunk - 1) / chunk));
+        // groups of 64 edges in the order of their places (row order for few
+        // edges, whose pairs cost less than the sort, and for more than the
+        // sort's 32-bit places hold)
+        const int64_t groups = (m + kCrossGroup - 1) / kCrossGroup;
+        MBuf key(s), order(s), seg(s), cbox(s);
+        const bool sorted = m >= kCrossSortMin && m < INT32_MAX;
+        if (sorted) {
+            GILA_TRY(key.alloc<uint32_t>((size_t)m));
+            GILA_TRY(order.alloc<int32_t>((size_t)m));
+            const float sx = (float)(256.0 / std::max(1e-300, (double)xmax - (double)xmin));
+            const float sy = (float)(256.0 / std::max(1e-300, (double)ymax - (double)ymin));
+            hipLaunchKernelGGL(cross_key_kernel, dim3(mgrid(m)), dim3(kBlock), 0, s, m, ends.as<int2>(),
+                               pf.as<float2>(), make_float2(xmin, ymin), make_float2(sx, sy),
+                               key.as<uint32_t>());
+            GILA_HIP(hipGetLastError());
+            GILA_TRY(stable_order_by_key((int32_t)m, key.as<uint32_t>(), ~0u, order.as<int32_t>(), s));
+        }
+        const int32_t* by_place = sorted ? order.as<int32_t>() : nullptr;
+        GILA_TRY(seg.alloc<float4>((size_t)m));
+        GILA_TRY(cbox.alloc<CrossBox>((size_t)groups));
+        hipLaunchKernelGGL(cross_prepare_kernel, dim3(mgrid(groups * 64)), dim3(kBlock), 0, s, m, groups,
+                           ends.as<int2>(), pf.as<float2>(), by_place, seg.as<float4>(),
+                           cbox.as<CrossBox>());
+        // about kCrossWaves wavefronts, each one group against a range of `span`
+        int64_t span = std::max<int64_t>(1, groups * groups / kCrossWaves);
+        span = std::max<int64_t>(span, (groups + 65534) / 65535);
+        const dim3 grid((unsigned)((groups + kWaves - 1) / kWaves), (unsigned)((groups + span - 1) / span));
+        // rounding of the values that the group verdicts compare; drawings so
+        // small or large that their squares leave float's range get none
+        const float eps = M > 1e-12 && M < 1e18 ? (float)(0x1p-19 * M * M) : INFINITY;
         if (edge_crossings) {
             GILA_HIP(hipMemsetAsync(edge_crossings, 0, sizeof(int64_t) * (size_t)m, s));
-            hipLaunchKernelGGL(crossings_kernel<false>, grid, dim3(kCrossTile), 0, s, m, chunk, M,
-                               ends.as<int2>(), pf.as<float2>(),
+            hipLaunchKernelGGL(crossings_kernel<false>, grid, dim3(kBlock), 0, s, m, groups, span, M, eps,
+                               seg.as<float4>(), cbox.as<CrossBox>(), by_place, ends.as<int2>(),
+                               pf.as<float2>(),
                                reinterpret_cast<unsigned long long*>(edge_crossings),
                                tot.as<unsigned long long>());
         } else {
-            hipLaunchKernelGGL(crossings_kernel<true>, grid, dim3(kCrossTile), 0, s, m, chunk, M,
-                               ends.as<int2>(), pf.as<float2>(), nullptr, tot.as<unsigned long long>());
+            hipLaunchKernelGGL(crossings_kernel<true>, grid, dim3(kBlock), 0, s, m, groups, span, M, eps,
+                               seg.as<float4>(), cbox.as<CrossBox>(), by_place, ends.as<int2>(),
+                               pf.as<float2>(), nullptr, tot.as<unsigned long long>());
         }
         GILA_HIP(hipGetLastError());
         unsigned long long t = 0;
@@ -927,7 +1156,7 @@ static int drawing_metrics(const gila_csr* g, const V* pos, int32_t what, hipStr
         GILA_TRY(hcount.alloc<int32_t>(1));
         GILA_HIP(hipMemsetAsync(hcount.p, 0, sizeof(int32_t), s));
         const float4 fbox = make_float4(xmin, xmax, ymin, ymax);
-        hipLaunchKernelGGL(gabriel_degree_kernel, dim3(mgrid(n)), dim3(kBlock), 0, s, n, gr,
+        hipLaunchKernelGGL(gabriel_degree_kernel, dim3(mgrid((int64_t)n * kGabrielLanes)), dim3(kBlock), 0, s, n, gr,
                            cstart.as<int64_t>(), pts.as<int32_t>(), pf.as<float2>(), (float)cell, fbox,
                            budget, gdeg.as<int32_t>(), hard.as<int32_t>(), hcount.as<int32_t>());
         hipLaunchKernelGGL(gabriel_wave_kernel, dim3(mgrid((int64_t)n * 64)), dim3(kBlock), 0, s, gr,

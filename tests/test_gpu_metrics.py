@@ -182,3 +182,46 @@ def test_metrics_full_size_rmat18(G, gabriel_budget):
     assert np.array_equal(jac, expect)
     assert out.gabriel_edges == sum(len(a) for a in adj) // 2
     print(f"rmat18 crossings={out.crossings} sim={out.similarity:.6f} gabriel={out.gabriel_edges}")
+
+
+def _crossing_drawings():
+    """Drawings at the edges of the crossing kernels: edge counts around one
+    group (64) and around the count from which edges are sorted (4096), edges
+    that cross whole groups, edges along one line, coincident points,
+    coordinates whose squares leave float's range, and a flat drawing."""
+    rng = np.random.default_rng(12)
+    out = []
+    for m in (1, 63, 64, 65, 4095, 4096, 4097, 4200):
+        g = inputs.to_csr(2 * m, np.arange(m) * 2, np.arange(m) * 2 + 1)
+        out.append((f"match{m}", g, rng.uniform(0.0, 100.0, (2 * m, 2))))
+    # two bundles of 2100 nearly parallel edges, crossing each other at right angles
+    m = 2100
+    a = np.stack([rng.uniform(40, 60, m), rng.uniform(0, 1, m)], 1)
+    b = np.stack([a[:, 0] + rng.uniform(-1, 1, m), rng.uniform(99, 100, m)], 1)
+    x = np.concatenate([a, b, a[:, ::-1], b[:, ::-1]])
+    e = np.arange(m)
+    out.append(("bundles", inputs.to_csr(4 * m, np.concatenate([e, 2 * m + e]),
+                                         np.concatenate([m + e, 3 * m + e])), x))
+    g = inputs.erdos_renyi(900, 4500, seed=3)
+    out.append(("line", g, np.stack([rng.integers(0, 50, g.n), 2.0 * rng.integers(0, 2, g.n)], 1).astype(float)))
+    out.append(("coincident", g, rng.integers(0, 8, (g.n, 2)).astype(float)))
+    y = rng.uniform(-1.0, 1.0, (g.n, 2))
+    out += [("huge", g, y * 1e30), ("tiny", g, y * 1e-30), ("flat", g, y * np.array([1.0, 0.0])),
+            ("far", g, y + 1e6)]
+    return out
+
+
+@pytest.mark.parametrize("i", range(15))
+def test_crossings_at_kernel_edges(G, i):
+    import torch
+    name, g, x = _crossing_drawings()[i]
+    print(f"crossings {name}", flush=True)
+    x = oracle.single(x)
+    rp, ci = G.to_device_csr(g)
+    pos = torch.from_numpy(x.astype(np.float32)).cuda()
+    per = torch.full((g.m,), -1, dtype=torch.int64, device="cuda")
+    want = oracle.edge_crossings(g.n, g.row_ptr, g.col_idx, x, np.arange(g.m))
+    total = G.drawing_metrics(rp, ci, G.FP32, pos, G.METRIC_CROSSINGS).crossings
+    both = G.drawing_metrics(rp, ci, G.FP32, pos, G.METRIC_CROSSINGS, edge_crossings=per).crossings
+    assert np.array_equal(per.cpu().numpy(), want)
+    assert total == both == int(want.sum()) // 2
