@@ -134,7 +134,8 @@ struct Ctl {
     double max_disp;
     double energy;
     int64_t coincident;
-    int64_t coinc_pending;  // coincident pairs counted by the segment kernel, not yet published
+    int64_t coinc_pending[2];  // coincident pairs counted by the segment kernel, not yet published
+                               // (by StepArgs::par)
     int64_t nonfinite;      // last iteration: vertices with a non-finite force (stopped = 2)
 };
 
@@ -166,8 +167,9 @@ struct StepArgs {
     double stop_fraction;
     double stop_displacement;
     int32_t check_stop;
-    int32_t hist_slot;          // < 0: no history (with temps: ctl->h_base + tick_j)
-    int32_t hist_cap;           // rows of the history table
+    int32_t h;                  // iteration, its row of the history (with temps: ctl->h_base + tick_j)
+    int32_t hist_cap;           // rows of the history table (later iterations are not recorded)
+    int32_t par;                // place in the launch sequence, modulo 2
     const int32_t* perm;        // internal -> caller ids (for F/D outputs)
     double* F_out;              // caller ids, may be null
     double* D_out;
@@ -178,6 +180,9 @@ struct StepArgs {
     // part[vsl[v] .. vsl[v + 1]), one per non-empty slice, in segment order
     const int64_t* vsl;
     const double2* part;
+    // one-segment graphs: (|F|^2, |Delta|) of each vertex, |Delta| = -1 for a
+    // non-finite force; null where workgroup partials hold the statistics
+    double2* recs;
     // weight of the repulsion each vertex exerts (internal ids; float for the
     // FP32 precisions, double for FP64); null = every weight 1
     const void* mass;
@@ -212,6 +217,10 @@ struct SegArgs {
     const int64_t* sl_dn;
     const uint64_t* dmask;
     int32_t dense_blocks;
+    // 1: workgroup 0 reduces the previous iteration's statistics (its records,
+    // in a one-segment graph, at prev_recs) and the plan starts at workgroup 1
+    int32_t has_prev;
+    const double2* prev_recs;
 };
 
 // Arguments of the k-hop frontier-expansion kernel (khop.hip).
@@ -357,9 +366,14 @@ int stable_counting_pass(int64_t T, int64_t tj, int32_t nkeys, const uint32_t* k
 // implemented in segment.hip
 int build_segments(gila_khop* kh, int precision, hipStream_t s);
 void free_segments(gila_khop* kh, Release rel = Release{});
-// span: null, or where the force kernel records its start and end (SegArgs)
-int launch_segment_step(const gila_khop* kh, int precision, const StepArgs& a, hipStream_t s,
-                        unsigned long long* span = nullptr);
+// One iteration of a sequence.  The statistics of an iteration are reduced by
+// the next one's force kernel (has_prev: there is one before this; the
+// iterations' StepArgs::par alternate from 0), those of the last by
+// launch_segment_stats.  span: null, or where the force kernel records its
+// start and end (SegArgs).
+int launch_segment_step(const gila_khop* kh, int precision, const StepArgs& a, bool has_prev,
+                        hipStream_t s, unsigned long long* span = nullptr);
+int launch_segment_stats(const gila_khop* kh, const StepArgs& a, hipStream_t s);
 bool segment_path_enabled();
 // segment size S for the handle's graph in `precision` (weighted repulsion
 // stores a weight beside each staged position)
@@ -369,8 +383,12 @@ bool segment_ready_for(const gila_khop* kh, int precision);
 // implemented in layout.hip: publishes an iteration's statistics from the
 // per-workgroup partials (launched after each per-vertex kernel)
 int launch_iteration_stats(const StepArgs& a, hipStream_t s);
-// implemented in layout.hip: one iteration on whichever path the handle is ready for
-int launch_iteration(const gila_khop* kh, int precision, const StepArgs& a, hipStream_t s);
+// implemented in layout.hip: one iteration of a sequence on whichever path the
+// handle is ready for (has_prev as in launch_segment_step), and, after the
+// sequence's last iteration (whose arguments `a` are), its statistics
+int launch_iteration(const gila_khop* kh, int precision, const StepArgs& a, bool has_prev,
+                     hipStream_t s);
+int end_sequence(const gila_khop* kh, int precision, const StepArgs& a, hipStream_t s);
 int prepare_precision(gila_khop* kh, int precision, hipStream_t s);
 // destroys the handle's captured graphs (their kernels or arguments changed)
 void drop_graphs(gila_khop* kh);

@@ -356,19 +356,18 @@ __device__ __forceinline__ bool capped_move_f32(double fx, double fy, double t, 
     return true;
 }
 
-// Cap, move and record one vertex (Section 3.1 temperature cap; the move is
-// written to the other buffer, so all vertices move together).  A vertex
-// whose force is not finite stays put and is counted in `nonfinite`.
+// Cap and move one vertex (Section 3.1 temperature cap; the move is written
+// to the other buffer, so all vertices move together); returns its |F|^2 and
+// |Delta|.  A vertex whose force is not finite stays put: (0, -1).
 template <class P>
-__device__ __forceinline__ void finish_vertex(const StepArgs& a, int32_t v, typename P::vec2 xv,
-                                              double fx, double fy, double& energy, double& maxd,
-                                              int64_t& moved, int64_t& nonfinite) {
+__device__ __forceinline__ double2 move_vertex(const StepArgs& a, int32_t v, typename P::vec2 xv,
+                                               double fx, double fy) {
     using V = typename P::vec2;
     using R = typename P::real;
     double dx, dy;
     const double t = a.temps ? a.temps[a.ctl->h_base + a.tick_j] : a.t;
-    if (!capped_move(fx, fy, t, dx, dy)) {
-        ++nonfinite;
+    const bool finite = capped_move(fx, fy, t, dx, dy);
+    if (!finite) {
         fx = 0.0;  // keeps the energy statistic finite
         fy = 0.0;
     }
@@ -383,17 +382,113 @@ __device__ __forceinline__ void finish_vertex(const StepArgs& a, int32_t v, type
         a.D_out[2 * (int64_t)o] = dx;
         a.D_out[2 * (int64_t)o + 1] = dy;
     }
-    const double dl = sqrt(dx * dx + dy * dy);
-    energy += fx * fx + fy * fy;
-    maxd = dl > maxd ? dl : maxd;
-    moved += dl > a.stop_displacement ? 1 : 0;
+    return make_double2(fx * fx + fy * fy, finite ? sqrt(dx * dx + dy * dy) : -1.0);
+}
+
+// move_vertex with the vertex's share of the statistics.
+template <class P>
+__device__ __forceinline__ void finish_vertex(const StepArgs& a, int32_t v, typename P::vec2 xv,
+                                              double fx, double fy, double& energy, double& maxd,
+                                              int64_t& moved, int64_t& nonfinite) {
+    const double2 r = move_vertex<P>(a, v, xv, fx, fy);
+    energy += r.x;
+    maxd = r.y > maxd ? r.y : maxd;
+    moved += r.y > a.stop_displacement ? 1 : 0;
+    nonfinite += r.y < 0.0 ? 1 : 0;
+}
+
+// The statistics of iteration a (Section 5.1 halting rule included), from the
+// per-vertex records or the workgroups' partials (a.nblocks of them), by the
+// first kBlock threads of a workgroup of any size, in a fixed order, so that
+// whichever kernel runs this publishes the same bits.  Every thread of the
+// workgroup must call it.  h: the iteration.
+__device__ __forceinline__ void iteration_stats(const StepArgs& a, const double2* recs, int par,
+                                                int32_t h) {
+    __shared__ double s_e[kWaves], s_m[kWaves];
+    __shared__ int64_t s_mv[kWaves], s_c[kWaves], s_nf[kWaves];
+    Ctl* ctl = a.ctl;
+    const int lane = lane64();
+    const int w = wave_id();
+    double e = 0.0, m = 0.0;
+    int64_t mv = 0, c = 0, nf = 0;
+    if (w < kWaves) {
+        if (recs) {
+            for (int i = threadIdx.x; i < a.n_active; i += kBlock) {
+                const double2 r = recs[i];
+                e += r.x;
+                m = r.y > m ? r.y : m;
+                mv += r.y > a.stop_displacement ? 1 : 0;
+                nf += r.y < 0.0 ? 1 : 0;
+            }
+        } else {
+            for (int i = threadIdx.x; i < a.nblocks; i += kBlock) {
+                const Partial p = a.partials[i];
+                e += p.energy;
+                m = p.max_disp > m ? p.max_disp : m;
+                mv += p.moved;
+                c += p.coincident;
+                nf += p.nonfinite;
+            }
+        }
+        e = wave_sum(e);
+        m = wave_max(m);
+        mv = wave_sum(mv);
+        c = wave_sum(c);
+        nf = wave_sum(nf);
+        if (lane == 0) {
+            s_e[w] = e;
+            s_m[w] = m;
+            s_mv[w] = mv;
+            s_c[w] = c;
+            s_nf[w] = nf;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        e = s_e[0];
+        m = s_m[0];
+        mv = s_mv[0];
+        c = s_c[0];
+        nf = s_nf[0];
+        for (int i = 1; i < kWaves; ++i) {
+            e += s_e[i];
+            m = s_m[i] > m ? s_m[i] : m;
+            mv += s_mv[i];
+            c += s_c[i];
+            nf += s_nf[i];
+        }
+        c += ctl->coinc_pending[par];
+        ctl->coinc_pending[par] = 0;
+        ctl->energy = e;
+        ctl->max_disp = m;
+        ctl->moved = mv;
+        ctl->coincident = c;
+        ctl->nonfinite = nf;
+        ctl->iters_run += 1;
+        if (a.check_stop && (double)mv < a.stop_fraction * (double)a.n_active) ctl->stopped = 1;
+        // a non-finite force ends the run (2: stopped by the error, not the rule)
+        if (nf > 0) ctl->stopped = 2;
+        if (h < a.hist_cap) {  // the iteration's row of the history
+            double* hrow = a.hist + 4 * (int64_t)h;
+            hrow[0] = e;
+            hrow[1] = m;
+            hrow[2] = (double)mv;
+            hrow[3] = (double)c;
+        }
+    }
+}
+
+// The iteration that the arguments are for (from the replay's base in a
+// captured chunk or tick).
+__device__ __forceinline__ int32_t iteration_index(const StepArgs& a) {
+    return a.temps ? a.ctl->h_base + a.tick_j : a.h;
 }
 
 // Ends the per-vertex part of an iteration kernel: the workgroup's statistics,
 // reduced in a fixed order, go to a.partials[blockIdx.x].  The iteration's
-// totals are published by iteration_stats_kernel, launched next on the same
-// stream (a kernel boundary makes the partials visible to it without a
-// device-wide cache writeback per workgroup).  Every thread of the workgroup
+// totals are published by a later launch on the same stream (a kernel
+// boundary makes the partials visible to it without a device-wide cache
+// writeback per workgroup).  Every thread of the workgroup
 // must call it.
 __device__ __forceinline__ void end_iteration(const StepArgs& a, double energy, double maxd,
                                               int64_t moved, int64_t coinc, int64_t nonfinite) {

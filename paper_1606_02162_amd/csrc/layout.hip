@@ -5,85 +5,17 @@
 #include <cstdio>
 #include <cstdlib>
 
-#include "device_util.h"
-#include "gila_internal.h"
 #include "host_logic.h"
+#include "iteration.h"
 
 namespace gila {
 
 // ------------------------------------------------------------------ iteration statistics
-// One workgroup, after the iteration's per-vertex kernel: reduces the
-// workgroups' partials (a.nblocks of them) in a fixed order and publishes the
-// iteration's statistics (Section 5.1 halting rule included).
+// One workgroup, after an iteration whose statistics no later force kernel
+// reduces.
 __global__ __launch_bounds__(kBlock) void iteration_stats_kernel(StepArgs a) {
-    __shared__ double s_e[kWaves], s_m[kWaves];
-    __shared__ int64_t s_mv[kWaves], s_c[kWaves], s_nf[kWaves];
-    Ctl* ctl = a.ctl;
-    if (ctl->stopped) return;
-    const int lane = lane64();
-    const int w = wave_id();
-    double e = 0.0, m = 0.0;
-    int64_t mv = 0, c = 0, nf = 0;
-    for (int i = threadIdx.x; i < a.nblocks; i += kBlock) {
-        const Partial p = a.partials[i];
-        e += p.energy;
-        m = p.max_disp > m ? p.max_disp : m;
-        mv += p.moved;
-        c += p.coincident;
-        nf += p.nonfinite;
-    }
-    e = wave_sum(e);
-    m = wave_max(m);
-    mv = wave_sum(mv);
-    c = wave_sum(c);
-    nf = wave_sum(nf);
-    if (lane == 0) {
-        s_e[w] = e;
-        s_m[w] = m;
-        s_mv[w] = mv;
-        s_c[w] = c;
-        s_nf[w] = nf;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        e = s_e[0];
-        m = s_m[0];
-        mv = s_mv[0];
-        c = s_c[0];
-        nf = s_nf[0];
-        for (int i = 1; i < kWaves; ++i) {
-            e += s_e[i];
-            m = s_m[i] > m ? s_m[i] : m;
-            mv += s_mv[i];
-            c += s_c[i];
-            nf += s_nf[i];
-        }
-        c += ctl->coinc_pending;
-        ctl->coinc_pending = 0;
-        ctl->energy = e;
-        ctl->max_disp = m;
-        ctl->moved = mv;
-        ctl->coincident = c;
-        ctl->nonfinite = nf;
-        ctl->iters_run += 1;
-        if (a.check_stop && (double)mv < a.stop_fraction * (double)a.n_active) ctl->stopped = 1;
-        // a non-finite force ends the run (2: stopped by the error, not the rule)
-        if (nf > 0) ctl->stopped = 2;
-        // the history row: this iteration's h (from the replay's base in a
-        // captured chunk or tick)
-        int32_t slot = a.hist_slot;
-        if (a.temps) {
-            const int32_t hh = ctl->h_base + a.tick_j;
-            slot = hh < a.hist_cap ? hh : -1;
-        }
-        if (slot >= 0) {
-            double* hrow = a.hist + 4 * (int64_t)slot;
-            hrow[0] = e;
-            hrow[1] = m;
-            hrow[2] = (double)mv;
-            hrow[3] = (double)c;
-        }
-    }
+    if (a.ctl->stopped) return;
+    iteration_stats(a, a.recs, a.par, iteration_index(a));
 }
 
 int launch_iteration_stats(const StepArgs& a, hipStream_t s) {
@@ -125,7 +57,8 @@ __global__ void reset_ctl_kernel(Ctl* ctl) {
     ctl->max_disp = 0.0;
     ctl->energy = 0.0;
     ctl->coincident = 0;
-    ctl->coinc_pending = 0;
+    ctl->coinc_pending[0] = 0;
+    ctl->coinc_pending[1] = 0;
     ctl->nonfinite = 0;
 }
 
@@ -224,7 +157,6 @@ static StepArgs base_args(const gila_khop* kh, const gila_params* p) {
     a.partials = kh->partials;
     a.ctl = kh->ctl;
     a.hist = kh->hist;
-    a.hist_slot = -1;
     a.hist_cap = kh->hist_cap;
     if (kh->mass64)
         a.mass = p->precision == GILA_FP64 ? (const void*)kh->mass64 : (const void*)kh->mass32;
@@ -252,6 +184,39 @@ int nonfinite_status(const Ctl& c) {
     return GILA_OK;
 }
 
+// Place j of a launch sequence: its buffers and parity.
+static void set_place(const gila_khop* kh, StepArgs& a, int32_t j) {
+    a.pos_cur = kh->pos[j & 1];
+    a.pos_next = kh->pos[(j + 1) & 1];
+    a.par = j & 1;
+}
+
+// Enqueues iterations [start_h, end_h) with the caps of the schedule, from the
+// first position buffer on.
+static int enqueue_iterations(const gila_khop* kh, const gila_params* p, StepArgs a, int32_t start_h,
+                              int32_t end_h, hipStream_t s, unsigned long long* span = nullptr) {
+    a.temps = nullptr;
+    for (int32_t h = start_h; h < end_h; ++h) {
+        set_place(kh, a, h - start_h);
+        a.t = p->temperature[h];
+        a.h = h;
+        if (span) GILA_TRY(launch_segment_step(kh, p->precision, a, h > start_h, s, span + 2 * (h - start_h)));
+        else GILA_TRY(launch_iteration(kh, p->precision, a, h > start_h, s));
+    }
+    return end_h > start_h ? end_sequence(kh, p->precision, a, s) : GILA_OK;
+}
+
+// Enqueues `count` iterations whose caps are read from a.temps at the base set
+// on the device.
+static int enqueue_from_base(const gila_khop* kh, int precision, StepArgs a, int32_t count, hipStream_t s) {
+    for (int32_t j = 0; j < count; ++j) {
+        set_place(kh, a, j);
+        a.tick_j = j;
+        GILA_TRY(launch_iteration(kh, precision, a, j > 0, s));
+    }
+    return count > 0 ? end_sequence(kh, precision, a, s) : GILA_OK;
+}
+
 // Enqueue: reset, permute in, iterations, permute out.
 int enqueue_run(gila_khop* kh, const gila_params* p, int32_t start_h, int32_t end_h,
                 void* pos_dev, hipStream_t s) {
@@ -260,14 +225,7 @@ int enqueue_run(gila_khop* kh, const gila_params* p, int32_t start_h, int32_t en
     GILA_TRY(launch_permute_in(kh, p->precision, pos_dev, s));
     StepArgs a = base_args(kh, p);
     a.check_stop = p->stop_fraction > 0.0 ? 1 : 0;
-    for (int32_t h = start_h; h < end_h; ++h) {
-        const int j = h - start_h;
-        a.pos_cur = kh->pos[j & 1];
-        a.pos_next = kh->pos[(j + 1) & 1];
-        a.t = p->temperature[h];
-        a.hist_slot = h < kh->hist_cap ? h : -1;
-        GILA_TRY(launch_iteration(kh, p->precision, a, s));
-    }
+    GILA_TRY(enqueue_iterations(kh, p, a, start_h, end_h, s));
     GILA_TRY(launch_permute_out(kh, p->precision, pos_dev, s));
     return GILA_OK;
 }
@@ -343,12 +301,7 @@ int enqueue_tick(gila_khop* kh, const gila_params* p, int32_t h, int32_t count,
         StepArgs a = base_args(kh, p);
         a.check_stop = p->stop_fraction > 0.0 ? 1 : 0;
         a.temps = kh->d_temps;
-        for (int32_t j = 0; j < count && rc == GILA_OK; ++j) {
-            a.pos_cur = kh->pos[j & 1];
-            a.pos_next = kh->pos[(j + 1) & 1];
-            a.tick_j = j;
-            rc = launch_iteration(kh, p->precision, a, cs);
-        }
+        if (rc == GILA_OK) rc = enqueue_from_base(kh, p->precision, a, count, cs);
         if (rc == GILA_OK) rc = launch_permute_out(kh, p->precision, pos_dev, cs);
         hipGraph_t graph = nullptr;
         const hipError_t ee = hipStreamEndCapture(cs, &graph);
@@ -417,9 +370,14 @@ int prepare_precision(gila_khop* kh, int precision, hipStream_t s) {
     return ensure_direct_plan(kh, s);
 }
 
-int launch_iteration(const gila_khop* kh, int precision, const StepArgs& a, hipStream_t s) {
-    if (segment_ready_for(kh, precision)) return launch_segment_step(kh, precision, a, s);
-    return launch_step(kh, precision, a, s);
+int launch_iteration(const gila_khop* kh, int precision, const StepArgs& a, bool has_prev,
+                     hipStream_t s) {
+    if (segment_ready_for(kh, precision)) return launch_segment_step(kh, precision, a, has_prev, s);
+    return launch_step(kh, precision, a, s);  // (publishes its own statistics)
+}
+
+int end_sequence(const gila_khop* kh, int precision, const StepArgs& a, hipStream_t s) {
+    return segment_ready_for(kh, precision) ? launch_segment_stats(kh, a, s) : GILA_OK;
 }
 
 // Everything the captured loop depends on besides the handle's own buffers
@@ -478,13 +436,7 @@ static int enqueue_chunked_run(gila_khop* kh, const gila_params* p, int32_t star
         if (!cs) return fail(GILA_EDEVICE, "cannot create capture stream");
         (void)hipGetLastError();  // no stale status may fail a check inside the capture
         GILA_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
-        int rc = GILA_OK;
-        for (int32_t j = 0; j < kRunChunk && rc == GILA_OK; ++j) {
-            a.pos_cur = kh->pos[j & 1];
-            a.pos_next = kh->pos[(j + 1) & 1];
-            a.tick_j = j;
-            rc = launch_iteration(kh, p->precision, a, cs);
-        }
+        const int rc = enqueue_from_base(kh, p->precision, a, kRunChunk, cs);
         hipGraph_t graph = nullptr;
         const hipError_t ee = hipStreamEndCapture(cs, &graph);
         if (rc != GILA_OK) {
@@ -510,14 +462,7 @@ static int enqueue_chunked_run(gila_khop* kh, const gila_params* p, int32_t star
         GILA_HIP(hipGraphLaunch(kh->chunk_exec, s));
     }
     // the rest one launch at a time, continuing in the first buffer
-    a.temps = nullptr;
-    for (int32_t j = 0; h < end_h; ++h, ++j) {
-        a.pos_cur = kh->pos[j & 1];
-        a.pos_next = kh->pos[(j + 1) & 1];
-        a.t = p->temperature[h];
-        a.hist_slot = h < kh->hist_cap ? h : -1;
-        GILA_TRY(launch_iteration(kh, p->precision, a, s));
-    }
+    GILA_TRY(enqueue_iterations(kh, p, a, h, end_h, s));
     return launch_permute_out(kh, p->precision, pos_dev, s);
 }
 
@@ -644,13 +589,9 @@ int gila_step(const gila_khop* kh_c, const gila_params* params, int32_t h, void*
     GILA_TRY(launch_permute_in(kh, params->precision, pos_dev, s));
     StepArgs a = base_args(kh, params);
     a.check_stop = 0;
-    a.pos_cur = kh->pos[0];
-    a.pos_next = kh->pos[1];
-    a.t = params->temperature[h];
-    a.hist_slot = h < kh->hist_cap ? h : -1;
     a.F_out = force_dev;
     a.D_out = disp_dev;
-    GILA_TRY(launch_iteration(kh, params->precision, a, s));
+    GILA_TRY(enqueue_iterations(kh, params, a, h, h + 1, s));
     GILA_TRY(launch_permute_out(kh, params->precision, pos_dev, s));
     if (out) {
         Ctl c{};
@@ -713,15 +654,8 @@ int gila_time_iterations(const gila_khop* kh_c, const gila_params* params, int32
         hipLaunchKernelGGL(reset_ctl_kernel, dim3(1), dim3(1), 0, q, kh->ctl);
         GILA_HIP(hipGetLastError());
         GILA_TRY(launch_permute_in(kh, params->precision, pos_dev, q));
-        StepArgs a = base_args(kh, params);
-        for (int32_t r = 0; r < reps; ++r) {
-            a.pos_cur = kh->pos[r & 1];
-            a.pos_next = kh->pos[(r + 1) & 1];
-            a.t = params->temperature[h + r];
-            a.hist_slot = h + r < kh->hist_cap ? h + r : -1;
-            if (seg) GILA_TRY(launch_segment_step(kh, params->precision, a, q, span + 2 * r));
-            else GILA_TRY(launch_step(kh, params->precision, a, q));
-        }
+        GILA_TRY(enqueue_iterations(kh, params, base_args(kh, params), h, h + reps, q,
+                                    seg ? span : nullptr));
         return launch_permute_out(kh, params->precision, pos_dev, q);
     };
     hipGraphExec_t exec = nullptr;

@@ -26,7 +26,14 @@
 //                      of row v are contiguous and in segment order.
 //   seg_combine_kernel one thread per vertex: adds the vertex's partials in
 //                      segment order, applies the temperature cap, writes the
-//                      vertex's next position and the iteration statistics.
+//                      vertex's next position and workgroup partials of the
+//                      iteration statistics.
+// A graph of one segment has one slice per row, so there the force kernel
+// moves the vertex itself and one kernel is the iteration.  The statistics of
+// an iteration are reduced by one more workgroup of the next iteration's force
+// kernel, beside its work: that iteration runs before the halting rule is
+// known to have ended the run, but into the other position buffer, which the
+// stopped run no longer reads; the one after sees the flag.
 // The result of every row depends only on the graph's plan (lanes per slice of
 // its workgroup) and on the fixed segment order, never on scheduling.
 //
@@ -397,8 +404,9 @@ __device__ __forceinline__ void quad_terms(uint2 w, const unsigned char* __restr
     }
 }
 
-template <class P, int LPV, bool WEIGHTED, int Q>
-__device__ __forceinline__ void seg_slices(const SegArgs& a, int ib, int ie,
+// ONE: the graph has one segment; each slice is a whole row, moved here.
+template <class P, int LPV, bool WEIGHTED, int Q, bool ONE>
+__device__ __forceinline__ void seg_slices(const SegArgs& a, const StepArgs& st, int ib, int ie,
                                            const typename P::vec2* __restrict__ lp,
                                            const unsigned char* __restrict__ lw, int* s_next,
                                            int& coinc) {
@@ -423,8 +431,13 @@ __device__ __forceinline__ void seg_slices(const SegArgs& a, int ib, int ie,
         if (i0 >= ie) break;
         const int i = i0 + wgrp;
         Acc<R, P::kahan> acc;
+        int32_t v = 0;
+        V xv;
+        xv.x = 0;
+        xv.y = 0;
         if (i < ie) {
-            const V xv = gpos[a.sl_v[i]];
+            v = a.sl_v[i];
+            xv = gpos[v];
             const int64_t kb = a.sl_k[i], ke = a.sl_k[i + 1];
             const uint2* __restrict__ q4 = reinterpret_cast<const uint2*>(a.kidx + kb);
             const int nq = (int)((ke - kb) >> 2);
@@ -514,7 +527,10 @@ __device__ __forceinline__ void seg_slices(const SegArgs& a, int ib, int ie,
         }
         const double fx = group_sum<LPV>(acc.x()) * d2;
         const double fy = group_sum<LPV>(acc.y()) * d2;
-        if (i < ie && gl == 0) a.part[a.sl_p[i]] = make_double2(fx, fy);
+        if (i < ie && gl == 0) {
+            if constexpr (ONE) st.recs[v] = move_vertex<P>(st, v, xv, fx, fy);
+            else a.part[a.sl_p[i]] = make_double2(fx, fy);
+        }
     }
 }
 
@@ -613,20 +629,28 @@ __device__ __forceinline__ void dense_slice(const SegArgs& a, int i, int nblk,
 // workgroups keep more of them per graph.  FP64 needs more registers.
 // WEIGHTED stages each vertex's repulsion weight in a static LDS array (slot
 // S of positions and weights holds the sentinel).
-template <int PREC, bool WEIGHTED, int Q, bool BIG>
-__global__ __launch_bounds__(seg_block<BIG>(), PREC == GILA_FP64 ? 4 : kSegWaves) void seg_force_kernel(SegArgs a) {
+// ONE (the move's double arithmetic besides) would spill at 64 registers, and
+// its graphs do not fill eight waves per SIMD.  With has_prev the first
+// workgroup reduces the previous iteration's statistics (SegArgs::has_prev).
+template <int PREC, bool WEIGHTED, int Q, bool BIG, bool ONE>
+__global__ __launch_bounds__(seg_block<BIG>(), PREC == GILA_FP64 ? 4 : (ONE ? 6 : kSegWaves)) void seg_force_kernel(
+    SegArgs a, StepArgs st) {
     constexpr int kSegBlock = seg_block<BIG>();
     using P = Prec<PREC>;
     using V = typename P::vec2;
     extern __shared__ __align__(16) unsigned char s_raw[];
     V* lp = reinterpret_cast<V*>(s_raw);
     __shared__ int64_t s_c[kSegBlock / 64];
+    if (a.has_prev && blockIdx.x == 0) {
+        if (!a.ctl->stopped) iteration_stats(st, a.prev_recs, st.par ^ 1, iteration_index(st) - 1);
+        return;
+    }
     if (a.span && threadIdx.x == 0) atomicMin(&a.span[0], (unsigned long long)wall_clock64());
     if (a.ctl->stopped) {
         if (a.span && threadIdx.x == 0) atomicMax(&a.span[1], (unsigned long long)wall_clock64());
         return;
     }
-    const int4 w = a.wg[blockIdx.x];
+    const int4 w = a.wg[blockIdx.x - a.has_prev];
     const int s = w.x, ib = w.y, ie = w.z, lpv = w.w;
     // stage the segment's positions
     const V* gpos = reinterpret_cast<const V*>(a.pos);
@@ -655,7 +679,7 @@ __global__ __launch_bounds__(seg_block<BIG>(), PREC == GILA_FP64 ? 4 : kSegWaves
     }
     __syncthreads();
     int coinc = 0;
-    if constexpr (PREC != GILA_FP64) {
+    if constexpr (PREC != GILA_FP64 && !ONE) {
         if (id > ib) {
             const int nblk = (cnt + 63) >> 6;
             const unsigned char* lds = reinterpret_cast<const unsigned char*>(lp);
@@ -671,13 +695,13 @@ __global__ __launch_bounds__(seg_block<BIG>(), PREC == GILA_FP64 ? 4 : kSegWaves
     }
     const unsigned char* wb = reinterpret_cast<const unsigned char*>(lw);
     switch (lpv) {
-        case 1: seg_slices<P, 1, WEIGHTED, Q>(a, id, ie, lp, wb, &s_next, coinc); break;
-        case 2: seg_slices<P, 2, WEIGHTED, Q>(a, id, ie, lp, wb, &s_next, coinc); break;
-        case 4: seg_slices<P, 4, WEIGHTED, Q>(a, id, ie, lp, wb, &s_next, coinc); break;
-        case 8: seg_slices<P, 8, WEIGHTED, Q>(a, id, ie, lp, wb, &s_next, coinc); break;
-        case 16: seg_slices<P, 16, WEIGHTED, Q>(a, id, ie, lp, wb, &s_next, coinc); break;
-        case 32: seg_slices<P, 32, WEIGHTED, Q>(a, id, ie, lp, wb, &s_next, coinc); break;
-        default: seg_slices<P, 64, WEIGHTED, Q>(a, id, ie, lp, wb, &s_next, coinc); break;
+        case 1: seg_slices<P, 1, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
+        case 2: seg_slices<P, 2, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
+        case 4: seg_slices<P, 4, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
+        case 8: seg_slices<P, 8, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
+        case 16: seg_slices<P, 16, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
+        case 32: seg_slices<P, 32, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
+        default: seg_slices<P, 64, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
     }
     const int64_t wc = wave_sum((int64_t)coinc);
     if (lane64() == 0) s_c[wave_id()] = wc;
@@ -685,7 +709,7 @@ __global__ __launch_bounds__(seg_block<BIG>(), PREC == GILA_FP64 ? 4 : kSegWaves
     if (threadIdx.x == 0) {
         int64_t c = 0;
         for (int i = 0; i < kSegBlock / 64; ++i) c += s_c[i];
-        if (c) atomicAdd((unsigned long long*)&a.ctl->coinc_pending, (unsigned long long)c);
+        if (c) atomicAdd((unsigned long long*)&a.ctl->coinc_pending[st.par], (unsigned long long)c);
         if (a.span) atomicMax(&a.span[1], (unsigned long long)wall_clock64());
     }
 }
@@ -927,7 +951,8 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     GILA_TRY(dalloc_t(&kh->sl_p, (size_t)T));
     GILA_TRY(dalloc_t(&kh->sl_k, (size_t)T + 1));
     GILA_TRY(dalloc_t(&kh->sl_a, (size_t)T + 1));
-    GILA_TRY(dalloc_t(&kh->part, (size_t)T));
+    // (one segment: two sets of per-vertex records)
+    GILA_TRY(dalloc_t(&kh->part, (size_t)T * (nseg == 1 ? 2 : 1)));
     if (dense_ok) GILA_TRY(dalloc_t(&kh->sl_dn, (size_t)T + 1));
 
     hipLaunchKernelGGL(slice_rows_kernel<true>, dim3(grid_rows), dim3(kBlock), 0, st, b);
@@ -1023,11 +1048,12 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     const size_t lds = seg_lds_bytes(kh, precision, S);
     if (lds > 48 * 1024) {
         const void* kernels[] = {
-#define GILA_SEG_KERNELS(W, Q, B)                                   \
-    (const void*)seg_force_kernel<GILA_FP64, W, Q, B>,              \
-        (const void*)seg_force_kernel<GILA_FP32, W, Q, B>,          \
-        (const void*)seg_force_kernel<GILA_FP32_KAHAN, W, Q, B>
-#define GILA_SEG_KERNELS_B(W, Q) GILA_SEG_KERNELS(W, Q, false), GILA_SEG_KERNELS(W, Q, true)
+#define GILA_SEG_KERNELS(W, Q, B, O)                                \
+    (const void*)seg_force_kernel<GILA_FP64, W, Q, B, O>,           \
+        (const void*)seg_force_kernel<GILA_FP32, W, Q, B, O>,       \
+        (const void*)seg_force_kernel<GILA_FP32_KAHAN, W, Q, B, O>
+#define GILA_SEG_KERNELS_B(W, Q) \
+    GILA_SEG_KERNELS(W, Q, false, false), GILA_SEG_KERNELS(W, Q, true, false), GILA_SEG_KERNELS(W, Q, false, true)
             GILA_SEG_KERNELS_B(false, 1), GILA_SEG_KERNELS_B(true, 1),  GILA_SEG_KERNELS_B(false, 0),
             GILA_SEG_KERNELS_B(true, 0),  GILA_SEG_KERNELS_B(false, 2), GILA_SEG_KERNELS_B(true, 2),
             GILA_SEG_KERNELS_B(false, 3), GILA_SEG_KERNELS_B(true, 3),  GILA_SEG_KERNELS_B(false, -1),
@@ -1049,32 +1075,55 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     return GILA_OK;
 }
 
-template <bool WEIGHTED, int Q, bool BIG>
-static void launch_seg_force(int precision, dim3 sg, size_t lds, hipStream_t s, const SegArgs& g) {
+template <bool WEIGHTED, int Q, bool BIG, bool ONE>
+static void launch_seg_force(int precision, dim3 sg, size_t lds, hipStream_t s, const SegArgs& g,
+                             const StepArgs& st) {
     const dim3 sb(seg_block<BIG>());
     switch (precision) {
-        case GILA_FP64: hipLaunchKernelGGL((seg_force_kernel<GILA_FP64, WEIGHTED, Q, BIG>), sg, sb, lds, s, g); break;
-        case GILA_FP32: hipLaunchKernelGGL((seg_force_kernel<GILA_FP32, WEIGHTED, Q, BIG>), sg, sb, lds, s, g); break;
-        default: hipLaunchKernelGGL((seg_force_kernel<GILA_FP32_KAHAN, WEIGHTED, Q, BIG>), sg, sb, lds, s, g); break;
+        case GILA_FP64: hipLaunchKernelGGL((seg_force_kernel<GILA_FP64, WEIGHTED, Q, BIG, ONE>), sg, sb, lds, s, g, st); break;
+        case GILA_FP32: hipLaunchKernelGGL((seg_force_kernel<GILA_FP32, WEIGHTED, Q, BIG, ONE>), sg, sb, lds, s, g, st); break;
+        default: hipLaunchKernelGGL((seg_force_kernel<GILA_FP32_KAHAN, WEIGHTED, Q, BIG, ONE>), sg, sb, lds, s, g, st); break;
     }
 }
 
 // Repulsion exponents with a kernel of their own; others run the general one.
-template <bool WEIGHTED, bool BIG>
+template <bool WEIGHTED, bool BIG, bool ONE>
 static void launch_seg_force_q(int q, int precision, dim3 sg, size_t lds, hipStream_t s,
-                               const SegArgs& g) {
+                               const SegArgs& g, const StepArgs& st) {
     switch (q) {
-        case 1: launch_seg_force<WEIGHTED, 1, BIG>(precision, sg, lds, s, g); break;
-        case 0: launch_seg_force<WEIGHTED, 0, BIG>(precision, sg, lds, s, g); break;
-        case 2: launch_seg_force<WEIGHTED, 2, BIG>(precision, sg, lds, s, g); break;
-        case 3: launch_seg_force<WEIGHTED, 3, BIG>(precision, sg, lds, s, g); break;
-        default: launch_seg_force<WEIGHTED, -1, BIG>(precision, sg, lds, s, g); break;
+        case 1: launch_seg_force<WEIGHTED, 1, BIG, ONE>(precision, sg, lds, s, g, st); break;
+        case 0: launch_seg_force<WEIGHTED, 0, BIG, ONE>(precision, sg, lds, s, g, st); break;
+        case 2: launch_seg_force<WEIGHTED, 2, BIG, ONE>(precision, sg, lds, s, g, st); break;
+        case 3: launch_seg_force<WEIGHTED, 3, BIG, ONE>(precision, sg, lds, s, g, st); break;
+        default: launch_seg_force<WEIGHTED, -1, BIG, ONE>(precision, sg, lds, s, g, st); break;
     }
 }
 
-int launch_segment_step(const gila_khop* kh, int precision, const StepArgs& a, hipStream_t s,
-                        unsigned long long* span) {
+// One kernel per iteration: a graph of one segment, in the small workgroup
+// shape and without dense slices (every row is then one offset-listed slice).
+static bool one_segment(const gila_khop* kh) {
+    return kh->nseg == 1 && !kh->seg_large && kh->ndense == 0;
+}
+
+// The arguments of the per-vertex part: where its statistics go.
+static StepArgs vertex_args(const gila_khop* kh, const StepArgs& a) {
+    StepArgs c = a;
+    c.vsl = kh->vsl;
+    c.part = kh->part;
+    c.nblocks = kh->comb_grid;
+    c.recs = one_segment(kh) ? kh->part + (a.par ? kh->nslices : 0) : nullptr;
+    return c;
+}
+
+int launch_segment_stats(const gila_khop* kh, const StepArgs& a, hipStream_t s) {
     if (kh->n_active == 0) return GILA_OK;
+    return launch_iteration_stats(vertex_args(kh, a), s);
+}
+
+int launch_segment_step(const gila_khop* kh, int precision, const StepArgs& a, bool has_prev,
+                        hipStream_t s, unsigned long long* span) {
+    if (kh->n_active == 0) return GILA_OK;
+    const bool one = one_segment(kh);
     SegArgs g{};
     g.na = kh->n_active;
     g.seg = kh->seg;
@@ -1096,27 +1145,29 @@ int launch_segment_step(const gila_khop* kh, int precision, const StepArgs& a, h
     g.sl_dn = kh->ndense > 0 ? kh->sl_dn : nullptr;
     g.dmask = kh->dmask;
     g.dense_blocks = kh->dense_blocks;
-    StepArgs c = a;
-    c.vsl = kh->vsl;
-    c.part = kh->part;
-    c.nblocks = kh->comb_grid;
+    g.has_prev = has_prev ? 1 : 0;
+    g.prev_recs = one ? kh->part + (a.par ? 0 : kh->nslices) : nullptr;
+    const StepArgs c = vertex_args(kh, a);
     if (precision != GILA_FP64 && precision != GILA_FP32 && precision != GILA_FP32_KAHAN)
         return fail(GILA_EINVAL, "unknown precision %d", precision);
     if ((a.mass != nullptr) != kh->seg_weighted)
         return fail(GILA_EINVAL, "segment layout built for other repulsion weights");
     const size_t lds = seg_lds_bytes(kh, precision, kh->seg);
-    const dim3 sg(kh->seg_grid), cg(kh->comb_grid), cb(kBlock);
+    const dim3 sg(kh->seg_grid + g.has_prev), cg(kh->comb_grid), cb(kBlock);
     const bool big = kh->seg_large;
-    if (a.mass && big) launch_seg_force_q<true, true>(a.rep_q, precision, sg, lds, s, g);
-    else if (a.mass) launch_seg_force_q<true, false>(a.rep_q, precision, sg, lds, s, g);
-    else if (big) launch_seg_force_q<false, true>(a.rep_q, precision, sg, lds, s, g);
-    else launch_seg_force_q<false, false>(a.rep_q, precision, sg, lds, s, g);
-    switch (precision) {
-        case GILA_FP64: hipLaunchKernelGGL(seg_combine_kernel<GILA_FP64>, cg, cb, 0, s, c); break;
-        case GILA_FP32: hipLaunchKernelGGL(seg_combine_kernel<GILA_FP32>, cg, cb, 0, s, c); break;
-        default: hipLaunchKernelGGL(seg_combine_kernel<GILA_FP32_KAHAN>, cg, cb, 0, s, c); break;
+    if (one && a.mass) launch_seg_force_q<true, false, true>(a.rep_q, precision, sg, lds, s, g, c);
+    else if (one) launch_seg_force_q<false, false, true>(a.rep_q, precision, sg, lds, s, g, c);
+    else if (a.mass && big) launch_seg_force_q<true, true, false>(a.rep_q, precision, sg, lds, s, g, c);
+    else if (a.mass) launch_seg_force_q<true, false, false>(a.rep_q, precision, sg, lds, s, g, c);
+    else if (big) launch_seg_force_q<false, true, false>(a.rep_q, precision, sg, lds, s, g, c);
+    else launch_seg_force_q<false, false, false>(a.rep_q, precision, sg, lds, s, g, c);
+    if (!one) {
+        switch (precision) {
+            case GILA_FP64: hipLaunchKernelGGL(seg_combine_kernel<GILA_FP64>, cg, cb, 0, s, c); break;
+            case GILA_FP32: hipLaunchKernelGGL(seg_combine_kernel<GILA_FP32>, cg, cb, 0, s, c); break;
+            default: hipLaunchKernelGGL(seg_combine_kernel<GILA_FP32_KAHAN>, cg, cb, 0, s, c); break;
+        }
     }
-    GILA_TRY(launch_iteration_stats(c, s));
     GILA_HIP(hipGetLastError());
     return GILA_OK;
 }

@@ -1,0 +1,71 @@
+"""The halting rule where an iteration's statistics are reduced beside the next
+one's forces: runs that stop at their first, a middle and their last
+iteration, on one-segment and many-segment graphs, in one captured range, in
+chunks and in split runs, against single steps whose statistics decide on the
+host.  The same kernels in the same order: the same bits."""
+import os
+
+import numpy as np
+import pytest
+
+from gpu_common import require_gpu
+from paper_1606_02162_amd import inputs
+
+pytestmark = pytest.mark.gpu
+PATHS = {"one_segment": {}, "segments": {"GILA_SEG_BYTES": "2048"},
+         "dense": {"GILA_DENSE_MIN": "1"}, "direct": {"GILA_PATH": "direct"}}
+
+
+@pytest.fixture(params=list(PATHS))
+def path(request, monkeypatch):
+    for k, v in PATHS[request.param].items():
+        monkeypatch.setenv(k, v)
+    return request.param
+
+
+@pytest.fixture(scope="module")
+def G():
+    require_gpu()
+    from paper_1606_02162_amd import gila
+    return gila
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_kahan"])
+@pytest.mark.parametrize("H,stop", [(1, 0), (6, 0), (6, 1), (7, 3), (7, 6), (7, None), (130, 101),
+                                    (130, 99), (130, None)])
+def test_stops_where_single_steps_do(G, path, precision, H, stop):
+    import torch
+    print(f"halting {path} {precision} H={H} stop={stop}", flush=True)
+    g = inputs.erdos_renyi(300, 800, seed=1)
+    rp, ci = G.to_device_csr(g)
+    prec = G.PRECISIONS[precision]
+    # every vertex moves by the cap until iteration `stop`, whose cap is below the threshold
+    temps = np.full(H, 0.5)
+    if stop is not None:
+        temps[stop] = 0.001
+    params = G.LayoutParams(temperature=temps, precision=prec, stop_fraction=0.5)
+    x = torch.from_numpy(inputs.uniform_positions(g.n, 3)).to(dtype=G.position_dtype(prec), device="cuda")
+    kh = G.build_khop(rp, ci, 2)
+    kh.enable_history(H)
+    ref, rows, ran = x.clone(), [], 0
+    for h in range(H):
+        st = G.step(kh, params, h, ref)
+        rows.append((st.energy, st.max_disp, float(st.moved), float(st.coincident)))
+        ran += 1
+        if stop is not None and h == stop:
+            break
+    kh.enable_history(H)
+    pos = x.clone()
+    st = G.run(kh, params, pos)
+    assert st.iterations_run == ran and st.stopped == (1 if stop is not None else 0)
+    assert torch.equal(pos, ref)
+    assert (st.energy, st.max_disp, float(st.moved), float(st.coincident)) == rows[-1]
+    hist = kh.history(0, H)
+    assert np.array_equal(hist[:ran], np.array(rows)) and np.isnan(hist[ran:]).all()
+    # split at an odd place: the same bits
+    pos = x.clone()
+    cut = min(3, H)
+    a = G.run(kh, params, pos, 0, cut)
+    if not a.stopped and cut < H:
+        G.run(kh, params, pos, cut, H)
+    assert torch.equal(pos, ref)
