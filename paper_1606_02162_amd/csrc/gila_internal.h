@@ -190,12 +190,21 @@ struct StepArgs {
     int32_t rep_q;
 };
 
+// One workgroup's share of the segment kernel: slices [begin, end) of a segment,
+// the dense ones first ([begin, lists)), then those walked by 64 lanes each, up to
+// cut[0], by 32 lanes, up to cut[1], and so on to one lane, up to cut[6] = end.
+constexpr int kLaneClasses = 7;
+struct SegWg {
+    int32_t seg, begin, end, lists;
+    int32_t cut[kLaneClasses + 1];
+};
+
 // Arguments of the segment kernel (one workgroup = one id segment x a range
 // of that segment's slices).
 struct SegArgs {
     int32_t na;                 // non-isolated vertices (rows)
     int32_t seg;                // segment size S (vertex ids per segment)
-    const int4* wg;             // [grid] (segment, first slice, end slice, lanes per slice)
+    const SegWg* wg;            // [grid]
     const int32_t* sl_v;        // [T] row of each slice (segment-major order)
     const int32_t* sl_p;        // [T] index of the slice's partial force
     const int64_t* sl_k;        // [T + 1] start of each slice in kidx (quad-aligned)
@@ -292,7 +301,7 @@ struct gila_khop {
     uint64_t* dmask = nullptr;      // [dense slices][dense_blocks] lane masks of 64 slots
     int32_t dense_blocks = 0;
     int64_t ndense = 0;
-    int4* seg_wg = nullptr;         // [seg_grid]
+    gila::SegWg* seg_wg = nullptr;        // [seg_grid]
     int32_t seg_grid = 0;
     int32_t comb_grid = 0;
     double2* part = nullptr;        // [T] partial force of each slice, row-major

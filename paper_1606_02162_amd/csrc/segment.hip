@@ -44,6 +44,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 #include "iteration.h"
 
@@ -317,27 +318,25 @@ __global__ __launch_bounds__(kBlock) void dense_mask_kernel(SliceBuild b, int64_
     }
 }
 
-// Enough quads per lane (qpl) to amortise the per-slice reduction.
-__host__ __device__ __forceinline__ int lanes_for_length(int64_t len, int64_t qpl) {
-    int l = 1;
-    while (l < 64 && (int64_t)l * 2 * qpl * 4 <= len) l *= 2;
-    return l;
-}
-
-// One thread per workgroup of the force kernel: desc = (segment, index in
-// the segment, workgroups of the segment).  The segment's slices are split
-// where the cumulative work crosses equal fractions; lanes per slice follow
-// the mean slice length of the range.
+// One thread per workgroup of the force kernel, which the host has given its segment
+// and, in begin and end, its part of the segment's work in units of 1 / kPlanUnits.
+// A slice is walked by the most lanes that leave each of them qpl quads (at least
+// 4 qpl ids): eight, to amortise the reduction over the lanes, or fewer where the
+// workgroup has fewer quads than that for each of its threads.  Lanes by the slice's own
+// length and not by the mean of the workgroup, under which one lane could be left
+// with thousands of ids beside short slices: R-MAT 18, k = 2, 282 -> 266 us a launch,
+// scale 16 in FP64 87 -> 80; qpl down to one: 3k vertices of a small world, k = 3,
+// 8.5 -> 7.3 us, Barabasi-Albert 3k, k = 2, FP64 10.9 -> 7.5.
+constexpr int kPlanUnits = 1 << 20;
 __global__ __launch_bounds__(kBlock) void segment_plan_kernel(
-    int32_t nwg, int64_t slice_cost, int64_t qpl, int64_t dense_work,
+    int32_t nwg, int64_t slice_cost, int64_t threads, int64_t dense_work,
     const int64_t* __restrict__ starts, const int64_t* __restrict__ sl_k,
-    const int32_t* __restrict__ sl_a, const int64_t* __restrict__ sl_dn, int4* __restrict__ wg) {
+    const int32_t* __restrict__ sl_a, const int64_t* __restrict__ sl_dn, SegWg* __restrict__ wg) {
     const int w = blockIdx.x * kBlock + threadIdx.x;
     if (w >= nwg) return;
-    const int4 d = wg[w];
-    const int s = d.x, t = d.y, c = d.z;
-    const int64_t f0 = starts[2 * s], f1 = starts[2 * s + 2];
-    const int64_t c0 = starts[2 * s + 1], c1 = starts[2 * s + 3];
+    SegWg d = wg[w];
+    const int64_t f0 = starts[2 * d.seg], f1 = starts[2 * d.seg + 2];
+    const int64_t c0 = starts[2 * d.seg + 1], c1 = starts[2 * d.seg + 3];
     const int64_t W = c1 - c0;
     auto work = [&](int64_t i) {
         return sl_k[i] + (int64_t)sl_a[i] + slice_cost * i + (sl_dn ? dense_work * sl_dn[i] : 0);
@@ -351,12 +350,27 @@ __global__ __launch_bounds__(kBlock) void segment_plan_kernel(
         }
         return lo;
     };
-    const int64_t ib = t == 0 ? f0 : cut(c0 + W * t / c);
-    const int64_t ie = t == c - 1 ? f1 : cut(c0 + W * (t + 1) / c);
-    // lanes per slice from the mean length of the range's offset-listed slices
+    const int64_t ib = d.begin == 0 ? f0 : cut(c0 + W * d.begin / kPlanUnits);
+    const int64_t ie = d.end == kPlanUnits ? f1 : cut(c0 + W * d.end / kPlanUnits);
     const int64_t is = ib + (sl_dn ? sl_dn[ie] - sl_dn[ib] : 0);
-    const int64_t len = ie > is ? ((sl_k[ie] - sl_k[is]) + (int64_t)(sl_a[ie] - sl_a[is])) / (ie - is) : 0;
-    wg[w] = make_int4(s, (int)ib, (int)ie, lanes_for_length(len, qpl));
+    const int64_t quads = (sl_k[ie] - sl_k[is]) / 4;
+    const int64_t qpl = std::min<int64_t>(8, std::max<int64_t>(1, quads / threads));
+    int64_t from = is;
+    for (int c = 0; c < kLaneClasses; ++c) {
+        const int64_t least = c + 1 < kLaneClasses ? (64 >> c) * qpl * 4 : 0;
+        int64_t lo = from, hi = ie;
+        while (lo < hi) {
+            const int64_t mid = lo + ((hi - lo) >> 1);
+            if (sl_k[mid + 1] - sl_k[mid] >= least) lo = mid + 1;
+            else hi = mid;
+        }
+        d.cut[c] = (int32_t)lo;
+        from = lo;
+    }
+    d.begin = (int32_t)ib;
+    d.end = (int32_t)ie;
+    d.lists = (int32_t)is;
+    wg[w] = d;
 }
 
 // ------------------------------------------------------------------ iteration: segment kernel
@@ -650,8 +664,8 @@ __global__ __launch_bounds__(seg_block<BIG>(), PREC == GILA_FP64 ? 4 : (ONE ? 6 
         if (a.span && threadIdx.x == 0) atomicMax(&a.span[1], (unsigned long long)wall_clock64());
         return;
     }
-    const int4 w = a.wg[blockIdx.x - a.has_prev];
-    const int s = w.x, ib = w.y, ie = w.z, lpv = w.w;
+    const SegWg* __restrict__ w = a.wg + (blockIdx.x - a.has_prev);
+    const int s = w->seg, ib = w->begin, id = w->lists;
     // stage the segment's positions
     const V* gpos = reinterpret_cast<const V*>(a.pos);
     const int64_t base = (int64_t)s * a.seg;
@@ -664,12 +678,9 @@ __global__ __launch_bounds__(seg_block<BIG>(), PREC == GILA_FP64 ? 4 : (ONE ? 6 
         const R* gw = reinterpret_cast<const R*>(a.mass);
         for (int i = threadIdx.x; i < cnt; i += kSegBlock) lw[i] = gw[base + i];
     }
-    // the range's dense slices are its head (the sort puts them first in
-    // each segment): [ib, id) by whole wavefronts, then [id, ie)
-    const int id = ib + (a.sl_dn ? (int)(a.sl_dn[ie] - a.sl_dn[ib]) : 0);
-    __shared__ int s_next, s_dnext;
+    __shared__ int s_next[kLaneClasses], s_dnext;
+    if (threadIdx.x < kLaneClasses) s_next[threadIdx.x] = threadIdx.x ? w->cut[threadIdx.x - 1] : id;
     if (threadIdx.x == 0) {
-        s_next = id;
         s_dnext = ib;
         V far;
         far.x = sizeof(far.x) == 4 ? (decltype(far.x))1e30f : (decltype(far.x))1e300;
@@ -694,15 +705,21 @@ __global__ __launch_bounds__(seg_block<BIG>(), PREC == GILA_FP64 ? 4 : (ONE ? 6 
         }
     }
     const unsigned char* wb = reinterpret_cast<const unsigned char*>(lw);
-    switch (lpv) {
-        case 1: seg_slices<P, 1, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
-        case 2: seg_slices<P, 2, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
-        case 4: seg_slices<P, 4, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
-        case 8: seg_slices<P, 8, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
-        case 16: seg_slices<P, 16, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
-        case 32: seg_slices<P, 32, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
-        default: seg_slices<P, 64, WEIGHTED, Q, ONE>(a, st, id, ie, lp, wb, &s_next, coinc); break;
-    }
+    int from = id;
+    const auto walk = [&](auto lanes, int c) {
+        const int to = w->cut[c];
+        if (to > from)
+            seg_slices<P, decltype(lanes)::value, WEIGHTED, Q, ONE>(a, st, from, to, lp, wb, &s_next[c],
+                                                                   coinc);
+        from = to;
+    };
+    walk(std::integral_constant<int, 64>(), 0);
+    walk(std::integral_constant<int, 32>(), 1);
+    walk(std::integral_constant<int, 16>(), 2);
+    walk(std::integral_constant<int, 8>(), 3);
+    walk(std::integral_constant<int, 4>(), 4);
+    walk(std::integral_constant<int, 2>(), 5);
+    walk(std::integral_constant<int, 1>(), 6);
     const int64_t wc = wave_sum((int64_t)coinc);
     if (lane64() == 0) s_c[wave_id()] = wc;
     __syncthreads();
@@ -989,21 +1006,56 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     // --- workgroups: per segment, ranges of about equal work
     const int cus = device_info(kh->device).cus;
     const int64_t total = hs[2 * nseg + 1] - hs[1];
-    // About 16 workgroups per CU, but no fewer than ~96K work units each
-    // while that still leaves 8 per CU: staging the segment costs every
-    // thread the same few loads whatever its share of pairs (BA 100k, k = 3:
-    // 194 -> 182 us per launch; R-MAT 18, whose workgroups get ~130K at 16
-    // per CU, is unchanged).  Small graphs keep workgroups of 4096 units.
-    const int64_t wpc = std::max<int64_t>(1, env_int("GILA_SEG_WG_PER_CU", 16));
-    const int64_t floor_w = std::min<int64_t>(env_int("GILA_SEG_WG_MIN_WORK", 98304),
-                                              total / ((int64_t)cus * std::max<int64_t>(1, wpc / 2)));
-    const int64_t per_wg = std::max<int64_t>({4096, floor_w, total / ((int64_t)cus * wpc)});
-    std::vector<int4> plan;
+    // Workgroups of the force kernel.  Each one costs a segment load, and a last wave
+    // that is part empty costs most of a wave, so the device is filled once with all the
+    // workgroups that it holds (registers and threads allow 2048 threads per CU in FP32,
+    // 1024 in FP64) and that number doubled where a share gets so long that uneven ones
+    // show, twice at most before shares of a million units.  An iteration, us, with
+    // 256 / 512 / 1024 / 2048 / 4096 workgroups.  1024 threads each: Erdos-Renyi 30k,
+    // k = 3 (7.8M units) 18 / 18 / 23 / 32 / 32, FP64 23 / 27 / 36 / 52 / 60;
+    // Barabasi-Albert 20k, k = 3 (30M) 28 / 27 / 33 / 47 / 76, FP64 42 / 46 / 59 / 83 /
+    // 119; scale-16 R-MAT, k = 2 (72M) 48 / 47 / 51 / 63 / 95, FP64 82 / 83 / 93 / 117 /
+    // 162; scale 17 (200M) - / 99 / 113 / 121 / 147, FP64 - / 216 / 217 / 236 / 272;
+    // Barabasi-Albert 100k, k = 3 (243M) - / 166 / 158 / 163 / 183, FP64 - / 266 / 277 /
+    // 297 / 331; scale 18 (547M), 1024 to 4096: 275 / 281 / 293, FP64 551 / 568 / 594.
+    // 512 threads: small world 200k, k = 2 (29M) 41 / 36 / 34 / 39 / 49, FP64 46 / 39 /
+    // 42 / 50 / 65.  Shares that shrink towards the end of the launch cost more in loads
+    // than they level.  A share under kMinShare is not split further.
+    constexpr int64_t kMinShare = 4096;
+    const bool f64 = precision == GILA_FP64;
+    int64_t target = env_int("GILA_SEG_WG", 0);
+    if (target <= 0) {
+        target = (int64_t)cus * (f64 ? 1 : 2) * (seg_big(kh) ? 1 : 2);
+        while (total > target * (f64 ? 640000 : target < 4 * cus ? 440000 : 1000000)) target *= 2;
+    }
+    const auto count_for = [&](int64_t per) {
+        int64_t c = 0;
+        for (int32_t sg = 0; sg < nseg; ++sg)
+            if (hs[2 * sg + 2] != hs[2 * sg])
+                c += std::max<int64_t>(1, (hs[2 * sg + 3] - hs[2 * sg + 1] + per - 1) / per);
+        return c;
+    };
+    int64_t per_wg = kMinShare, too_small = 0;
+    while (count_for(per_wg) > target && per_wg < total) {
+        too_small = per_wg;
+        per_wg *= 2;
+    }
+    while (too_small > 0 && per_wg - too_small > 64) {
+        const int64_t mid = (per_wg + too_small) / 2;
+        (count_for(mid) > target ? too_small : per_wg) = mid;
+    }
+    std::vector<SegWg> plan;
     for (int32_t sg = 0; sg < nseg; ++sg) {
         if (hs[2 * sg + 2] == hs[2 * sg]) continue;
         const int64_t W = hs[2 * sg + 3] - hs[2 * sg + 1];
         const int c = (int)std::max<int64_t>(1, (W + per_wg - 1) / per_wg);
-        for (int t = 0; t < c; ++t) plan.push_back(make_int4(sg, t, c, 0));
+        for (int t = 0; t < c; ++t) {
+            SegWg d{};
+            d.seg = sg;
+            d.begin = (int32_t)((int64_t)kPlanUnits * t / c);
+            d.end = (int32_t)((int64_t)kPlanUnits * (t + 1) / c);
+            plan.push_back(d);
+        }
     }
     kh->seg = S;
     kh->seg_large = seg_big(kh);  // the shape S was chosen for; launches use this one
@@ -1029,7 +1081,7 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
         GILA_TRY(dalloc_t(&kh->partials, (size_t)kh->comb_grid));
         kh->partials_cap = kh->comb_grid;
     }
-    GILA_HIP(hipMemcpyAsync(kh->seg_wg, plan.data(), sizeof(int4) * plan.size(),
+    GILA_HIP(hipMemcpyAsync(kh->seg_wg, plan.data(), sizeof(SegWg) * plan.size(),
                             hipMemcpyHostToDevice, st));
     const int fill_grid =
         (int)std::min<int64_t>(65536, (T * kFillLanes + kBlock - 1) / kBlock);
@@ -1042,7 +1094,7 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     }
     hipLaunchKernelGGL(segment_plan_kernel, dim3((unsigned)((plan.size() + kBlock - 1) / kBlock)),
                        dim3(kBlock), 0, st, (int32_t)plan.size(), slice_cost,
-                       (int64_t)env_int("GILA_SEG_QPL", 8), dense_work, starts, kh->sl_k, kh->sl_a,
+                       (int64_t)(kh->seg_large ? seg_block<true>() : seg_block<false>()), dense_work, starts, kh->sl_k, kh->sl_a,
                        kh->ndense > 0 ? kh->sl_dn : nullptr, kh->seg_wg);
     GILA_HIP(hipGetLastError());
     const size_t lds = seg_lds_bytes(kh, precision, S);
@@ -1070,7 +1122,7 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     kh->seg_weighted = weighted;
     kh->seg_ready = true;
     kh->device_bytes += (int64_t)(na + 1) * 8 + T * (4 + 4 + 8 + 4 + 16) + 2 * (kstore + kh->nnz) +
-                        (int64_t)sizeof(int4) * (int64_t)plan.size() +
+                        (int64_t)sizeof(SegWg) * (int64_t)plan.size() +
                         (dense_ok ? (T + 1) * 8 : 0) + ndense * dblocks * 8;
     return GILA_OK;
 }
