@@ -141,7 +141,11 @@ __global__ __launch_bounds__(kBlock) void validate_csr_kernel(int32_t n, int64_t
 // per source instead of O(n/32).
 // Frontier rows at least this long are walked by a whole wavefront.
 constexpr int64_t kWaveRow = 32;
+// The first kBfsSingles sources are taken one at a time, then kBfsTake (one atomic per
+// group, ~12 ns on one address): the hubs come first, and four of them one after the
+// other on one workgroup were the whole R-MAT 18 fill (3.3 ms; 2.5 taken singly).
 constexpr int32_t kBfsTake = 4;
+constexpr int32_t kBfsSingles = 4096;
 
 // BS threads per workgroup (256 or 512; see run_bfs).  With 512, registers
 // are capped so that 8 wavefronts fit per SIMD.
@@ -159,6 +163,8 @@ __global__ __launch_bounds__(BS, BS / 64) void khop_bfs_kernel(BfsArgs a) {
     __shared__ int32_t s_nbig;             // long rows listed in this chunk
     __shared__ int64_t s_red[kBfsWaves];
 
+    const int32_t nsrc = a.list ? a.work[1] : a.nverts;
+    if (nsrc == 0) return;
     uint32_t* bm = LDS_BITMAP ? s_dyn : a.gbitmap + (size_t)blockIdx.x * a.nwords;
     uint32_t* sm = s_dyn + a.nwords;  // summary (LDS bitmap only)
     int32_t* queue = a.queue ? a.queue + (size_t)blockIdx.x * a.qcap : nullptr;
@@ -177,14 +183,15 @@ __global__ __launch_bounds__(BS, BS / 64) void khop_bfs_kernel(BfsArgs a) {
         return !(old & bit);
     };
 
-    // sources are taken kBfsTake at a time (one atomic per group)
     for (;;) {
-        if (threadIdx.x == 0) s_v = atomicAdd(a.work, kBfsTake);
+        if (threadIdx.x == 0) s_v = atomicAdd(a.work, 1);
         __syncthreads();
-        const int32_t v0 = s_v;
-        if (v0 >= a.nverts) break;
-        const int32_t v1 = min(v0 + kBfsTake, a.nverts);
-        for (int32_t v = v0; v < v1; ++v) {
+        const int32_t c = s_v;
+        const int32_t v0 = c < kBfsSingles ? c : kBfsSingles + (c - kBfsSingles) * kBfsTake;
+        if (v0 >= nsrc) break;
+        const int32_t v1 = min(v0 + (c < kBfsSingles ? 1 : kBfsTake), nsrc);
+        for (int32_t vi = v0; vi < v1; ++vi) {
+            const int32_t v = a.list ? a.list[vi] : vi;
             // the source's graph: id base, bitmap words and k
             int64_t base = 0;
             int32_t nw = a.nwords, k = a.k;
@@ -385,6 +392,210 @@ __global__ __launch_bounds__(BS, BS / 64) void khop_bfs_kernel(BfsArgs a) {
     }
 }
 
+// ------------------------------------------------------------------ short rows
+// Sources with at most kWaveCap ids within k hops, one wavefront each: the ids
+// found so far are a hash set in LDS and a list, which is the frontier queue and,
+// sorted, the row.  A source costs a chain of dependent row reads whatever the size of
+// its row, so what counts is the number of sources in flight: 24 per CU here
+// (6 KB each) against the 4 or 8 of khop_bfs_kernel, whose workgroups mostly wait at
+// barriers on such rows: Watts-Strogatz 200k, k = 2 (18 ids a row), count 692 -> 96 us,
+// fill 1377 -> 103, adjacency sort 593 -> 104.  A source that outgrows the cap is left
+// to khop_bfs_kernel (counts[v] = -1; the fill pass knows the length); finding that out
+// takes 172 us for R-MAT 18, whose count pass falls from 2.6 ms to 1.5 (with the order
+// of long_rows_list_kernel) all the same.
+constexpr int kWaveCap = 512;
+constexpr uint32_t kWaveTable = 1024;  // at most kWaveCap + 64 + 1 entries are taken
+constexpr uint32_t kNoId = ~0u;
+
+// Orders LDS accesses of one wavefront (which the hardware executes in order).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) void khop_wave_kernel(BfsArgs a) {
+    __shared__ __align__(16) uint32_t s_tab[kWaves][kWaveTable];
+    __shared__ int32_t s_list[kWaves][kWaveCap + 64];
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id());
+    uint32_t* tab = s_tab[wave];
+    int32_t* list = s_list[wave];
+    const int lane = lane64();
+    const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+    for (int64_t v = (int64_t)blockIdx.x * kWaves + wave; v < a.nverts; v += nwaves) {
+        const int64_t rb = a.rp[v], re = a.rp[v + 1];
+        int64_t out = 0, len = 0;
+        if constexpr (FILL) {
+            out = a.kptr[v];
+            len = a.kptr[v + 1] - out;
+            if (len == 0 || len > kWaveCap) continue;
+        }
+        if (re - rb > kWaveCap) {
+            if (!FILL && lane == 0) a.counts[v] = -1;
+            continue;
+        }
+        int n = 0;  // ids found, uniform
+        if (a.k == 1) {
+            n = (int)(re - rb);
+            if constexpr (FILL)
+                for (int i = lane; i < n; i += 64) list[i] = a.ci[rb + i];
+        } else {
+            for (uint32_t i = lane * 4; i < kWaveTable; i += 256)
+                *reinterpret_cast<uint4*>(tab + i) = make_uint4(kNoId, kNoId, kNoId, kNoId);
+            wave_lds_fence();
+            // adds u (where take) to the set and the new ones to the list
+            auto add = [&](bool take, uint32_t u) {
+                bool fresh = false;
+                if (take) {
+                    uint32_t h = (u * 2654435769u) >> 22;
+                    for (;;) {
+                        const uint32_t old = atomicCAS(&tab[h], kNoId, u);
+                        if (old == kNoId) fresh = true;
+                        if (old == kNoId || old == u) break;
+                        h = (h + 1) & (kWaveTable - 1);
+                    }
+                }
+                const uint64_t m = __ballot(fresh);
+                if (fresh) list[n + __popcll(m & ((1ull << lane) - 1))] = (int32_t)u;
+                n += __popcll(m);
+            };
+            if (lane == 0) tab[((uint32_t)v * 2654435769u) >> 22] = (uint32_t)v;
+            wave_lds_fence();
+            for (int64_t e = rb; e < re; e += 64)
+                add(e + lane < re, e + lane < re ? (uint32_t)a.ci[e + lane] : 0u);
+            // (a simple graph's row has re - rb distinct ids: n <= kWaveCap here)
+            int from = 0;
+            for (int level = 2; level <= a.k && n <= kWaveCap; ++level) {
+                const int to = n;
+                if (from == to) break;
+                for (int c = from; c < to && n <= kWaveCap; c += 64) {
+                    wave_lds_fence();
+                    int64_t start = 0;
+                    int deg = 0;
+                    if (c + lane < to) {
+                        const int32_t w = list[c + lane];
+                        start = a.rp[w];
+                        const int64_t d = a.rp[w + 1] - start;
+                        // (w and its row but for v are ids within k hops: too many)
+                        deg = d > kWaveCap ? kWaveCap + 1 : (int)d;
+                    }
+                    if (__ballot(deg > kWaveCap)) {
+                        n = kWaveCap + 1;
+                        break;
+                    }
+                    // the entries of these rows one after another, 64 at a time
+                    const int inc = wave_inclusive_scan(deg);
+                    const int total = __shfl(inc, 63, 64);
+                    const int64_t first = start - (inc - deg);  // entry t of the run: ci[first + t]
+                    for (int t0 = 0; t0 < total && n <= kWaveCap; t0 += 64) {
+                        const int t = t0 + lane;
+                        int o = 0;  // the row of entry t: the first with inc > t
+#pragma unroll
+                        for (int s = 32; s >= 1; s >>= 1)
+                            if (__shfl(inc, o + s - 1, 64) <= t) o += s;
+                        const int64_t at = __shfl(first, o & 63, 64) + t;
+                        add(t < total, t < total ? (uint32_t)a.ci[at] : 0u);
+                    }
+                }
+                from = to;
+            }
+        }
+        if constexpr (!FILL) {
+            if (lane == 0) a.counts[v] = n > kWaveCap ? -1 : n;
+        } else {
+            wave_lds_fence();
+            int32_t* row = a.kidx + out;
+            n = min(n, (int)len);
+            if (n <= 64) {
+                int32_t x = lane < n ? list[lane] : INT32_MAX;
+#pragma unroll
+                for (int size = 2; size <= 64; size *= 2)
+#pragma unroll
+                    for (int s = size / 2; s >= 1; s /= 2) {
+                        const int32_t y = __shfl_xor(x, s, 64);
+                        const bool low = ((lane & s) == 0) == ((lane & size) == 0);
+                        x = low ? min(x, y) : max(x, y);
+                    }
+                if (lane < n) row[lane] = x;
+            } else {
+                int p2 = 128;
+                while (p2 < n) p2 *= 2;
+                for (int i = n + lane; i < p2; i += 64) list[i] = INT32_MAX;
+                for (int size = 2; size <= p2; size *= 2)
+                    for (int s = size / 2; s >= 1; s /= 2) {
+                        wave_lds_fence();
+                        for (int q = lane; q < p2 / 2; q += 64) {
+                            const int i = 2 * q - (q & (s - 1)), j = i + s;
+                            const int32_t x = list[i], y = list[j];
+                            if ((x > y) == ((i & size) == 0)) {
+                                list[i] = y;
+                                list[j] = x;
+                            }
+                        }
+                    }
+                wave_lds_fence();
+                for (int i = lane; i < n; i += 64) row[i] = list[i];
+            }
+            wave_lds_fence();
+        }
+    }
+}
+
+// The sources that khop_wave_kernel leaves, listed in order, those of more than
+// kWaveCap neighbours first: a hub begun last would be waited for alone (the R-MAT 18
+// fill, whose order has the longest rows first, took 4.6 ms with the tiles of the list
+// in the order of an atomic counter, 3.3 in order).  First the numbers in each tile of
+// kListTile ids, then the list.
+constexpr int kListTile = kBlock * 8;
+template <bool FILL>
+__device__ __forceinline__ uint2 long_rows_of(const BfsArgs& a, int64_t v0) {
+    uint2 bits = make_uint2(0, 0);  // hubs, others
+    for (int i = 0; i < 8; ++i) {
+        const int64_t v = v0 + i;
+        if (v >= a.nverts) break;
+        if (FILL ? a.kptr[v + 1] - a.kptr[v] > kWaveCap : a.counts[v] < 0)
+            (a.rp[v + 1] - a.rp[v] > kWaveCap ? bits.x : bits.y) |= 1u << i;
+    }
+    return bits;
+}
+
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) void long_rows_count_kernel(BfsArgs a, int2* __restrict__ tiles) {
+    __shared__ int32_t s_red[kWaves];
+    const uint2 bits = long_rows_of<FILL>(a, (int64_t)blockIdx.x * kListTile + threadIdx.x * 8);
+    const int32_t hubs = block_sum<int32_t>(__popc(bits.x), s_red);
+    const int32_t others = block_sum<int32_t>(__popc(bits.y), s_red);
+    if (threadIdx.x == 0) tiles[blockIdx.x] = make_int2(hubs, others);
+}
+
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) void long_rows_list_kernel(BfsArgs a, const int2* __restrict__ tiles,
+                                                                int32_t* __restrict__ list) {
+    __shared__ int32_t s_red[kWaves];
+    const int64_t v0 = (int64_t)blockIdx.x * kListTile + threadIdx.x * 8;
+    int32_t before = 0, others_before = 0, hubs = 0, others = 0;
+    for (int t = threadIdx.x; t < (int)gridDim.x; t += kBlock) {
+        const int2 c = tiles[t];
+        hubs += c.x;
+        others += c.y;
+        if (t < (int)blockIdx.x) {
+            before += c.x;
+            others_before += c.y;
+        }
+    }
+    before = block_sum<int32_t>(before, s_red);
+    others_before = block_sum<int32_t>(others_before, s_red);
+    hubs = block_sum<int32_t>(hubs, s_red);
+    others = block_sum<int32_t>(others, s_red);
+    const uint2 bits = long_rows_of<FILL>(a, v0);
+    int32_t total;
+    int32_t at = before + block_exclusive_scan<int32_t>(__popc(bits.x), s_red, total);
+    for (uint32_t b = bits.x; b; b &= b - 1u) list[at++] = (int32_t)(v0 + __builtin_ctz(b));
+    at = hubs + others_before + block_exclusive_scan<int32_t>(__popc(bits.y), s_red, total);
+    for (uint32_t b = bits.y; b; b &= b - 1u) list[at++] = (int32_t)(v0 + __builtin_ctz(b));
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.work[1] = hubs + others;
+}
+
 // ------------------------------------------------------------------ relabelling
 // Internal row i is caller row perm[i] with every id mapped through iperm.
 __global__ __launch_bounds__(kBlock) void relabel_csr_kernel(
@@ -514,9 +725,38 @@ int run_bfs(bool fill, int device, hipStream_t s, BfsArgs a) {
             return rc;
         }
     }
+    // One graph's short rows by khop_wave_kernel (GILA_BFS_BITMAP: every row by
+    // khop_bfs_kernel, with that bitmap).
+    int32_t* list = nullptr;  // the numbers in each tile, then the sources left
+    const int64_t list_tiles = std::max<int64_t>(1, ((int64_t)a.nverts + kListTile - 1) / kListTile);
+    if (!a.gvbase && !bm_env) {
+        int rc = dalloc_t(&list, (size_t)std::max(1, a.nverts) + 2 * (size_t)list_tiles);
+        if (rc) {
+            dfree_on(a.queue, s);
+            dfree_on(a.gbitmap, s);
+            return rc;
+        }
+    }
     int rc = GILA_OK;
     hipError_t e = hipSuccess;
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, s, a.work);
+    if (list) {
+        const unsigned wgrid = (unsigned)std::min<int64_t>((int64_t)di.cus * 6,
+                                                           ((int64_t)a.nverts + kWaves - 1) / kWaves);
+        const unsigned lgrid = (unsigned)list_tiles;
+        int2* tiles = reinterpret_cast<int2*>(list);
+        int32_t* sources = list + 2 * list_tiles;
+        if (fill) {
+            hipLaunchKernelGGL(khop_wave_kernel<true>, dim3(wgrid), dim3(kBlock), 0, s, a);
+            hipLaunchKernelGGL(long_rows_count_kernel<true>, dim3(lgrid), dim3(kBlock), 0, s, a, tiles);
+            hipLaunchKernelGGL(long_rows_list_kernel<true>, dim3(lgrid), dim3(kBlock), 0, s, a, tiles, sources);
+        } else {
+            hipLaunchKernelGGL(khop_wave_kernel<false>, dim3(wgrid), dim3(kBlock), 0, s, a);
+            hipLaunchKernelGGL(long_rows_count_kernel<false>, dim3(lgrid), dim3(kBlock), 0, s, a, tiles);
+            hipLaunchKernelGGL(long_rows_list_kernel<false>, dim3(lgrid), dim3(kBlock), 0, s, a, tiles, sources);
+        }
+        a.list = sources;
+    }
     const size_t shm = lds ? bm_bytes : 0;
     auto launch = [&](auto kernel, int threads) {
         if (shm > 65536)
@@ -542,6 +782,7 @@ int run_bfs(bool fill, int device, hipStream_t s, BfsArgs a) {
         rc = fail(GILA_EDEVICE, "k-hop kernel: %s", hipGetErrorString(se));
     dfree_on(a.queue, s);
     dfree_on(a.gbitmap, s);
+    dfree_on(list, s);
     return rc;
 }
 
@@ -669,8 +910,8 @@ int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out) {
     GILA_TRY(validate_graph(g, s, kLocalWindow, &checked));
     kh->n_active = checked.active;
     const unsigned long long near_edges = checked.near;
-    int32_t* d_work = nullptr;  // BFS work counter
-    GILA_TRY(dalloc_t(&d_work, 1));
+    int32_t* d_work = nullptr;  // BFS work counters
+    GILA_TRY(dalloc_t(&d_work, 2));
     struct F {
         int32_t* p;
         hipStream_t s;
@@ -762,7 +1003,7 @@ int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out) {
         a.n = n;
         a.k = 1;
         a.nverts = n_active;
-        a.nwords = nwords;
+        a.nwords = (n_active + 31) / 32;
         a.rp = kh->rp;
         a.ci = kh->ci;
         a.kptr = kh->rp;
@@ -784,7 +1025,7 @@ int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out) {
         a.n = n;
         a.k = k;
         a.nverts = n_active;
-        a.nwords = nwords;
+        a.nwords = (n_active + 31) / 32;
         a.rp = kh->rp;
         a.ci = kh->ci;
         a.kptr = kh->kptr;
