@@ -84,4 +84,10 @@ __device__ __forceinline__ T wave_max(T v) {
     return v;
 }
 
+// Orders LDS accesses of one wavefront (which the hardware executes in order).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 }  // namespace gila

@@ -247,7 +247,7 @@ struct BfsArgs {
     int32_t* queue;            // [grid][qcap] frontier storage (k >= 3)
     int64_t qcap;
     uint32_t* gbitmap;         // [grid][nwords] when the bitmap is not in LDS
-    int32_t* work;             // next source (atomic); with list also its length, work[1]
+    int32_t* work;             // next source (atomic); with list also its length in work[1]
     const int32_t* list;       // null, or the sources (one graph): those left by khop_wave_kernel
     // batch mode (gvbase != nullptr)
     const int64_t* gvbase;     // [ngraphs + 1] first vertex of each graph

@@ -366,7 +366,26 @@ __global__ __launch_bounds__(BS, BS / 64) void khop_bfs_kernel(BfsArgs a) {
                                     if (h >= off) inc += y;
                                 }
                                 int64_t o = pos + s_lex[j] + (inc - cnt);
-                                emit(wi, word, o);
+                                // Where the words hold four ids or more on average,
+                                // the half takes one word after another, lane h its
+                                // bit h: neighbouring lanes store neighbouring ids
+                                // (R-MAT 18 fill 2.47 -> 2.27 ms).
+                                uint32_t left = (uint32_t)(__ballot(word != 0u) >> (half * 32));
+                                if (__shfl(inc, 31, 32) >= 4 * __popc(left)) {
+                                    for (; left; left &= left - 1u) {
+                                        const int w = __builtin_ctz(left);
+                                        const uint32_t x = __shfl(word, w, 32);
+                                        const int64_t at = pos + s_lex[j] + __shfl(inc - cnt, w, 32) +
+                                                           __popc(x & ((1u << h) - 1u));
+                                        if ((x >> h & 1u) && at < end) {
+                                            const int64_t local = ((int64_t)s_lsi[j] * 32 + w) * 32 + h;
+                                            if (a.kidx16) a.kidx16[at] = (uint16_t)local;
+                                            else a.kidx[at] = (int32_t)(base + local);
+                                        }
+                                    }
+                                } else {
+                                    emit(wi, word, o);
+                                }
                                 if (wi < nw) bm[wi] = 0u;
                             }
                             pos += total;
@@ -406,12 +425,6 @@ __global__ __launch_bounds__(BS, BS / 64) void khop_bfs_kernel(BfsArgs a) {
 constexpr int kWaveCap = 512;
 constexpr uint32_t kWaveTable = 1024;  // at most kWaveCap + 64 + 1 entries are taken
 constexpr uint32_t kNoId = ~0u;
-
-// Orders LDS accesses of one wavefront (which the hardware executes in order).
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 template <bool FILL>
 __global__ __launch_bounds__(kBlock) void khop_wave_kernel(BfsArgs a) {

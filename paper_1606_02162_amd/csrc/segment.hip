@@ -250,7 +250,6 @@ __global__ __launch_bounds__(kBlock) void slice_fill_kernel(
     const int64_t g = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kFillLanes;
     const int64_t ng = ((int64_t)gridDim.x * kBlock) / kFillLanes;
     const int gl = threadIdx.x % kFillLanes;
-    const uint16_t sentinel = (uint16_t)(b.S * b.pos_bytes);
     for (int64_t i = g; i < T; i += ng) {
         const int32_t j = order[i];
         const int32_t s = b.d_seg[j];
@@ -258,8 +257,19 @@ __global__ __launch_bounds__(kBlock) void slice_fill_kernel(
         const int64_t k0 = b.d_k0[j];
         const int32_t kn = b.d_kn[j];
         const int64_t dst = sl_k[i], kpad = sl_k[i + 1] - dst;
-        for (int64_t t = gl; t < kpad; t += kFillLanes)
-            sk_idx[dst + t] = t < kn ? (uint16_t)((b.kidx[k0 + t] - lo) * b.pos_bytes) : sentinel;
+        // one quad of offsets per lane and step, 16 bytes read and 8 written (R-MAT 18,
+        // k = 2: 1018 -> 754 us for the 3 GB)
+        for (int64_t t = gl * 4; t < kpad; t += kFillLanes * 4) {
+            int32_t id[4];
+            if (t + 4 <= kn) {
+                __builtin_memcpy(id, b.kidx + k0 + t, sizeof(id));
+            } else {
+                for (int u = 0; u < 4; ++u) id[u] = t + u < kn ? b.kidx[k0 + t + u] : lo + b.S;
+            }
+            uint32_t o[4];
+            for (int u = 0; u < 4; ++u) o[u] = (uint32_t)(id[u] - lo) * (uint32_t)b.pos_bytes;
+            *reinterpret_cast<uint2*>(sk_idx + dst + t) = make_uint2(o[0] | o[1] << 16, o[2] | o[3] << 16);
+        }
         const int32_t a0 = b.d_a0[j], an = b.d_an[j];
         const int64_t adst = sl_a64[i];
         for (int32_t t = gl; t < an; t += kFillLanes)
@@ -273,52 +283,48 @@ __global__ __launch_bounds__(kBlock) void slice_fill_kernel(
     }
 }
 
-// The bitmap of each dense slice, one wavefront per slice: slot 64 b + l is
-// bit l of mask b.  The slice's ids are ascending, so each 64-id chunk spans
-// a few consecutive masks; each mask is the OR over the wavefront of its
-// lanes' bits, kept in a register while later chunks may still add to it and
-// written once (masks no id reaches stay zero).
-__global__ __launch_bounds__(kBlock) void dense_mask_kernel(SliceBuild b, int64_t T,
+// The bitmap of each dense slice, one wavefront per slice: slot 64 b + l is bit l of
+// mask b.  Each id sets its slot's byte in LDS and each mask is a ballot over 64 of the
+// bytes: no reduction per mask, whose chain of lane exchanges was the time before
+// (R-MAT 18, k = 2: 671 -> 278 us).  The wavefront finds its slice, the di-th dense
+// one, in the counts sl_dn.
+constexpr int kMaxDenseSlots = 8192;
+__global__ __launch_bounds__(kBlock) void dense_mask_kernel(SliceBuild b, int64_t T, int64_t ndense,
                                                             const int32_t* __restrict__ order,
                                                             const int64_t* __restrict__ sl_dn,
                                                             int32_t dense_blocks,
                                                             uint64_t* __restrict__ dmask) {
-    const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * kBlock) >> 6;
+    __shared__ __align__(16) unsigned char s_slot[kWaves][kMaxDenseSlots];
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id());
+    unsigned char* slot = s_slot[wave];
     const int lane = lane64();
-    for (int64_t i = wave; i < T; i += nwaves) {
-        if (sl_dn[i + 1] == sl_dn[i]) continue;
+    for (int64_t di = (int64_t)blockIdx.x * kWaves + wave; di < ndense; di += (int64_t)gridDim.x * kWaves) {
+        for (int t = lane * 16; t < dense_blocks * 64; t += 1024)
+            *reinterpret_cast<uint4*>(slot + t) = make_uint4(0, 0, 0, 0);
+        // the last slice with di dense ones before it
+        const int64_t i = lower_bound_ids(sl_dn, 0, T + 1, di + 1) - 1;
         const int32_t j = order[i];
         const int32_t lo = b.d_seg[j] * b.S;
-        const int64_t k0 = b.d_k0[j];
+        const int32_t* __restrict__ ids = b.kidx + b.d_k0[j];
         const int32_t kn = b.d_kn[j];
-        uint64_t* m = dmask + sl_dn[i] * dense_blocks;
-        uint64_t cur = 0;
-        int32_t curw = -1;
-        for (int32_t c = 0; c < kn; c += 64) {
-            const int32_t t = c + lane;
-            const int32_t local = t < kn ? b.kidx[k0 + t] - lo : 0;
-            const int32_t w = t < kn ? local >> 6 : -1;
-            const uint64_t bit = t < kn ? 1ull << (local & 63) : 0ull;
-            const int32_t wlo = __builtin_amdgcn_readfirstlane(w);
-            const int32_t whi = __shfl(w, kn - c < 64 ? kn - c - 1 : 63, 64);
-            for (int32_t ww = wlo; ww <= whi; ++ww) {
-                uint64_t v = w == ww ? bit : 0ull;
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) v |= __shfl_xor(v, off, 64);
-                if (ww != curw) {
-                    if (curw >= 0 && lane == 0) m[curw] = cur;
-                    cur = 0;
-                    curw = ww;
-                }
-                cur |= v;
+        wave_lds_fence();
+        for (int32_t t = lane; t < kn; t += 64) slot[ids[t] - lo] = 1;
+        wave_lds_fence();
+        uint64_t* m = dmask + di * dense_blocks;
+        for (int32_t w0 = 0; w0 < dense_blocks; w0 += 64) {
+            uint64_t mine = 0;
+            const int32_t nw = min(64, dense_blocks - w0);
+            for (int32_t w = 0; w < nw; ++w) {
+                const uint64_t x = __ballot(slot[(w0 + w) * 64 + lane] != 0);
+                if (w == lane) mine = x;
             }
+            if (lane < nw) m[w0 + lane] = mine;
         }
-        if (curw >= 0 && lane == 0) m[curw] = cur;
+        wave_lds_fence();
     }
 }
 
-// One thread per workgroup of the force kernel, which the host has given its segment
+// kPlanLanes threads per workgroup of the force kernel, which the host has given its segment
 // and, in begin and end, its part of the segment's work in units of 1 / kPlanUnits.
 // A slice is walked by the most lanes that leave each of them qpl quads (at least
 // 4 qpl ids): eight, to amortise the reduction over the lanes, or fewer where the
@@ -328,13 +334,14 @@ __global__ __launch_bounds__(kBlock) void dense_mask_kernel(SliceBuild b, int64_
 // scale 16 in FP64 87 -> 80; qpl down to one: 3k vertices of a small world, k = 3,
 // 8.5 -> 7.3 us, Barabasi-Albert 3k, k = 2, FP64 10.9 -> 7.5.
 constexpr int kPlanUnits = 1 << 20;
+constexpr int kPlanLanes = kLaneClasses + 1;
 __global__ __launch_bounds__(kBlock) void segment_plan_kernel(
     int32_t nwg, int64_t slice_cost, int64_t threads, int64_t dense_work,
     const int64_t* __restrict__ starts, const int64_t* __restrict__ sl_k,
     const int32_t* __restrict__ sl_a, const int64_t* __restrict__ sl_dn, SegWg* __restrict__ wg) {
-    const int w = blockIdx.x * kBlock + threadIdx.x;
+    const int w = (blockIdx.x * kBlock + threadIdx.x) / kPlanLanes, c = threadIdx.x % kPlanLanes;
     if (w >= nwg) return;
-    SegWg d = wg[w];
+    const SegWg d = wg[w];
     const int64_t f0 = starts[2 * d.seg], f1 = starts[2 * d.seg + 2];
     const int64_t c0 = starts[2 * d.seg + 1], c1 = starts[2 * d.seg + 3];
     const int64_t W = c1 - c0;
@@ -355,22 +362,23 @@ __global__ __launch_bounds__(kBlock) void segment_plan_kernel(
     const int64_t is = ib + (sl_dn ? sl_dn[ie] - sl_dn[ib] : 0);
     const int64_t quads = (sl_k[ie] - sl_k[is]) / 4;
     const int64_t qpl = std::min<int64_t>(8, std::max<int64_t>(1, quads / threads));
-    int64_t from = is;
-    for (int c = 0; c < kLaneClasses; ++c) {
-        const int64_t least = c + 1 < kLaneClasses ? (64 >> c) * qpl * 4 : 0;
-        int64_t lo = from, hi = ie;
-        while (lo < hi) {
-            const int64_t mid = lo + ((hi - lo) >> 1);
-            if (sl_k[mid + 1] - sl_k[mid] >= least) lo = mid + 1;
-            else hi = mid;
-        }
-        d.cut[c] = (int32_t)lo;
-        from = lo;
+    // lane c of the workgroup's lanes finds the end of lane class c, the last lane
+    // writes the rest (wg[w] has been read by the whole wavefront)
+    __builtin_amdgcn_wave_barrier();
+    if (c == kLaneClasses) {
+        wg[w].begin = (int32_t)ib;
+        wg[w].end = (int32_t)ie;
+        wg[w].lists = (int32_t)is;
+        return;
     }
-    d.begin = (int32_t)ib;
-    d.end = (int32_t)ie;
-    d.lists = (int32_t)is;
-    wg[w] = d;
+    const int64_t least = c + 1 < kLaneClasses ? (64 >> c) * qpl * 4 : 0;
+    int64_t lo = is, hi = ie;
+    while (lo < hi) {
+        const int64_t mid = lo + ((hi - lo) >> 1);
+        if (sl_k[mid + 1] - sl_k[mid] >= least) lo = mid + 1;
+        else hi = mid;
+    }
+    wg[w].cut[c] = (int32_t)lo;
 }
 
 // ------------------------------------------------------------------ iteration: segment kernel
@@ -926,7 +934,8 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     // (dblocks, a whole number of the kernel's eight-block steps).
     const int32_t dblocks = ((S + 63) / 64 + 7) / 8 * 8;
     const int dense_permille = env_int("GILA_DENSE_MIN", 750);
-    const bool dense_ok = precision != GILA_FP64 && dense_permille > 0;
+    const bool dense_ok =
+        precision != GILA_FP64 && dense_permille > 0 && (int64_t)dblocks * 64 <= kMaxDenseSlots;
     const int32_t dmin =
         dense_ok ? std::max<int32_t>(64, (int32_t)((int64_t)S * dense_permille / 1000)) : 0;
     const int64_t dense_work = S;
@@ -1070,9 +1079,7 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     kh->ndense = ndense;
     kh->dense_blocks = ndense > 0 ? dblocks : 0;
     if (ndense > 0) {
-        const size_t masks = (size_t)ndense * dblocks;
-        GILA_TRY(dalloc_t(&kh->dmask, masks));
-        GILA_HIP(hipMemsetAsync(kh->dmask, 0, masks * sizeof(uint64_t), st));
+        GILA_TRY(dalloc_t(&kh->dmask, (size_t)ndense * dblocks));
     }
     if (kh->comb_grid > kh->partials_cap) {
         dfree_on(kh->partials, st);
@@ -1088,11 +1095,11 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     hipLaunchKernelGGL(slice_fill_kernel, dim3(fill_grid), dim3(kBlock), 0, st, b, T, order,
                        kh->sl_k, sl_a64, kh->sk_idx, kh->sa_idx, kh->sl_v, kh->sl_p, kh->sl_a);
     if (ndense > 0) {
-        const int mgrid = (int)std::min<int64_t>(4096, (T * 64 + kBlock - 1) / kBlock);
-        hipLaunchKernelGGL(dense_mask_kernel, dim3(mgrid), dim3(kBlock), 0, st, b, T, order,
+        const int mgrid = (int)std::min<int64_t>(4096, (ndense + kWaves - 1) / kWaves);
+        hipLaunchKernelGGL(dense_mask_kernel, dim3(mgrid), dim3(kBlock), 0, st, b, T, ndense, order,
                            kh->sl_dn, dblocks, kh->dmask);
     }
-    hipLaunchKernelGGL(segment_plan_kernel, dim3((unsigned)((plan.size() + kBlock - 1) / kBlock)),
+    hipLaunchKernelGGL(segment_plan_kernel, dim3((unsigned)((plan.size() * kPlanLanes + kBlock - 1) / kBlock)),
                        dim3(kBlock), 0, st, (int32_t)plan.size(), slice_cost,
                        (int64_t)(kh->seg_large ? seg_block<true>() : seg_block<false>()), dense_work, starts, kh->sl_k, kh->sl_a,
                        kh->ndense > 0 ? kh->sl_dn : nullptr, kh->seg_wg);
