@@ -190,65 +190,77 @@ __global__ void gather_bounds_kernel(const int64_t* __restrict__ kptr,
 }
 
 // ------------------------------------------------------------------ k-hop lists of small graphs
-// One workgroup per graph (largest first): the graph's CSR is copied into LDS
-// with local ids, then each wavefront takes one source at a time and runs a
-// level-synchronous BFS to depth k on three bitmaps of its own in LDS
-// (visited, this level, next level), deduplicating with LDS atomic ORs.  The
-// count pass writes |N_v(k)|; the fill pass writes the row ascending by
-// scanning the visited bitmap.  Used when every graph of the batch fits.
+// One workgroup per unit, at most kUnitSources sources of one graph (largest first):
+// the graph's CSR is copied into LDS with local ids, then each wavefront takes one
+// source at a time and runs a level-synchronous BFS to depth k on a visited bitmap of
+// its own in LDS, deduplicating with LDS atomic ORs, and writes the row ascending by
+// scanning that bitmap.  A level's new vertices are listed (in up to list_cap entries)
+// and their rows walked one after another, an entry per lane: with a lane per frontier
+// vertex the longest row of each level was waited for, and with whole graphs for units the
+// largest graph (1000 random trees of 50 to 5000 vertices, k = 3: 2275 -> 1351 us).
+// A level that outgrows the list is followed by one that expands every vertex visited
+// so far, from a copy of the bitmap: the same set.  Used when every graph of the batch
+// fits.
 // Workgroups of 1024 threads (16 wavefronts share one graph, so that the
 // largest graphs, taken first, do not leave a long tail) when the per-wave
 // bitmaps fit beside the graph in LDS, else 512.
 
 struct BatchBfsArgs {
-    int32_t count;
-    const int32_t* gorder;   // graphs, largest first
+    int32_t units;
+    const int4* unit;        // [units]: graph, first source, end source; largest first
     const int64_t* vbase;    // [count + 1]
     const int64_t* rp;       // union CSR (global ids)
     const int32_t* ci;
     const int32_t* gk;       // k of each graph
-    const int64_t* gbase;    // [count]: start of each graph's block of kidx
+    const int64_t* bound;    // [nv]: the sum of the walk bounds of the rows before each
     int64_t* counts;         // [nv]: |N_v(k)|
     int64_t* kstart;         // [nv]: start of each row in kidx
     int32_t* klen;           // [nv]: its length, padded to whole quads
     uint16_t* kidx;          // local ids, each row padded with the sentinel n
-    int32_t* work;           // next graph (atomic)
+    int32_t* work;           // next unit (atomic)
     int32_t nmax;            // largest graph: vertices ...
     int64_t nnzmax;          // ... and adjacency entries
 };
 
+constexpr int kUnitSources = 512;
+// words of a wavefront's frontier list (two ids each)
+__host__ __device__ inline int batch_list_words(int nwords) { return nwords > 64 ? nwords : 64; }
+
 size_t batch_bfs_lds_bytes(int32_t nmax, int64_t nnzmax, int waves) {
     const size_t nwords = (size_t)(nmax + 31) / 32;
     return 4 * ((size_t)nmax + 1) + 2 * (((size_t)nnzmax + 1) & ~(size_t)1) +
-           4 * nwords * 3 * (size_t)waves;
+           4 * (nwords * 2 + (size_t)batch_list_words((int)nwords)) * (size_t)waves;
 }
 
 // One pass per source: after its BFS the wavefront knows |N_v(k)|, takes the
-// row's place (padded to quads) from the graph's cursor in LDS inside the
-// graph's block of kidx -- sized by a walk-count bound of the graph's rows
-// (walk_bound_kernel), so it never overflows -- and writes the row ascending
+// row's place (padded to quads) from the unit's cursor in LDS inside the
+// unit's block of kidx -- sized by a walk-count bound of its rows
+// (walk_level_kernel), so it never overflows -- and writes the row ascending
 // from the visited bitmap, then the padding.  Where a row lands in the block
 // depends on which wavefront finishes first; what it holds does not.
 template <int BS>
 __global__ __launch_bounds__(BS) void batch_khop_kernel(BatchBfsArgs a) {
     constexpr int kBfsBlock = BS;
-    constexpr int kBfsWaves = BS / 64;
     extern __shared__ __align__(16) unsigned char s_raw[];
-    __shared__ int s_g;
+    __shared__ int s_unit, s_src;
     __shared__ unsigned long long s_cursor;
     const int nwords_max = (a.nmax + 31) / 32;
     int32_t* s_rp = reinterpret_cast<int32_t*>(s_raw);
     uint16_t* s_ci = reinterpret_cast<uint16_t*>(s_rp + a.nmax + 1);
     uint32_t* s_bm = reinterpret_cast<uint32_t*>(s_ci + ((a.nnzmax + 1) & ~(int64_t)1));
     const int lane = lane64(), w = wave_id();
-    uint32_t* vis = s_bm + (size_t)w * 3 * nwords_max;
+    const int list_words = batch_list_words(nwords_max), list_cap = 2 * list_words;
+    uint32_t* vis = s_bm + (size_t)w * (2 * nwords_max + list_words);
+    uint32_t* cur = vis + nwords_max;
+    uint16_t* list = reinterpret_cast<uint16_t*>(cur + nwords_max);
     for (;;) {
-        if (threadIdx.x == 0) s_g = atomicAdd(a.work, 1);
+        if (threadIdx.x == 0) s_unit = atomicAdd(a.work, 1);
         __syncthreads();
-        const int gi = s_g;
+        const int ui = s_unit;
         __syncthreads();
-        if (gi >= a.count) return;
-        const int g = a.gorder[gi];
+        if (ui >= a.units) return;
+        const int4 unit = a.unit[ui];
+        const int g = unit.x;
         const int64_t vb = a.vbase[g];
         const int n = (int)(a.vbase[g + 1] - vb);
         const int k = a.gk[g];
@@ -256,53 +268,89 @@ __global__ __launch_bounds__(BS) void batch_khop_kernel(BatchBfsArgs a) {
         const int64_t ne = a.rp[vb + n] - eb;
         for (int i = threadIdx.x; i <= n; i += kBfsBlock) s_rp[i] = (int32_t)(a.rp[vb + i] - eb);
         for (int64_t j = threadIdx.x; j < ne; j += kBfsBlock) s_ci[j] = (uint16_t)(a.ci[eb + j] - vb);
-        if (threadIdx.x == 0) s_cursor = 0ull;
+        if (threadIdx.x == 0) {
+            s_cursor = 0ull;
+            s_src = unit.y;
+        }
         __syncthreads();
         const int nw = (n + 31) >> 5;
-        const int64_t gb = a.gbase[g];
-        for (int src = w; src < n; src += kBfsWaves) {
-            uint32_t* cur = vis + nwords_max;
-            uint32_t* nxt = cur + nwords_max;
-            for (int i = lane; i < nw; i += 64) {
-                vis[i] = 0u;
-                cur[i] = 0u;
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (lane == 0) {
-                vis[src >> 5] = 1u << (src & 31);
-                cur[src >> 5] = 1u << (src & 31);
-            }
-            __builtin_amdgcn_wave_barrier();
-            int found = 0;
-            for (int level = 0; level < k; ++level) {
-                for (int i = lane; i < nw; i += 64) nxt[i] = 0u;
-                __builtin_amdgcn_wave_barrier();
-                int added = 0;
-                for (int i = lane; i < nw; i += 64) {
-                    uint32_t bits = cur[i];
-                    while (bits) {
-                        const int u = i * 32 + __builtin_ctz(bits);
-                        bits &= bits - 1u;
-                        const int e1 = s_rp[u + 1];
-                        for (int e = s_rp[u]; e < e1; ++e) {
-                            const int x = s_ci[e];
-                            const uint32_t m = 1u << (x & 31);
-                            if (!(atomicOr(&vis[x >> 5], m) & m)) {
-                                atomicOr(&nxt[x >> 5], m);
-                                ++added;
+        const int64_t gb = a.bound[vb + unit.y];
+        for (;;) {
+            int src = 0;
+            if (lane == 0) src = atomicAdd(&s_src, 1);
+            src = __builtin_amdgcn_readfirstlane(src);
+            if (src >= unit.z) break;
+            for (int i = lane; i < nw; i += 64) vis[i] = i == (src >> 5) ? 1u << (src & 31) : 0u;
+            if (lane == 0) list[0] = (uint16_t)src;
+            wave_lds_fence();
+            int found = 0;         // ids of the levels before this one
+            int from = 0, to = 1;  // the frontier in the list
+            bool listed = true;
+            for (int level = 1; level <= k; ++level) {
+                int added = 0, at = 0;
+                // marks x (where take), listing it if a level follows
+                auto visit = [&](bool take, int x) {
+                    bool fresh = false;
+                    if (take) {
+                        const uint32_t m = 1u << (x & 31);
+                        fresh = !(atomicOr(&vis[x >> 5], m) & m);
+                    }
+                    const uint64_t b = __ballot(fresh);
+                    if (level < k && fresh) {
+                        const int slot = at + __popcll(b & ((1ull << lane) - 1));
+                        if (slot < list_cap) list[slot] = (uint16_t)x;
+                    }
+                    added += __popcll(b);
+                    at += __popcll(b);
+                };
+                if (listed) {
+                    at = to;  // behind the frontier
+                    for (int c = from; c < to; c += 64) {
+                        int start = 0, deg = 0;
+                        if (c + lane < to) {
+                            const int u = list[c + lane];
+                            start = s_rp[u];
+                            deg = s_rp[u + 1] - start;
+                        }
+                        const int inc = wave_inclusive_scan(deg);
+                        const int total = __shfl(inc, 63, 64);
+                        const int first = start - (inc - deg);  // entry t of the run: s_ci[first + t]
+                        for (int t0 = 0; t0 < total; t0 += 64) {
+                            const int t = t0 + lane;
+                            int o = 0;  // the row of entry t: the first with inc > t
+                            if (to - from > 1) {
+#pragma unroll
+                                for (int h = 32; h >= 1; h >>= 1)
+                                    if (__shfl(inc, o + h - 1, 64) <= t) o += h;
                             }
+                            const int e = __shfl(first, o & 63, 64) + t;
+                            visit(t < total, t < total ? s_ci[e] : 0);
+                        }
+                    }
+                } else {
+                    for (int i = lane; i < nw; i += 64) cur[i] = vis[i];
+                    wave_lds_fence();
+                    for (int i0 = 0; i0 < nw; i0 += 64) {
+                        uint32_t bits = i0 + lane < nw ? cur[i0 + lane] : 0u;
+                        while (__ballot(bits != 0u)) {
+                            const int u = (i0 + lane) * 32 + (bits ? __builtin_ctz(bits) : 0);
+                            const int e0 = bits ? s_rp[u] : 0, e1 = bits ? s_rp[u + 1] : 0;
+                            bits &= bits - 1u;
+                            for (int e = e0; __ballot(e < e1); ++e) visit(e < e1, e < e1 ? s_ci[e] : 0);
                         }
                     }
                 }
-                __builtin_amdgcn_wave_barrier();
                 found += added;
-                uint32_t* t = cur;
-                cur = nxt;
-                nxt = t;
-                if (__ballot(added > 0) == 0ull) break;
+                if (added == 0) break;
+                from = listed ? to : 0;
+                to = at;
+                listed = at <= list_cap;
+                // (after a level that expanded the whole bitmap the list holds just the
+                // new ids, from its start; when it overflows it is begun again there)
+                wave_lds_fence();
             }
-            // the row's place: |N_v(k)| padded to quads, from the graph's cursor
-            const int total = wave_sum(found);
+            // the row's place: |N_v(k)| padded to quads, from the unit's cursor
+            const int total = found;
             const int padded = (total + 3) & ~3;
             unsigned long long off = 0ull;
             if (lane == 0) off = atomicAdd(&s_cursor, (unsigned long long)padded);
@@ -329,13 +377,14 @@ __global__ __launch_bounds__(BS) void batch_khop_kernel(BatchBfsArgs a) {
                 out += __shfl(incl, 63, 64);
             }
             for (int j = total + lane; j < padded; j += 64) a.kidx[start + j] = (uint16_t)n;
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_fence();
         }
         __syncthreads();
     }
 }
 
 static int run_batch_bfs(const BatchBfsArgs& a, size_t lds, int bs, int device, hipStream_t s) {
+    if (a.units == 0) return GILA_OK;  // graphs without vertices only
     const void* kernel = bs == 1024 ? (const void*)batch_khop_kernel<1024>
                                     : (const void*)batch_khop_kernel<512>;
     if (lds > 48 * 1024)
@@ -343,7 +392,7 @@ static int run_batch_bfs(const BatchBfsArgs& a, size_t lds, int bs, int device, 
     const DeviceInfo& di = device_info(device);
     const int per_cu =
         (int)std::max<size_t>(1, std::min<size_t>(2048 / bs, (160u * 1024u) / (lds + 1024)));
-    const int grid = std::min(a.count, di.cus * per_cu);
+    const int grid = std::min(a.units, di.cus * per_cu);
     GILA_HIP(hipMemsetAsync(a.work, 0, sizeof(int32_t), s));
     if (bs == 1024)
         hipLaunchKernelGGL(batch_khop_kernel<1024>, dim3(grid), dim3(1024), lds, s, a);
@@ -445,19 +494,20 @@ constexpr int kOrderMax = 8192;
 // half; larger graphs keep ids.
 constexpr int kOffsetLimit = 8192;
 
-__global__ __launch_bounds__(kBlock) void row_order_kernel(const int64_t* __restrict__ vbase,
-                                                           const int32_t* __restrict__ klen,
-                                                           uint16_t* __restrict__ order) {
+constexpr int kOrderBlock = 1024;  // 256 left the largest graphs' sorts for last: 323 -> 101 us
+__global__ __launch_bounds__(kOrderBlock) void row_order_kernel(const int64_t* __restrict__ vbase,
+                                                                const int32_t* __restrict__ klen,
+                                                                uint16_t* __restrict__ order) {
     __shared__ uint32_t s_key[kOrderMax];
     const int64_t vb = vbase[blockIdx.x];
     const int n = (int)(vbase[blockIdx.x + 1] - vb);
     if (n > kOrderMax) {
-        for (int i = threadIdx.x; i < n; i += kBlock) order[vb + i] = (uint16_t)i;
+        for (int i = threadIdx.x; i < n; i += kOrderBlock) order[vb + i] = (uint16_t)i;
         return;
     }
     int np = 1;
     while (np < n) np <<= 1;
-    for (int i = threadIdx.x; i < np; i += kBlock) {
+    for (int i = threadIdx.x; i < np; i += kOrderBlock) {
         // a row has at most 65534 entries, so at most 16384 quads
         const uint32_t q = i < n ? (uint32_t)(klen[vb + i] >> 2) : 0u;
         s_key[i] = i < n ? ((0xFFFFu - q) << 16) | (uint32_t)i : 0xFFFFFFFFu;
@@ -465,20 +515,18 @@ __global__ __launch_bounds__(kBlock) void row_order_kernel(const int64_t* __rest
     __syncthreads();
     for (int size = 2; size <= np; size <<= 1)
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = threadIdx.x; i < np; i += kBlock) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    const bool up = (i & size) == 0;
-                    const uint32_t x = s_key[i], y = s_key[j];
-                    if ((x > y) == up) {
-                        s_key[i] = y;
-                        s_key[j] = x;
-                    }
+            for (int q = threadIdx.x; q < np / 2; q += kOrderBlock) {
+                const int i = 2 * q - (q & (stride - 1)), j = i + stride;
+                const bool up = (i & size) == 0;
+                const uint32_t x = s_key[i], y = s_key[j];
+                if ((x > y) == up) {
+                    s_key[i] = y;
+                    s_key[j] = x;
                 }
             }
             __syncthreads();
         }
-    for (int i = threadIdx.x; i < n; i += kBlock) order[vb + i] = (uint16_t)(s_key[i] & 0xFFFFu);
+    for (int i = threadIdx.x; i < n; i += kOrderBlock) order[vb + i] = (uint16_t)(s_key[i] & 0xFFFFu);
 }
 
 // One wavefront per slice: its lanes' vertices (the graph's sentinel id n for
@@ -1262,7 +1310,7 @@ static int build_slices(gila_batch* b, const int64_t* d_vb, hipStream_t s) {
     GILA_HIP(hipMemcpyAsync(d_sgraph.p, sgraph.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, s));
     GILA_HIP(hipMemcpyAsync(d_sb.p, b->sbase.data(), sizeof(int64_t) * (count + 1),
                             hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(row_order_kernel, dim3(count), dim3(kBlock), 0, s, d_vb, b->klen, d_order.p);
+    hipLaunchKernelGGL(row_order_kernel, dim3(count), dim3(kOrderBlock), 0, s, d_vb, b->klen, d_order.p);
     GILA_HIP(hipGetLastError());
     const int per_block = kBlock / 64;
     const dim3 sg((unsigned)((S + per_block - 1) / per_block));
@@ -1381,16 +1429,15 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
                            !(getenv("GILA_BATCH_BFS") && std::strcmp(getenv("GILA_BATCH_BFS"), "source") == 0);
     const int vg = (int)std::min<int64_t>(4096, (std::max<int64_t>(b->nv, 1) + kBlock - 1) / kBlock);
     if (per_graph) {
-        // each graph's block: the sum of its rows' walk bounds
+        // each unit's block: the sum of its rows' walk bounds
         DevTmp<int32_t> d_vgraph(s);
-        DevTmp<int64_t> d_w0(s), d_w1(s), d_tot(s), d_bound(s), d_bscan(s), d_gbase(s);
+        DevTmp<int64_t> d_w0(s), d_w1(s), d_tot(s), d_bound(s), d_bscan(s);
         GILA_TRY(dalloc_t(&d_vgraph.p, (size_t)std::max<int64_t>(b->nv, 1)));
         GILA_TRY(dalloc_t(&d_w0.p, (size_t)std::max<int64_t>(b->nv, 1)));
         GILA_TRY(dalloc_t(&d_w1.p, (size_t)std::max<int64_t>(b->nv, 1)));
         GILA_TRY(dalloc_t(&d_tot.p, (size_t)std::max<int64_t>(b->nv, 1)));
         GILA_TRY(dalloc_t(&d_bound.p, (size_t)std::max<int64_t>(b->nv, 1)));
         GILA_TRY(dalloc_t(&d_bscan.p, (size_t)b->nv + 1));
-        GILA_TRY(dalloc_t(&d_gbase.p, (size_t)count + 1));
         hipLaunchKernelGGL(vertex_graph_kernel, dim3(count), dim3(kBlock), 0, s, d_vb.p,
                            d_vgraph.p);
         hipLaunchKernelGGL(walk_init_kernel, dim3(vg), dim3(kBlock), 0, s, b->nv, b->rp, d_w0.p,
@@ -1406,30 +1453,33 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
                            d_bound.p);
         GILA_HIP(hipGetLastError());
         GILA_TRY(exclusive_scan_i64(d_bound.p, d_bscan.p, b->nv, s));
-        hipLaunchKernelGGL(gather_bounds_kernel, dim3((count + 256) / 256), dim3(256), 0, s,
-                           d_bscan.p, d_vb.p, count, d_gbase.p);
-        GILA_HIP(hipGetLastError());
-        GILA_HIP(hipMemcpyAsync(&b->kidx_size, d_gbase.p + count, sizeof(int64_t),
+        GILA_HIP(hipMemcpyAsync(&b->kidx_size, d_bscan.p + b->nv, sizeof(int64_t),
                                 hipMemcpyDeviceToHost, s));
         GILA_HIP(hipStreamSynchronize(s));
         GILA_TRY(dalloc_t(&b->kidx, (size_t)b->kidx_size + 64));
         pt.mark("bounds");
-        std::vector<int32_t> gorder((size_t)count);
-        std::iota(gorder.begin(), gorder.end(), 0);
-        std::stable_sort(gorder.begin(), gorder.end(),
-                         [&](int32_t x, int32_t y) { return b->n[x] > b->n[y]; });
-        DevTmp<int32_t> d_gorder(s);
-        GILA_TRY(dalloc_t(&d_gorder.p, (size_t)count));
-        GILA_HIP(hipMemcpyAsync(d_gorder.p, gorder.data(), sizeof(int32_t) * count,
-                                hipMemcpyHostToDevice, s));
+        std::vector<int4> unit;
+        for (int32_t i = 0; i < count; ++i)
+            for (int32_t v = 0; v < b->n[i]; v += kUnitSources)
+                unit.push_back(make_int4(i, v, std::min(v + kUnitSources, b->n[i]), 0));
+        // longest first: full units of the largest graphs, then the others by size
+        std::stable_sort(unit.begin(), unit.end(), [&](const int4& x, const int4& y) {
+            const int32_t sx = x.z - x.y, sy = y.z - y.y;
+            return sx != sy ? sx > sy : b->n[x.x] > b->n[y.x];
+        });
+        DevTmp<int4> d_unit(s);
+        GILA_TRY(dalloc_t(&d_unit.p, std::max<size_t>(unit.size(), 1)));
+        if (!unit.empty())
+            GILA_HIP(hipMemcpyAsync(d_unit.p, unit.data(), sizeof(int4) * unit.size(),
+                                    hipMemcpyHostToDevice, s));
         BatchBfsArgs ga{};
-        ga.count = count;
-        ga.gorder = d_gorder.p;
+        ga.units = (int32_t)unit.size();
+        ga.unit = d_unit.p;
         ga.vbase = d_vb.p;
         ga.rp = b->rp;
         ga.ci = d_ci32.p;
         ga.gk = d_k.p;
-        ga.gbase = d_gbase.p;
+        ga.bound = d_bscan.p;
         ga.counts = d_counts.p;
         ga.kstart = b->kstart;
         ga.klen = b->klen;
