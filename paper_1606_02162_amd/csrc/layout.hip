@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kBlock) void init_positions_kernel(int32_t n, uint6
 }
 
 // ------------------------------------------------------------------ small kernels
-__global__ void reset_ctl_kernel(Ctl* ctl) {
+__device__ __forceinline__ void reset_ctl(Ctl* ctl) {
     ctl->stopped = 0;
     ctl->iters_run = 0;
     ctl->done_blocks = 0u;
@@ -62,19 +62,29 @@ __global__ void reset_ctl_kernel(Ctl* ctl) {
     ctl->nonfinite = 0;
 }
 
-// Caller positions -> internal buffer 0; isolated vertices (the tail of the
-// internal order) never move, so they are written to buffer 1 as well.
+__global__ void reset_ctl_kernel(Ctl* ctl) { reset_ctl(ctl); }
+
+// The start of a sequence: the control block, caller positions -> internal buffer 0
+// (isolated vertices, the tail of the internal order, never move, so they are written
+// to buffer 1 as well) and, where asked for, no force and no displacement.  One launch:
+// each costs about what a small graph's whole iteration does (32 x 32 grid, one step,
+// FP64: 43 us a call with this and the two clears in it, 74 with launches of their own).
 template <class V>
-__global__ __launch_bounds__(kBlock) void permute_in_kernel(int32_t n, int32_t n_active,
-                                                            const int32_t* __restrict__ perm,
-                                                            const V* __restrict__ src,
-                                                            V* __restrict__ b0,
-                                                            V* __restrict__ b1) {
+__global__ __launch_bounds__(kBlock) void begin_kernel(int32_t n, int32_t n_active, Ctl* ctl,
+                                                       const int32_t* __restrict__ perm,
+                                                       const V* __restrict__ src, V* __restrict__ b0,
+                                                       V* __restrict__ b1, double* __restrict__ force,
+                                                       double* __restrict__ disp) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) reset_ctl(ctl);
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * kBlock) {
         const V p = src[perm[i]];
         b0[i] = p;
         if (i >= n_active) b1[i] = p;
+        if (force) {
+            force[2 * i] = force[2 * i + 1] = 0.0;
+            disp[2 * i] = disp[2 * i + 1] = 0.0;
+        }
     }
 }
 
@@ -96,17 +106,19 @@ static int grid_for(int64_t items) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(4096, (items + kBlock - 1) / kBlock));
 }
 
-static int launch_permute_in(const gila_khop* kh, int precision, const void* pos, hipStream_t s) {
-    if (kh->n == 0) return GILA_OK;
+static int launch_begin(const gila_khop* kh, int precision, const void* pos, hipStream_t s,
+                        double* force = nullptr, double* disp = nullptr) {
     const int g = grid_for(kh->n);
-    if (precision == GILA_FP64)
-        hipLaunchKernelGGL(permute_in_kernel<double2>, dim3(g), dim3(kBlock), 0, s, kh->n,
-                           kh->n_active, kh->perm, (const double2*)pos, (double2*)kh->pos[0],
-                           (double2*)kh->pos[1]);
+    if (kh->n == 0)
+        hipLaunchKernelGGL(reset_ctl_kernel, dim3(1), dim3(1), 0, s, kh->ctl);
+    else if (precision == GILA_FP64)
+        hipLaunchKernelGGL(begin_kernel<double2>, dim3(g), dim3(kBlock), 0, s, kh->n, kh->n_active,
+                           kh->ctl, kh->perm, (const double2*)pos, (double2*)kh->pos[0],
+                           (double2*)kh->pos[1], force, disp);
     else
-        hipLaunchKernelGGL(permute_in_kernel<float2>, dim3(g), dim3(kBlock), 0, s, kh->n,
-                           kh->n_active, kh->perm, (const float2*)pos, (float2*)kh->pos[0],
-                           (float2*)kh->pos[1]);
+        hipLaunchKernelGGL(begin_kernel<float2>, dim3(g), dim3(kBlock), 0, s, kh->n, kh->n_active,
+                           kh->ctl, kh->perm, (const float2*)pos, (float2*)kh->pos[0],
+                           (float2*)kh->pos[1], force, disp);
     GILA_HIP(hipGetLastError());
     return GILA_OK;
 }
@@ -220,9 +232,7 @@ static int enqueue_from_base(const gila_khop* kh, int precision, StepArgs a, int
 // Enqueue: reset, permute in, iterations, permute out.
 int enqueue_run(gila_khop* kh, const gila_params* p, int32_t start_h, int32_t end_h,
                 void* pos_dev, hipStream_t s) {
-    hipLaunchKernelGGL(reset_ctl_kernel, dim3(1), dim3(1), 0, s, kh->ctl);
-    GILA_HIP(hipGetLastError());
-    GILA_TRY(launch_permute_in(kh, p->precision, pos_dev, s));
+    GILA_TRY(launch_begin(kh, p->precision, pos_dev, s));
     StepArgs a = base_args(kh, p);
     a.check_stop = p->stop_fraction > 0.0 ? 1 : 0;
     GILA_TRY(enqueue_iterations(kh, p, a, start_h, end_h, s));
@@ -294,10 +304,7 @@ int enqueue_tick(gila_khop* kh, const gila_params* p, int32_t h, int32_t count,
             (void)hipGetLastError();
             return enqueue_run(kh, p, h, h + count, pos_dev, s);
         }
-        int rc = GILA_OK;
-        hipLaunchKernelGGL(reset_ctl_kernel, dim3(1), dim3(1), 0, cs, kh->ctl);
-        if (hipGetLastError() != hipSuccess) rc = fail(GILA_EDEVICE, "tick capture: reset");
-        if (rc == GILA_OK) rc = launch_permute_in(kh, p->precision, pos_dev, cs);
+        int rc = launch_begin(kh, p->precision, pos_dev, cs);
         StepArgs a = base_args(kh, p);
         a.check_stop = p->stop_fraction > 0.0 ? 1 : 0;
         a.temps = kh->d_temps;
@@ -452,9 +459,7 @@ static int enqueue_chunked_run(gila_khop* kh, const gila_params* p, int32_t star
         }
         kh->chunk_key = key;
     }
-    hipLaunchKernelGGL(reset_ctl_kernel, dim3(1), dim3(1), 0, s, kh->ctl);
-    GILA_HIP(hipGetLastError());
-    GILA_TRY(launch_permute_in(kh, p->precision, pos_dev, s));
+    GILA_TRY(launch_begin(kh, p->precision, pos_dev, s));
     int32_t h = start_h;
     for (; end_h - h >= kRunChunk; h += kRunChunk) {
         hipLaunchKernelGGL(set_h_base_kernel, dim3(1), dim3(1), 0, s, kh->ctl, h);
@@ -579,14 +584,8 @@ int gila_step(const gila_khop* kh_c, const gila_params* params, int32_t h, void*
     DeviceGuard dg(kh->device);
     hipStream_t s = (hipStream_t)stream;
     GILA_TRY(prepare_precision(kh, params->precision, s));
-    if (force_dev && kh->n > 0) {
-        // isolated vertices feel no force and do not move
-        GILA_HIP(hipMemsetAsync(force_dev, 0, sizeof(double) * 2 * kh->n, s));
-        GILA_HIP(hipMemsetAsync(disp_dev, 0, sizeof(double) * 2 * kh->n, s));
-    }
-    hipLaunchKernelGGL(reset_ctl_kernel, dim3(1), dim3(1), 0, s, kh->ctl);
-    GILA_HIP(hipGetLastError());
-    GILA_TRY(launch_permute_in(kh, params->precision, pos_dev, s));
+    // isolated vertices feel no force and do not move
+    GILA_TRY(launch_begin(kh, params->precision, pos_dev, s, force_dev, disp_dev));
     StepArgs a = base_args(kh, params);
     a.check_stop = 0;
     a.F_out = force_dev;
@@ -651,9 +650,7 @@ int gila_time_iterations(const gila_khop* kh_c, const gila_params* params, int32
     // the iterations h .. h + reps - 1 exactly as gila_run runs them (which
     // advance pos_dev), the force kernels recording their spans
     auto enqueue = [&](hipStream_t q) -> int {
-        hipLaunchKernelGGL(reset_ctl_kernel, dim3(1), dim3(1), 0, q, kh->ctl);
-        GILA_HIP(hipGetLastError());
-        GILA_TRY(launch_permute_in(kh, params->precision, pos_dev, q));
+        GILA_TRY(launch_begin(kh, params->precision, pos_dev, q));
         GILA_TRY(enqueue_iterations(kh, params, base_args(kh, params), h, h + reps, q,
                                     seg ? span : nullptr));
         return launch_permute_out(kh, params->precision, pos_dev, q);
