@@ -121,11 +121,7 @@ struct SliceBuild {
 };
 
 __device__ __forceinline__ void emit_slice(const SliceBuild& b, int64_t j, int32_t v, int32_t s,
-                                           int64_t k0, int64_t ke, int64_t ab, int64_t ae) {
-    const int64_t lo = (int64_t)s * b.S, hi = lo + b.S;
-    const int64_t k1 = lower_bound_ids(b.kidx, k0, ke, hi);
-    const int64_t a0 = lower_bound_ids(b.ci, ab, ae, lo);
-    const int64_t a1 = lower_bound_ids(b.ci, a0, ae, hi);
+                                           int64_t k0, int64_t k1, int64_t a0, int64_t a1) {
     b.d_seg[j] = s;
     b.d_k0[j] = k0;
     b.d_kn[j] = (int32_t)(k1 - k0);
@@ -134,50 +130,70 @@ __device__ __forceinline__ void emit_slice(const SliceBuild& b, int64_t j, int32
     b.d_row[j] = v;
 }
 
-// Wave per row: the segments a sorted k-hop row touches.  Short rows are
-// scanned for segment changes; long rows binary-search each segment.  The
-// count pass writes the number of slices; the emit pass writes them at
-// vsl[v] onward in segment order.  Every adjacency id of v is also a k-hop id
-// of v (k >= 1), so the k-hop slices cover the adjacency slices.
+// kRowLanes lanes per row: the segments a sorted k-hop row touches.  Short rows are
+// scanned for segment changes; long rows binary-search each segment, whose end is
+// where the next lane's begins.  The count pass writes the number of slices; the emit
+// pass writes them at vsl[v] onward in segment order.  Every adjacency id of v is also
+// a k-hop id of v (k >= 1), so the k-hop slices cover the adjacency slices.  Bound by
+// the chain of a search, so by the rows in flight: with a wavefront per row and a search
+// for both ends R-MAT 18, k = 2 (15 segments) took 148 + 244 us for the two passes,
+// 142 + 127 now; Watts-Strogatz 200k, k = 2 (49 segments, 18 ids a row) 34 + 122,
+// 17 + 51 now.
+constexpr int kRowLanes = 16;
 template <bool EMIT>
 __global__ __launch_bounds__(kBlock) void slice_rows_kernel(SliceBuild b) {
-    const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * kBlock) >> 6;
-    const int lane = lane64();
-    const uint64_t below = (1ull << lane) - 1ull;
-    for (int64_t vv = wave; vv < b.na; vv += nwaves) {
+    constexpr int G = kRowLanes;
+    const int64_t group = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / G;
+    const int64_t ngroups = ((int64_t)gridDim.x * kBlock) / G;
+    const int gl = threadIdx.x % G, shift = lane64() - gl;
+    const uint32_t below = (1u << gl) - 1u;
+    auto ballot = [&](bool x) { return (uint32_t)(__ballot(x) >> shift) & ((1u << G) - 1u); };
+    for (int64_t vv = group; vv < b.na; vv += ngroups) {
         const int32_t v = (int32_t)vv;
         const int64_t kb = b.kptr[v], ke = b.kptr[v + 1];
         const int64_t ab = b.rp[v], ae = b.rp[v + 1];
         int64_t t = EMIT ? b.vsl[v] : 0;
         if (ke - kb > (int64_t)kLongRow * b.nseg) {
-            for (int32_t s0 = 0; s0 < b.nseg; s0 += 64) {
-                const int32_t s = s0 + lane;
-                bool ne = false;
-                int64_t k0 = ke;
-                if (s < b.nseg) {
-                    k0 = lower_bound_ids(b.kidx, kb, ke, (int64_t)s * b.S);
-                    ne = k0 < ke && (int64_t)b.kidx[k0] < (int64_t)(s + 1) * b.S;
+            for (int32_t s0 = 0; s0 < b.nseg; s0 += G) {
+                const int32_t s = s0 + gl;
+                const int64_t lo = (int64_t)s * b.S, hi = lo + b.S;
+                const bool last = gl == G - 1 && s + 1 < b.nseg;
+                const int64_t k0 = s < b.nseg ? lower_bound_ids(b.kidx, kb, ke, lo) : ke;
+                int64_t k1 = __shfl_down(k0, 1, G);
+                if (gl == G - 1) k1 = last ? lower_bound_ids(b.kidx, k0, ke, hi) : ke;
+                const bool ne = k0 < k1;
+                const uint32_t m = ballot(ne);
+                if constexpr (EMIT) {
+                    const int64_t a0 = s < b.nseg ? lower_bound_ids(b.ci, ab, ae, lo) : ae;
+                    int64_t a1 = __shfl_down(a0, 1, G);
+                    if (gl == G - 1) a1 = last ? lower_bound_ids(b.ci, a0, ae, hi) : ae;
+                    if (ne) emit_slice(b, t + __popc(m & below), v, s, k0, k1, a0, a1);
                 }
-                const uint64_t m = __ballot(ne);
-                if (EMIT && ne) emit_slice(b, t + __popcll(m & below), v, s, k0, ke, ab, ae);
-                t += __popcll(m);
+                t += __popc(m);
             }
         } else {
-            for (int64_t j0 = kb; j0 < ke; j0 += 64) {
-                const int64_t j = j0 + lane;
+            for (int64_t j0 = kb; j0 < ke; j0 += G) {
+                const int64_t j = j0 + gl;
                 bool start = false;
                 int32_t s = 0;
                 if (j < ke) {
                     s = b.kidx[j] / b.S;
                     start = j == kb || b.kidx[j - 1] / b.S != s;
                 }
-                const uint64_t m = __ballot(start);
-                if (EMIT && start) emit_slice(b, t + __popcll(m & below), v, s, j, ke, ab, ae);
-                t += __popcll(m);
+                const uint32_t m = ballot(start);
+                if constexpr (EMIT) {
+                    if (start) {
+                        const int64_t lo = (int64_t)s * b.S, hi = lo + b.S;
+                        const int64_t k1 = lower_bound_ids(b.kidx, j, ke, hi);
+                        const int64_t a0 = lower_bound_ids(b.ci, ab, ae, lo);
+                        const int64_t a1 = lower_bound_ids(b.ci, a0, ae, hi);
+                        emit_slice(b, t + __popc(m & below), v, s, j, k1, a0, a1);
+                    }
+                }
+                t += __popc(m);
             }
         }
-        if (!EMIT && lane == 0) b.rs[v] = t;
+        if (!EMIT && gl == 0) b.rs[v] = t;
     }
 }
 
@@ -892,7 +908,7 @@ int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     const int32_t nseg = (int32_t)((na + (int64_t)S - 1) / S);
     if (nseg > kMaxSegments) return fail(GILA_EUNSUPPORTED, "too many segments (%d)", nseg);
     PhaseTimer pt("build_segments", st);
-    const int grid_rows = (int)std::min<int64_t>(16384, ((int64_t)na * 64 + kBlock - 1) / kBlock);
+    const int grid_rows = (int)std::min<int64_t>(16384, ((int64_t)na * kRowLanes + kBlock - 1) / kBlock);
 
     // --- slices per row, row-major offsets
     GILA_TRY(dalloc_t(&kh->vsl, (size_t)na + 1));
