@@ -925,7 +925,7 @@ static int layout_components(const gila_csr* g, int32_t k, const gila_params* pa
         while (small_first > 0 && o.size[small_first - 1] <= kSmallComponent) --small_first;
     for (int32_t r = 0; r < small_first; ++r) {
         gila_khop* kh = nullptr;
-        GILA_TRY(build_khop(&cg[r], k, s, &kh));
+        GILA_TRY(build_khop(&cg[r], k, s, &kh, params->precision));
         gila_stats st{};
         int rc;
         {

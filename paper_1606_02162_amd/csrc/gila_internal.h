@@ -332,7 +332,12 @@ int launch_step(const gila_khop* kh, int precision, const StepArgs& a, hipStream
 int plan_iteration(gila_khop* kh, const std::vector<int64_t>& counts_internal,
                    const std::vector<int64_t>& rp_internal, hipStream_t s);
 // implemented in khop.hip
-int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out);
+// plan_for: the precision whose segments are built with the lists, or kNoPlan: they are
+// built before the first iteration (prepare_precision).  A plan for another precision, or
+// without the weights that are set before the first iteration, would be built twice.
+constexpr int kNoPlan = -1;
+int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out,
+               int plan_for = GILA_FP32_KAHAN);
 void free_khop(gila_khop* kh, Release rel = Release{});
 int run_bfs(bool fill, int device, hipStream_t s, BfsArgs a);
 // What the checks of a CSR on the device found (zeroed before they run).

@@ -901,7 +901,7 @@ __global__ __launch_bounds__(kBlock) void internal_rows_kernel(
     }
 }
 
-int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out) {
+int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out, int plan_for) {
     if (!out) return fail(GILA_EINVAL, "out is NULL");
     *out = nullptr;
     if (!g) return fail(GILA_EINVAL, "graph is NULL");
@@ -1055,11 +1055,11 @@ int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out) {
     GILA_TRY(dalloc_t(&kh->ctl, 1));
     GILA_HIP(hipMemsetAsync(kh->ctl, 0, sizeof(Ctl), s));
     GILA_HIP(hipStreamSynchronize(s));
-    // segment-blocked lists for FP32 positions (the common case); FP64 runs
-    // rebuild them for their own segment size on first use
+    // segment-blocked lists, for a handle those of FP32 positions (the common case);
+    // FP64 runs rebuild them for their own segment size on first use
     pt.mark("plan");
-    if (segment_path_enabled()) {
-        const int src = build_segments(kh, GILA_FP32_KAHAN, s);
+    if (plan_for != kNoPlan && segment_path_enabled()) {
+        const int src = build_segments(kh, plan_for, s);
         if (src != GILA_OK && src != GILA_EUNSUPPORTED) return src;
         clear_error();
     }

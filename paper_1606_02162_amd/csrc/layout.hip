@@ -767,7 +767,7 @@ int gila_layout(const gila_csr* g_dev, int32_t k, const gila_params* params, voi
     clear_error();
     GILA_TRY(check_params(params, true));
     gila_khop* kh = nullptr;
-    GILA_TRY(gila_build_khop(g_dev, k, stream, &kh));
+    GILA_TRY(build_khop(g_dev, k, (hipStream_t)stream, &kh, params->precision));
     int rc;
     {
         std::lock_guard<std::mutex> lk(kh->mu);

@@ -814,7 +814,7 @@ int gila_layout_pruned(const gila_csr* g_dev, int32_t k, const gila_params* para
     PrunedHolder ph{p, Release{true, s}};
     gila_csr pg{p->n_kept, p->nnz_kept, p->rp, p->ci};
     gila_khop* kh = nullptr;
-    GILA_TRY(build_khop(&pg, k, s, &kh));
+    GILA_TRY(build_khop(&pg, k, s, &kh, kNoPlan));
     struct KH {
         gila_khop* k;
         hipStream_t s;

@@ -301,7 +301,7 @@ static int admit_large(gila_server* s, Job* j) {
     TraceRange trace_range("gila_server: large-job build");
     GILA_TRY(upload_job(s, j, s->build));
     gila_csr c{j->n, j->nnz, j->d_rp, j->d_ci};
-    GILA_TRY(build_khop(&c, j->k, s->build, &j->kh));
+    GILA_TRY(build_khop(&c, j->k, s->build, &j->kh, j->params.precision));
     GILA_TRY(prepare_precision(j->kh, j->params.precision, s->build));
     GILA_HIP(hipStreamSynchronize(s->build));
     j->h = 0;
