@@ -652,17 +652,23 @@ int entries_status(const CsrCheck& c, const char* where) {
                 (flag & 4) ? " row not strictly ascending" : "", (flag & 8) ? " not symmetric" : "");
 }
 
-// The checks of a caller's CSR (the rules of gila_csr), on the device, with
-// one read back.  `out` (may be null) receives what the checks counted.
-// Synchronises `s`.
-int validate_graph(const gila_csr* g, hipStream_t s, int32_t window, CsrCheck* out) {
-    if (out) *out = CsrCheck{};
+// The checks of a caller's CSR that need no device.
+static int csr_arguments_status(const gila_csr* g) {
     if (!g) return fail(GILA_EINVAL, "graph is NULL");
     if (g->n < 0 || g->nnz < 0) return fail(GILA_EINVAL, "negative n or nnz");
     if (g->n > 0 && !g->row_ptr) return fail(GILA_EINVAL, "row_ptr is NULL");
     if (g->nnz > 0 && !g->col_idx) return fail(GILA_EINVAL, "col_idx is NULL");
     if (g->nnz > (int64_t)g->n * (int64_t)(g->n > 0 ? g->n - 1 : 0))
         return fail(GILA_EINVAL, "nnz exceeds n(n-1)");
+    return GILA_OK;
+}
+
+// The checks of a caller's CSR (the rules of gila_csr), on the device, with
+// one read back.  `out` (may be null) receives what the checks counted.
+// Synchronises `s`.
+int validate_graph(const gila_csr* g, hipStream_t s, int32_t window, CsrCheck* out) {
+    if (out) *out = CsrCheck{};
+    GILA_TRY(csr_arguments_status(g));
     if (g->n == 0) return GILA_OK;
     CsrCheck* d = nullptr;
     GILA_TRY(dalloc_t(&d, 1));
@@ -906,6 +912,7 @@ int build_khop(const gila_csr* g, int32_t k, hipStream_t s, gila_khop** out, int
     *out = nullptr;
     if (!g) return fail(GILA_EINVAL, "graph is NULL");
     if (k < 1) return fail(GILA_EINVAL, "k must be >= 1 (got %d)", k);
+    GILA_TRY(csr_arguments_status(g));
     int dev = 0;
     GILA_HIP(hipGetDevice(&dev));
     const int32_t n = g->n;
