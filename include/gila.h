@@ -246,9 +246,11 @@ int gila_run(const gila_khop* kh, const gila_params* params, int32_t start_h, in
  * segment path each force kernel also records on the device wall clock when
  * its first workgroup started and its last one ended.  ms_out[0] receives the
  * force kernel's average span (on the direct path, the whole iteration: its
- * gather kernel moves the vertices itself), ms_out[1] the iteration's average
- * from the events minus ms_out[0] (the combine and statistics kernels and the
- * launch gaps; 0 on the direct path), ms_out[2] 1 if the iterations ran as a
+ * gather kernel moves the vertices itself, as the force kernel of a graph of
+ * one segment does), ms_out[1] the iteration's average from the events minus
+ * ms_out[0] (the combine kernel, where there is one, and the launch gaps; 0 on
+ * the direct path; the statistics are reduced beside the next iteration's
+ * forces), ms_out[2] 1 if the iterations ran as a
  * graph replay, 0 if eagerly; ms_out holds 3 doubles.  Synchronises
  * `stream`. */
 int gila_time_iterations(const gila_khop* kh, const gila_params* params, int32_t h,
