@@ -679,12 +679,20 @@ __global__ __launch_bounds__(seg_block<BIG>(), PREC == GILA_FP64 ? 4 : (ONE ? 6 
     extern __shared__ __align__(16) unsigned char s_raw[];
     V* lp = reinterpret_cast<V*>(s_raw);
     __shared__ int64_t s_c[kSegBlock / 64];
+    // The flag is read once per workgroup: the statistics workgroup of this very launch may
+    // be setting it, and wavefronts that read it for themselves could part here, the first
+    // one gone and the others walking slices from LDS counters it never wrote.  Workgroups
+    // may differ: what they write then is not read any more (see the top of the file).
+    __shared__ int s_stopped;
+    if (threadIdx.x == 0) s_stopped = a.ctl->stopped;
+    __syncthreads();
+    const bool stopped = __builtin_amdgcn_readfirstlane(s_stopped) != 0;
     if (a.has_prev && blockIdx.x == 0) {
-        if (!a.ctl->stopped) iteration_stats(st, a.prev_recs, st.par ^ 1, iteration_index(st) - 1);
+        if (!stopped) iteration_stats(st, a.prev_recs, st.par ^ 1, iteration_index(st) - 1);
         return;
     }
     if (a.span && threadIdx.x == 0) atomicMin(&a.span[0], (unsigned long long)wall_clock64());
-    if (a.ctl->stopped) {
+    if (stopped) {
         if (a.span && threadIdx.x == 0) atomicMax(&a.span[1], (unsigned long long)wall_clock64());
         return;
     }

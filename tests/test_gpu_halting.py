@@ -69,3 +69,31 @@ def test_stops_where_single_steps_do(G, path, precision, H, stop):
     if not a.stopped and cut < H:
         G.run(kh, params, pos, cut, H)
     assert torch.equal(pos, ref)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_kahan"])
+@pytest.mark.parametrize("H,stop", [(7, 3), (130, 70)])
+def test_stops_with_more_workgroups_than_the_device_holds(G, precision, H, stop, monkeypatch):
+    """4096 workgroups a launch, of which at most 1024 are resident: some of the launch after
+    the last iteration begin while, or after, its first workgroup sets the flag that they
+    read.  As above: the bits of single steps (the longer run in replayed chunks)."""
+    import torch
+    print(f"halting 4096 workgroups {precision} H={H} stop={stop}", flush=True)
+    monkeypatch.setenv("GILA_SEG_WG", "4096")
+    g = inputs.barabasi_albert(20000, 3, seed=4)
+    rp, ci = G.to_device_csr(g)
+    prec = G.PRECISIONS[precision]
+    temps = np.full(H, 0.5)
+    temps[stop] = 0.001
+    params = G.LayoutParams(temperature=temps, precision=prec, stop_fraction=0.5)
+    x = torch.from_numpy(inputs.uniform_positions(g.n, 3)).to(dtype=G.position_dtype(prec), device="cuda")
+    kh = G.build_khop(rp, ci, 3)
+    ref = x.clone()
+    for h in range(stop + 1):
+        last = G.step(kh, params, h, ref)
+    pos = x.clone()
+    st = G.run(kh, params, pos)
+    assert st.iterations_run == stop + 1 and st.stopped == 1
+    assert (st.energy, st.max_disp, st.moved, st.coincident) == \
+        (last.energy, last.max_disp, last.moved, last.coincident)
+    assert torch.equal(pos, ref)
