@@ -306,7 +306,7 @@ struct gila_khop {
     int32_t seg_grid = 0;
     int32_t comb_grid = 0;
     double2* part = nullptr;        // [T] partial force of each slice, row-major
-    int32_t seg_precision = -1;     // precision the segment size was chosen for
+    int32_t seg_precision = -1;     // precision the segments were built for
     bool seg_weighted = false;      // segment size chosen with a weight per staged vertex
     bool seg_large = false;         // force kernel shape: 1024 threads (else 512)
     // weights of the repulsion each vertex exerts (internal ids), null = unit

@@ -851,9 +851,17 @@ static size_t seg_lds_bytes(const gila_khop* kh, int precision, int S) {
     return (size_t)(S + 1) * pos_bytes_of(precision);
 }
 
-bool segment_ready_for(const gila_khop* kh, int precision) {
-    return kh->seg_ready && segment_path_enabled() && kh->seg == seg_size_for(kh, precision) &&
+// Whether the segments of the handle are those that build_segments would make: offsets
+// scale with the position's size (and dense slices exist in FP32 only), so a plan serves
+// FP32 and FP32 + Kahan, or FP64, also where both take segments of the same size.
+static bool segments_fit(const gila_khop* kh, int precision) {
+    return kh->seg_ready && kh->seg == seg_size_for(kh, precision) &&
+           pos_bytes_of(kh->seg_precision) == pos_bytes_of(precision) &&
            kh->seg_weighted == (kh->mass64 != nullptr) && kh->seg_large == seg_big(kh);
+}
+
+bool segment_ready_for(const gila_khop* kh, int precision) {
+    return segment_path_enabled() && segments_fit(kh, precision);
 }
 
 void free_segments(gila_khop* kh, Release rel) {
@@ -905,11 +913,10 @@ struct Arena {
 
 int build_segments(gila_khop* kh, int precision, hipStream_t st) {
     const int32_t na = kh->n_active;
-    const int pos_bytes = precision == GILA_FP64 ? 16 : 8;
+    const int pos_bytes = pos_bytes_of(precision);
     const int S = seg_size_for(kh, precision);
     const bool weighted = kh->mass64 != nullptr;
-    if (kh->seg_ready && kh->seg == S && kh->seg_weighted == weighted && kh->seg_large == seg_big(kh))
-        return GILA_OK;
+    if (segments_fit(kh, precision)) return GILA_OK;
     free_segments(kh);
     if (na == 0) return GILA_OK;
     if (kh->nnz >= (int64_t)INT32_MAX) return fail(GILA_EUNSUPPORTED, "adjacency too large");

@@ -228,3 +228,31 @@ def test_dense_slice_coincident_and_forces(G, k, monkeypatch):
     assert per_vertex_force_err(F_g, F_o, S) <= 1e-5
     assert pos_err(x_g, x_o) <= 1e-5
     kh.free()
+
+
+@pytest.mark.parametrize("seg_bytes", ["512", "1040", "32768"])
+@pytest.mark.parametrize("dense", ["0", "1"])
+def test_precisions_in_turn_on_one_handle(G, seg_bytes, dense, monkeypatch):
+    """Segments of 64 vertices in every precision (GILA_SEG_BYTES=512: the least), of 129 and
+    64, and of the usual sizes: a handle that ran in one precision runs in another as a new
+    handle does, to the bit, and within the gates of the oracle."""
+    print(f"precisions in turn {seg_bytes} {dense}", flush=True)
+    monkeypatch.setenv("GILA_SEG_BYTES", seg_bytes)
+    monkeypatch.setenv("GILA_DENSE_MIN", dense)
+    g = inputs.barabasi_albert(700, 3, seed=8)
+    rp, ci = _dev(G, g)
+    x = inputs.uniform_positions(g.n, seed=9, width=400.0).astype(np.float32).astype(np.float64)
+    optr, oidx = oracle_rows(g, 2)
+    x_o, F_o, _, _ = oracle.step(g.n, g.row_ptr, g.col_idx, optr, oidx, 20.0, 10.0, x)
+    kept = G.build_khop(rp, ci, 2)
+    for precision in ("fp32", "fp64", "fp32_kahan", "fp64", "fp32"):
+        p = G.LayoutParams(temperature=np.array([10.0]), ideal_length=20.0,
+                           precision=G.PRECISIONS[precision])
+        x_g, F_g, _, _ = _gpu_step(G, kept, p, 0, x)
+        tol = 1e-12 if precision == "fp64" else 1e-5
+        assert rel_l2(F_g, F_o) <= tol and pos_err(x_g, x_o) <= tol, precision
+        own = G.build_khop(rp, ci, 2)
+        x_n, F_n, _, _ = _gpu_step(G, own, p, 0, x)
+        own.free()
+        assert np.array_equal(F_g, F_n) and np.array_equal(x_g, x_n), precision
+    kept.free()
