@@ -243,3 +243,28 @@ def test_labels_and_pack_at_kernel_edges(G, i):
     G.pack_components(label, 3.25, G.FP64, pos)
     # the same comparisons and sums in the same order: the same bits
     assert np.array_equal(pos.cpu().numpy(), oracle.pack(ol, 3.25, x))
+
+
+@pytest.mark.parametrize("length", [64, 1000])
+def test_labels_where_many_trees_link_late(G, length):
+    """Randomly numbered paths: after the first rounds every path is still many trees, which
+    workgroups of different XCDs link and flatten at the same time.  Every label is its
+    component's smallest id, as the host and as kernels of another shape read it."""
+    rng = np.random.default_rng(length)
+    n = 1 << 20
+    p, i = rng.permutation(n), np.arange(n - 1)
+    i = i[i % length != length - 1]
+    g = inputs.to_csr(n, p[i], p[i + 1], name=f"paths_of_{length}")
+    ol, oc = oracle.components(g.n, g.row_ptr, g.col_idx)
+    rp, ci = G.to_device_csr(g)
+    import torch
+    pos = torch.from_numpy(inputs.uniform_positions(n, 1)).float().cuda()
+    for run in range(3):
+        print(f"components {g.name} run {run}", flush=True)
+        label, count = G.components(rp, ci)
+        assert count == oc
+        assert np.array_equal(label.cpu().numpy(), ol)
+        G.pack_components(label, 10.0, G.FP32, pos)  # refuses labels that are no roots
+        label.fill_(-1)
+        assert G.components_noalloc(rp, ci, label) == oc
+        assert np.array_equal(label.cpu().numpy(), ol)
