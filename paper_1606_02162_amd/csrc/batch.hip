@@ -1723,6 +1723,7 @@ extern "C" {
 int gila_batch_build(const gila_csr* graphs_dev, int32_t count, const int32_t* k, void* stream,
                      gila_batch** out) {
     clear_error();
+    SettleOnReturn settle(stream);
     return batch_build(graphs_dev, count, k, (hipStream_t)stream, out);
 }
 
@@ -1730,6 +1731,7 @@ int gila_batch_run(gila_batch* b, const gila_params* params, void* const* pos_de
                    gila_stats* out) {
     TraceRange trace_range("gila_batch_run");
     clear_error();
+    SettleOnReturn settle(stream);
     if (!b) return fail(GILA_EINVAL, "batch is NULL");
     std::lock_guard<std::mutex> lk(b->mu);
     DeviceGuard dg(b->device);
@@ -1827,6 +1829,7 @@ int gila_batch_set_plan(gila_batch* b, const int32_t* lanes_host) {
 
 int gila_batch_tune(gila_batch* b, int32_t precision, void* stream, int32_t* class_lanes_host) {
     clear_error();
+    SettleOnReturn settle(stream);
     if (!b) return fail(GILA_EINVAL, "batch is NULL");
     if (precision != GILA_FP64 && precision != GILA_FP32 && precision != GILA_FP32_KAHAN)
         return fail(GILA_EINVAL, "unknown precision %d", precision);
@@ -1849,6 +1852,7 @@ int gila_layout_batch(const gila_csr* graphs_dev, int32_t count, const int32_t* 
                       gila_stats* out) {
     TraceRange trace_range("gila_layout_batch");
     clear_error();
+    SettleOnReturn settle(stream);
     gila_batch* b = nullptr;
     GILA_TRY(batch_build(graphs_dev, count, k, (hipStream_t)stream, &b));
     int rc;

@@ -1071,6 +1071,7 @@ int gila_components_noalloc(const gila_csr* g_dev, int32_t* label_dev, int32_t* 
 int gila_components(const gila_csr* g_dev, int32_t* label_dev, int32_t* count_out, void* stream) {
     TraceRange trace_range("gila_components");
     clear_error();
+    SettleOnReturn settle(stream);
     hipStream_t s = (hipStream_t)stream;
     GILA_TRY(validate_graph(g_dev, s));
     if (g_dev->n > 0 && !label_dev) return fail(GILA_EINVAL, "label_dev is NULL");
@@ -1096,6 +1097,7 @@ int gila_pack_components(int32_t n, const int32_t* label_dev, double gap, int32_
                          void* pos_dev, void* stream) {
     TraceRange trace_range("gila_pack_components");
     clear_error();
+    SettleOnReturn settle(stream);
     if (n < 0) return fail(GILA_EINVAL, "n must be >= 0");
     if (n > 0 && (!label_dev || !pos_dev)) return fail(GILA_EINVAL, "label_dev or pos_dev is NULL");
     if (!(gap >= 0.0) || !std::isfinite(gap)) return fail(GILA_EINVAL, "gap must be finite and >= 0");
@@ -1114,6 +1116,7 @@ int gila_layout_components(const gila_csr* g_dev, int32_t k, const gila_params* 
                            int32_t* iterations_host) {
     TraceRange trace_range("gila_layout_components");
     clear_error();
+    SettleOnReturn settle(stream);
     if (!params) return fail(GILA_EINVAL, "params is NULL");
     gila_params p = *params;
     p.temperature = nullptr;  // the caps are the components' own

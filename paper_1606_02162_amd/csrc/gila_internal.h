@@ -56,6 +56,18 @@ void dfree(void* p);
 // knows no work uses it).  No device-wide synchronisation.
 void dfree_on(void* p, hipStream_t s, bool idle = false);
 
+// Waits for `s` if blocks released on it are not yet known to be free, and marks them so.
+void settle_released(hipStream_t s);
+// At the end of a public call, after its other locals (declare it first): the caller may
+// destroy the stream once the call has returned.
+struct SettleOnReturn {
+    hipStream_t s;
+    explicit SettleOnReturn(void* stream) : s((hipStream_t)stream) {}
+    ~SettleOnReturn() { settle_released(s); }
+    SettleOnReturn(const SettleOnReturn&) = delete;
+    SettleOnReturn& operator=(const SettleOnReturn&) = delete;
+};
+
 // How a handle's device memory is released: hipFree (the default, safe for
 // work on any stream), or into the cache once the work on `stream` is done.
 struct Release {

@@ -1086,6 +1086,7 @@ extern "C" {
 
 int gila_build_khop(const gila_csr* g_dev, int32_t k, void* stream, gila_khop** out) {
     clear_error();
+    SettleOnReturn settle(stream);
     return build_khop(g_dev, k, (hipStream_t)stream, out);
 }
 
@@ -1176,6 +1177,7 @@ int gila_khop_export(const gila_khop* kh, int64_t* ptr_host, int32_t* idx_host) 
 
 int gila_khop_set_mass(gila_khop* kh, const double* mass_dev, void* stream) {
     clear_error();
+    SettleOnReturn settle(stream);
     if (!kh) return fail(GILA_EINVAL, "handle is NULL");
     std::lock_guard<std::mutex> lk(kh->mu);
     DeviceGuard dg(kh->device);

@@ -572,6 +572,7 @@ int gila_step(const gila_khop* kh_c, const gila_params* params, int32_t h, void*
               double* force_dev, double* disp_dev, void* stream, gila_stats* out) {
     TraceRange trace_range("gila_step");
     clear_error();
+    SettleOnReturn settle(stream);
     gila_khop* kh = const_cast<gila_khop*>(kh_c);
     if (!kh) return fail(GILA_EINVAL, "handle is NULL");
     GILA_TRY(check_params(params, true));
@@ -607,6 +608,7 @@ int gila_run(const gila_khop* kh_c, const gila_params* params, int32_t start_h, 
              void* pos_dev, void* stream, gila_stats* out) {
     TraceRange trace_range("gila_run");
     clear_error();
+    SettleOnReturn settle(stream);
     gila_khop* kh = const_cast<gila_khop*>(kh_c);
     if (!kh) return fail(GILA_EINVAL, "handle is NULL");
     GILA_TRY(check_params(params, true));
@@ -622,6 +624,7 @@ int gila_time_iterations(const gila_khop* kh_c, const gila_params* params, int32
                          int32_t reps, void* pos_dev, void* stream, double* ms_out) {
     TraceRange trace_range("gila_time_iterations");
     clear_error();
+    SettleOnReturn settle(stream);
     gila_khop* kh = const_cast<gila_khop*>(kh_c);
     if (!kh) return fail(GILA_EINVAL, "handle is NULL");
     if (!ms_out) return fail(GILA_EINVAL, "ms_out is NULL");
@@ -721,6 +724,7 @@ int gila_time_iterations(const gila_khop* kh_c, const gila_params* params, int32
 
 int gila_enable_history(gila_khop* kh, int32_t capacity, void* stream) {
     clear_error();
+    SettleOnReturn settle(stream);
     if (!kh) return fail(GILA_EINVAL, "handle is NULL");
     if (capacity < 0) return fail(GILA_EINVAL, "capacity must be >= 0");
     std::lock_guard<std::mutex> lk(kh->mu);
@@ -765,6 +769,7 @@ int gila_layout(const gila_csr* g_dev, int32_t k, const gila_params* params, voi
                 void* stream, gila_stats* out) {
     TraceRange trace_range("gila_layout");
     clear_error();
+    SettleOnReturn settle(stream);
     GILA_TRY(check_params(params, true));
     gila_khop* kh = nullptr;
     GILA_TRY(build_khop(g_dev, k, (hipStream_t)stream, &kh, params->precision));

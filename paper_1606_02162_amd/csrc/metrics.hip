@@ -1199,6 +1199,7 @@ int gila_drawing_metrics(const gila_csr* g_dev, int32_t precision, const void* p
                          int64_t* edge_crossings_dev, double* jaccard_dev) {
     TraceRange trace_range("gila_drawing_metrics");
     clear_error();
+    SettleOnReturn settle(stream);
     if (!out) return fail(GILA_EINVAL, "out is NULL");
     if (precision != GILA_FP64 && precision != GILA_FP32 && precision != GILA_FP32_KAHAN)
         return fail(GILA_EINVAL, "unknown precision %d", precision);

@@ -741,6 +741,7 @@ extern "C" {
 int gila_prune(const gila_csr* g_dev, void* stream, gila_pruned** out) {
     TraceRange trace_range("gila_prune");
     clear_error();
+    SettleOnReturn settle(stream);
     return prune(g_dev, (hipStream_t)stream, out);
 }
 
@@ -792,6 +793,7 @@ int gila_reinsert(const gila_pruned* p, double ideal_length, int32_t precision,
                   const void* pos_kept_dev, void* pos_all_dev, void* stream) {
     TraceRange trace_range("gila_reinsert");
     clear_error();
+    SettleOnReturn settle(stream);
     return reinsert(p, ideal_length, precision, pos_kept_dev, pos_all_dev, (hipStream_t)stream);
 }
 
@@ -805,6 +807,7 @@ int gila_layout_pruned(const gila_csr* g_dev, int32_t k, const gila_params* para
                        void* stream, gila_stats* out) {
     TraceRange trace_range("gila_layout_pruned");
     clear_error();
+    SettleOnReturn settle(stream);
     GILA_TRY(check_params(params, true));
     if (k < 1) return fail(GILA_EINVAL, "k must be >= 1 (got %d)", k);
     if (g_dev && g_dev->n > 0 && !pos_dev) return fail(GILA_EINVAL, "pos_dev is NULL");

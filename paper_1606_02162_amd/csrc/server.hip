@@ -755,6 +755,11 @@ void gila_server_destroy(gila_server* s) {
     (void)quiet(hipStreamSynchronize(s->download));
     for (Job* j : s->resident) release_device(j, s->build);
     for (Job* j : s->ready) release_device(j, s->build);
+    // no cached block may keep an event of a stream that is destroyed below
+    for (int c = 0; c < gila_server::kComputeStreams; ++c) settle_released(s->compute[c]);
+    settle_released(s->build);
+    for (auto& q : s->small) settle_released(q);
+    settle_released(s->download);
     for (auto& kv : s->jobs) delete kv.second;
     for (int c = 0; c < gila_server::kComputeStreams; ++c) (void)quiet(hipStreamDestroy(s->compute[c]));
     (void)quiet(hipStreamDestroy(s->build));

@@ -323,12 +323,18 @@ void clear_error() { t_last_error[0] = '\0'; }
 // launches, ticks) never waits for the whole device.  dfree() keeps
 // hipFree's semantics.  Cached blocks beyond kCacheLimit are returned to the
 // device (oldest first), and all of them when an allocation fails.
+//
+// An event must not be asked about once the stream it was recorded on is gone (the
+// runtime may look at that stream), so no event outlives its stream here: a public call
+// settles what it released on the caller's stream before it returns (SettleOnReturn), the
+// layout server what was released on its own streams before it destroys them.
 namespace {
 struct CachedBlock {
     void* p;
     size_t bytes;
     hipEvent_t ev;  // null: reusable at once
     uint64_t seq;
+    hipStream_t stream;  // of the event
 };
 struct LiveBlock {
     int device;
@@ -432,7 +438,7 @@ void dfree_on(void* p, hipStream_t s, bool idle) {
         (void)quiet(hipFree(p));
         return;
     }
-    CachedBlock c{p, it->second.bytes, nullptr, ++g_seq};
+    CachedBlock c{p, it->second.bytes, nullptr, ++g_seq, s};
     if (!idle) {
         if (hipEventCreateWithFlags(&c.ev, hipEventDisableTiming) != hipSuccess ||
             hipEventRecord(c.ev, s) != hipSuccess) {
@@ -446,6 +452,27 @@ void dfree_on(void* p, hipStream_t s, bool idle) {
     g_cached_bytes += c.bytes;
     g_live.erase(it);
     if (g_cached_bytes > kCacheLimit) trim_locked(kCacheLimit / 2);
+}
+
+void settle_released(hipStream_t s) {
+    if (!s) return;  // (the null stream stays)
+    uint64_t upto = 0;
+    {
+        std::lock_guard<std::mutex> lk(g_mem_mu);
+        for (const auto& kv : g_cache)
+            if (kv.second.ev && kv.second.stream == s) upto = std::max(upto, kv.second.seq);
+    }
+    if (upto == 0) return;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (quiet(hipStreamIsCapturing(s, &st)) != hipSuccess || st != hipStreamCaptureStatusNone) return;
+    if (quiet(hipStreamSynchronize(s)) != hipSuccess) return;
+    std::lock_guard<std::mutex> lk(g_mem_mu);
+    for (auto& kv : g_cache) {
+        CachedBlock& c = kv.second;
+        if (!c.ev || c.stream != s || c.seq > upto) continue;
+        (void)quiet(hipEventDestroy(c.ev));
+        c.ev = nullptr;
+    }
 }
 
 int64_t release_cached() {

@@ -1,0 +1,87 @@
+// Bursts of layout jobs on servers that come and go, and calls on streams of the caller
+// that come and go too, over the stand-in runtime (fake_hip.cpp).
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+#include "../../include/gila.h"
+
+extern "C" int hipStreamCreateWithFlags(void**, unsigned);
+extern "C" int hipStreamDestroy(void*);
+extern "C" int hipStreamSynchronize(void*);
+extern "C" int hipMalloc(void**, size_t);
+extern "C" int hipFree(void*);
+
+static void need(bool ok, const char* what) {
+    if (!ok) {
+        std::printf("FAILED %s: %s\n", what, gila_last_error());
+        std::fflush(stdout);
+        std::_Exit(2);
+    }
+}
+
+struct Ring {  // every vertex joined to the two on either side
+    std::vector<int64_t> rp;
+    std::vector<int32_t> ci;
+    gila_csr csr{};
+    explicit Ring(int32_t n) {
+        rp.push_back(0);
+        for (int32_t v = 0; v < n; ++v) {
+            int32_t u[4] = {(v + n - 2) % n, (v + n - 1) % n, (v + 1) % n, (v + 2) % n};
+            for (int i = 0; i < 4; ++i)
+                for (int j = i + 1; j < 4; ++j)
+                    if (u[j] < u[i]) std::swap(u[i], u[j]);
+            ci.insert(ci.end(), u, u + 4);
+            rp.push_back((int64_t)ci.size());
+        }
+        csr.n = n;
+        csr.nnz = (int64_t)ci.size();
+        csr.row_ptr = rp.data();
+        csr.col_idx = ci.data();
+    }
+};
+
+int main() {
+    setenv("GILA_PATH", "direct", 1);  // (segments are planned from counts that kernels make)
+    std::vector<double> temps(70, 1.0);
+    gila_params p{};
+    p.iterations = (int32_t)temps.size();
+    p.temperature = temps.data();
+    p.ideal_length = 10.0;
+    p.precision = GILA_FP32_KAHAN;
+    p.force_model = GILA_MODEL_FR;
+    std::vector<Ring> ring;
+    for (int32_t n : {100, 137, 400, 1024, 1025, 3000, 7000, 20000}) ring.emplace_back(n);
+    for (int round = 0; round < 4; ++round) {
+        gila_server* s = nullptr;
+        need(gila_server_create(0, 0, 16, &s) == GILA_OK, "create");
+        std::vector<uint64_t> t(40);
+        std::vector<std::vector<double>> out(40);
+        for (int i = 0; i < 40; ++i) {
+            const Ring& r = ring[i % ring.size()];
+            out[i].assign(2 * (size_t)r.csr.n, 0.5);
+            p.precision = i % 3 ? GILA_FP32_KAHAN : GILA_FP64;
+            need(gila_submit(s, &r.csr, 2, &p, out[i].data(), &t[i]) == GILA_OK, "submit");
+        }
+        for (int i = 0; i < 40; i += 7) need(gila_cancel(s, t[i]) == GILA_OK, "cancel");
+        for (int i = 0; i < 40; ++i) {
+            const int rc = gila_wait(s, t[i], out[i].data(), nullptr);
+            need(rc == GILA_OK || rc == GILA_ECANCELED, "wait");
+        }
+        gila_server_destroy(s);
+        // the calling thread's own streams, destroyed as soon as the call has returned
+        for (const Ring& r : ring) {
+            void* st = nullptr;
+            need(hipStreamCreateWithFlags(&st, 1) == 0, "stream");
+            void* pos = nullptr;
+            need(hipMalloc(&pos, 16 * (size_t)r.csr.n) == 0, "positions");
+            p.precision = GILA_FP32;
+            need(gila_layout(&r.csr, 2, &p, pos, st, nullptr) == GILA_OK, "layout");
+            need(hipStreamSynchronize(st) == 0 && hipStreamDestroy(st) == 0, "stream end");
+            need(hipFree(pos) == 0, "positions end");
+        }
+    }
+    std::printf("OK\n");
+    return 0;
+}
