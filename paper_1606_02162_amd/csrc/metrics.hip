@@ -339,9 +339,11 @@ __device__ __forceinline__ void orient_range(const CrossBox& B, float zx, float 
 // What a group's boxes say of an edge (ends z0, z1): 0 it crosses none of the
 // group, 1 all of it, 2 unsure.  eps covers the rounding of every value
 // compared, so 0 and 1 are what the exact signs give for each edge of the
-// group: the values are sums of two products of coordinate differences, each
-// at most (2 M)^2, whose float evaluation errs by less than 2^-19 M^2.  (An
-// edge that shares an end with one of the group, or is one of it, is never
+// group: the values are differences of two products of coordinate differences.
+// With u = 2^-24 a coordinate difference, at most 2 M, errs by 2 M u, a product
+// of two by 12 M^2 u (8 from its factors, 4 from itself) and the whole, at most
+// 8 M^2, by 2 * 12 + 8 = 32 M^2 u = 2^-19 M^2 and terms in u^2; eps is twice that.
+// (An edge that shares an end with one of the group, or is one of it, is never
 // found to cross all: that orientation is 0.)
 __device__ __forceinline__ int group_verdict(const CrossBox& B, float4 z, float eps) {
     if (fmaxf(z.x, z.z) < fminf(B.px0, B.qx0) || fminf(z.x, z.z) > fmaxf(B.px1, B.qx1) ||
@@ -1074,7 +1076,7 @@ static int drawing_metrics(const gila_csr* g, const V* pos, int32_t what, hipStr
         const dim3 grid((unsigned)((groups + kWaves - 1) / kWaves), (unsigned)((groups + span - 1) / span));
         // rounding of the values that the group verdicts compare; drawings so
         // small or large that their squares leave float's range get none
-        const float eps = M > 1e-12 && M < 1e18 ? (float)(0x1p-19 * M * M) : INFINITY;
+        const float eps = M > 1e-12 && M < 1e18 ? (float)(0x1p-18 * M * M) : INFINITY;
         if (edge_crossings) {
             GILA_HIP(hipMemsetAsync(edge_crossings, 0, sizeof(int64_t) * (size_t)m, s));
             hipLaunchKernelGGL(crossings_kernel<false>, grid, dim3(kBlock), 0, s, m, groups, span, M, eps,
