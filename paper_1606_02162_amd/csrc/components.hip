@@ -731,23 +731,24 @@ __global__ __launch_bounds__(kBlock) void pack_move_kernel(int32_t n, int32_t co
                                                            const double4* __restrict__ box,
                                                            const double* __restrict__ colx,
                                                            const double* __restrict__ rowy,
-                                                           V* __restrict__ pos) {
+                                                           const V* src, V* pos) {
     for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
          v += (int64_t)gridDim.x * kBlock) {
         const int32_t r = rank_of[label[v]];
         const double bx = box[r].x, by = box[r].y;
-        V p = pos[v];
+        V p = src[v];
         p.x = (decltype(p.x))((double)p.x + (colx[r % cols] - bx));
         p.y = (decltype(p.y))((double)p.y + (rowy[r / cols] - by));
         pos[v] = p;
     }
 }
 
-// Packs the drawings of the labelled components in place (caller's ids).
-// EINVAL, with pos untouched, for labels out of range or not naming a vertex
-// labelled with itself.
+// Packs the drawings of the labelled components (caller's ids) from src into pos, which
+// may be one.  Whatever fails -- EINVAL for labels out of range or not naming a vertex
+// labelled with itself, ENOMEM -- fails before pos is written.
 template <class V>
-static int pack_positions(int32_t n, const int32_t* label, double gap, V* pos, hipStream_t s) {
+static int pack_positions(int32_t n, const int32_t* label, double gap, const V* src, V* pos,
+                          hipStream_t s) {
     using R = decltype(V::x);
     if (n == 0) return GILA_OK;
     Buf size(s), lbox(s), flag(s), at(s), ws(s), small(s);
@@ -766,7 +767,7 @@ static int pack_positions(int32_t n, const int32_t* label, double gap, V* pos, h
                        lbox.as<LabelBox<R>>());
     // (few enough workgroups that each reduces many vertices of the largest component)
     hipLaunchKernelGGL((pack_reduce_kernel<V, R>), dim3((unsigned)std::min(grid_for(n), 512)), dim3(kBlock),
-                       0, s, n, label, most, pos, size.as<int32_t>(), lbox.as<LabelBox<R>>(), bad);
+                       0, s, n, label, most, src, size.as<int32_t>(), lbox.as<LabelBox<R>>(), bad);
     hipLaunchKernelGGL(root_flag_kernel, grid, dim3(kBlock), 0, s, n, label, flag.as<int64_t>());
     GILA_HIP(hipGetLastError());
     GILA_TRY(enqueue_exclusive_scan_i64(flag.as<int64_t>(), at.as<int64_t>(), n, ws.as<int64_t>(), s));
@@ -803,7 +804,7 @@ static int pack_positions(int32_t n, const int32_t* label, double gap, V* pos, h
     hipLaunchKernelGGL(pack_cells_kernel, dim3(2), dim3(kBlock), 0, s, cols, rows, gap, colw, rowh, colx,
                        rowy);
     hipLaunchKernelGGL(pack_move_kernel<V>, grid, dim3(kBlock), 0, s, n, cols, label,
-                       rank_of.as<int32_t>(), box.as<double4>(), colx, rowy, pos);
+                       rank_of.as<int32_t>(), box.as<double4>(), colx, rowy, src, pos);
     GILA_HIP(hipGetLastError());
     return GILA_OK;
 }
@@ -956,10 +957,12 @@ static int layout_components(const gila_csr* g, int32_t k, const gila_params* pa
         GILA_TRY(rc);
         for (int32_t j = 0; j < nsmall; ++j) runs[small_first + j] = st[j].iterations_run;
     }
+    Buf laid(s);  // the drawing before it is packed: pos stays as it was until nothing can fail
+    GILA_TRY(laid.alloc<V>((size_t)n));
     hipLaunchKernelGGL(scatter_old_kernel<V>, dim3(grid_for(n)), dim3(kBlock), 0, s, n,
-                       o.perm.as<int32_t>(), npos.as<V>(), pos);
+                       o.perm.as<int32_t>(), npos.as<V>(), laid.as<V>());
     GILA_HIP(hipGetLastError());
-    GILA_TRY(pack_positions<V>(n, label.as<int32_t>(), d, pos, s));
+    GILA_TRY(pack_positions<V>(n, label.as<int32_t>(), d, laid.as<V>(), pos, s));
     if (iterations_host) {
         std::vector<int32_t> perm((size_t)n);
         GILA_HIP(hipMemcpyAsync(perm.data(), o.perm.p, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s));
@@ -1105,8 +1108,8 @@ int gila_pack_components(int32_t n, const int32_t* label_dev, double gap, int32_
         return fail(GILA_EINVAL, "unknown precision %d", precision);
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GILA_OK;
-    if (precision == GILA_FP64) GILA_TRY(pack_positions<double2>(n, label_dev, gap, (double2*)pos_dev, s));
-    else GILA_TRY(pack_positions<float2>(n, label_dev, gap, (float2*)pos_dev, s));
+    if (precision == GILA_FP64) GILA_TRY(pack_positions<double2>(n, label_dev, gap, (double2*)pos_dev, (double2*)pos_dev, s));
+    else GILA_TRY(pack_positions<float2>(n, label_dev, gap, (float2*)pos_dev, (float2*)pos_dev, s));
     GILA_HIP(hipStreamSynchronize(s));
     return GILA_OK;
 }

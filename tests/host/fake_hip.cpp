@@ -41,7 +41,9 @@ Stream g_null;
 thread_local dim3_ t_grid, t_block;
 thread_local size_t t_shm;
 thread_local void* t_stream;
-int64_t g_fail_after = -1;  // hipMalloc calls until one fails (< 0: none does)
+int64_t g_fail_after = -1;  // hipMalloc calls until they fail (< 0: none does)
+const void* g_watched;      // positions whose writers are looked for (watched_by)
+bool g_touched;
 
 [[noreturn]] void violation(const char* call, const char* what) {
     std::printf("VIOLATION %s: %s\n", call, what);
@@ -97,6 +99,12 @@ bool was_written(const void* p) {
 thread_local const int64_t* t_deg;
 thread_local const int64_t* t_rp;
 
+// Which argument of a kernel is the positions it writes (-1: not one of these).
+int watched_by(const std::string& name) {
+    const auto is = [&](const char* k) { return name.find(k) != std::string::npos; };
+    return is("scatter_old_kernel") ? 3 : is("pack_move_kernel") ? 8 : -1;
+}
+
 void emulate(const std::string& name, void** a) {
     const auto is = [&](const char* k) { return name.find(k) != std::string::npos; };
     if (is("scan_tiles_kernel")) {
@@ -125,6 +133,11 @@ void emulate(const std::string& name, void** a) {
 extern "C" {
 
 void fake_hip_fail_malloc_after(int64_t calls) { g_fail_after = calls; }
+void fake_hip_watch(const void* positions) {
+    g_watched = positions;
+    g_touched = false;
+}
+int fake_hip_touched() { return g_touched ? 1 : 0; }
 
 void** __hipRegisterFatBinary(const void*) { return new void*(nullptr); }
 void __hipUnregisterFatBinary(void** m) { delete m; }
@@ -155,6 +168,8 @@ hipError_t hipLaunchKernel(const void* f, dim3_ grid, dim3_ block, void** args, 
     }
     if (grid.x == 0 || grid.y == 0 || block.x == 0 || block.x > 1024)
         violation(g_kernels[f].c_str(), "launch shape");
+    const int w = watched_by(g_kernels[f]);
+    if (w >= 0 && arg<const void*>(args, w) == g_watched) g_touched = true;
     if (!capturing) emulate(g_kernels[f], args);
     return hipSuccess;
 }
@@ -178,7 +193,8 @@ hipError_t hipGetSymbolAddress(void** p, const void*) {
 hipError_t hipFuncSetAttribute(const void*, int, int) { return hipSuccess; }
 
 hipError_t hipMalloc(void** p, size_t n) {
-    if (g_fail_after >= 0 && g_fail_after-- == 0) return hipErrorOutOfMemory;
+    if (g_fail_after == 0) return hipErrorOutOfMemory;
+    if (g_fail_after > 0) --g_fail_after;
     *p = std::calloc(1, n);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }

@@ -1,8 +1,10 @@
-// Bursts of layout jobs on servers that come and go, and calls on streams of the caller
-// that come and go too, over the stand-in runtime (fake_hip.cpp).
+// Over the stand-in runtime (fake_hip.cpp), by the argument: "streams", bursts of layout
+// jobs on servers that come and go, and calls on streams of the caller that come and go
+// too; "memory", a components' layout at every allocation that can fail.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "../../include/gila.h"
@@ -12,6 +14,9 @@ extern "C" int hipStreamDestroy(void*);
 extern "C" int hipStreamSynchronize(void*);
 extern "C" int hipMalloc(void**, size_t);
 extern "C" int hipFree(void*);
+extern "C" void fake_hip_fail_malloc_after(int64_t);
+extern "C" void fake_hip_watch(const void*);
+extern "C" int fake_hip_touched();
 
 static void need(bool ok, const char* what) {
     if (!ok) {
@@ -42,7 +47,27 @@ struct Ring {  // every vertex joined to the two on either side
     }
 };
 
-int main() {
+// A call that fails for want of memory leaves the caller's positions as they were.
+static void memory(const gila_csr& g, gila_params p) {
+    std::vector<double> pos(2 * (size_t)g.n, 0.5);
+    p.precision = GILA_FP64;
+    int failed = 0;
+    for (int64_t i = 0;; ++i) {
+        (void)hipStreamSynchronize(nullptr);
+        (void)gila_release_cached_memory();
+        fake_hip_watch(pos.data());
+        fake_hip_fail_malloc_after(i);
+        const int rc = gila_layout_components(&g, 2, &p, pos.data(), nullptr, nullptr, nullptr);
+        fake_hip_fail_malloc_after(-1);
+        if (rc == GILA_OK) break;
+        need(rc == GILA_ENOMEM, "out of memory");
+        need(!fake_hip_touched(), "positions written by a call that failed");
+        ++failed;
+    }
+    need(failed > 20 && fake_hip_touched(), "allocations that fail, and one call that does not");
+}
+
+int main(int argc, char** argv) {
     setenv("GILA_PATH", "direct", 1);  // (segments are planned from counts that kernels make)
     std::vector<double> temps(70, 1.0);
     gila_params p{};
@@ -53,6 +78,11 @@ int main() {
     p.force_model = GILA_MODEL_FR;
     std::vector<Ring> ring;
     for (int32_t n : {100, 137, 400, 1024, 1025, 3000, 7000, 20000}) ring.emplace_back(n);
+    if (argc > 1 && !std::strcmp(argv[1], "memory")) {
+        memory(ring[0].csr, p);
+        std::printf("OK\n");
+        return 0;
+    }
     for (int round = 0; round < 4; ++round) {
         gila_server* s = nullptr;
         need(gila_server_create(0, 0, 16, &s) == GILA_OK, "create");

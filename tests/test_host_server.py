@@ -2,8 +2,8 @@
 --offload-host-only) over a stand-in for the HIP runtime (tests/host/fake_hip.cpp) whose
 kernels do nothing and whose streams, events and graphs are watched, so that a call naming a
 destroyed one, or asking about an event whose stream was destroyed, is an error.  The driver
-(tests/host/server_driver.cpp) sends bursts of jobs to servers that come and go, and makes
-calls on streams of its own that come and go."""
+(tests/host/server_driver.cpp) sends bursts of jobs to servers that come and go, makes calls
+on streams of its own that come and go, and lets every allocation of a call fail."""
 import concurrent.futures as cf
 import glob
 import os
@@ -53,5 +53,12 @@ def driver(tmp_path_factory):
 
 
 def test_no_event_outlives_its_stream(driver):
-    rc, out = _run([driver], timeout=240)
+    rc, out = _run([driver, "streams"], timeout=240)
+    assert rc == 0 and out.strip().endswith("OK"), out
+
+
+def test_positions_stay_when_memory_runs_out(driver):
+    """gila_layout_components with the i-th device allocation and all after it failing, for
+    every i: ENOMEM, and no kernel that writes the caller's positions was launched."""
+    rc, out = _run([driver, "memory"], timeout=240)
     assert rc == 0 and out.strip().endswith("OK"), out
