@@ -220,16 +220,14 @@ struct BatchBfsArgs {
     int32_t* work;           // next unit (atomic)
     int32_t nmax;            // largest graph: vertices ...
     int64_t nnzmax;          // ... and adjacency entries
+    int32_t list_words;      // of a wavefront's frontier list (two ids each)
 };
 
 constexpr int kUnitSources = 512;
-// words of a wavefront's frontier list (two ids each)
-__host__ __device__ inline int batch_list_words(int nwords) { return nwords > 64 ? nwords : 64; }
-
-size_t batch_bfs_lds_bytes(int32_t nmax, int64_t nnzmax, int waves) {
+size_t batch_bfs_lds_bytes(int32_t nmax, int64_t nnzmax, int waves, int list_words) {
     const size_t nwords = (size_t)(nmax + 31) / 32;
     return 4 * ((size_t)nmax + 1) + 2 * (((size_t)nnzmax + 1) & ~(size_t)1) +
-           4 * (nwords * 2 + (size_t)batch_list_words((int)nwords)) * (size_t)waves;
+           4 * (nwords * 2 + (size_t)list_words) * (size_t)waves;
 }
 
 // One pass per source: after its BFS the wavefront knows |N_v(k)|, takes the
@@ -249,7 +247,7 @@ __global__ __launch_bounds__(BS) void batch_khop_kernel(BatchBfsArgs a) {
     uint16_t* s_ci = reinterpret_cast<uint16_t*>(s_rp + a.nmax + 1);
     uint32_t* s_bm = reinterpret_cast<uint32_t*>(s_ci + ((a.nnzmax + 1) & ~(int64_t)1));
     const int lane = lane64(), w = wave_id();
-    const int list_words = batch_list_words(nwords_max), list_cap = 2 * list_words;
+    const int list_words = a.list_words, list_cap = 2 * list_words;
     uint32_t* vis = s_bm + (size_t)w * (2 * nwords_max + list_words);
     uint32_t* cur = vis + nwords_max;
     uint16_t* list = reinterpret_cast<uint16_t*>(cur + nwords_max);
@@ -1417,14 +1415,20 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
     GILA_TRY(dalloc_t(&d_counts.p, (size_t)std::max<int64_t>(b->nv, 1)));
     GILA_TRY(dalloc_t(&b->kstart, (size_t)std::max<int64_t>(b->nv, 1)));
     GILA_TRY(dalloc_t(&b->klen, (size_t)std::max<int64_t>(b->nv, 1)));
-    // graphs whose CSR and three bitmaps per wavefront fit in LDS: one
-    // workgroup per graph, one pass; otherwise one workgroup per source,
-    // count then fill
+    // graphs whose CSR and three bitmaps per wavefront (the third as the
+    // frontier list) fit in LDS: one workgroup per unit, one pass; otherwise
+    // one workgroup per source, count then fill.  The list takes 64 words
+    // where a bitmap is shorter and LDS allows: a level of more ids than it
+    // holds expands every vertex visited so far once more.
     int64_t nnzmax = 0;
     for (int32_t i = 0; i < count; ++i) nnzmax = std::max(nnzmax, b->ebase[i + 1] - b->ebase[i]);
     const size_t max_lds = device_info(dev).max_lds_per_block;
-    const int bfs_bs = batch_bfs_lds_bytes(b->nmax, nnzmax, 16) + 1024 <= max_lds ? 1024 : 512;
-    const size_t bfs_lds = batch_bfs_lds_bytes(b->nmax, nnzmax, bfs_bs / 64);
+    const int nwords_max = (b->nmax + 31) / 32;
+    const auto lds_for = [&](int bs, int list) { return batch_bfs_lds_bytes(b->nmax, nnzmax, bs / 64, list); };
+    const int bfs_bs = lds_for(1024, nwords_max) + 1024 <= max_lds ? 1024 : 512;
+    const int long_list = std::max(nwords_max, 64);
+    const int bfs_list = lds_for(bfs_bs, long_list) + 1024 <= max_lds ? long_list : nwords_max;
+    const size_t bfs_lds = lds_for(bfs_bs, bfs_list);
     const bool per_graph = bfs_lds + 1024 <= max_lds &&
                            !(getenv("GILA_BATCH_BFS") && std::strcmp(getenv("GILA_BATCH_BFS"), "source") == 0);
     const int vg = (int)std::min<int64_t>(4096, (std::max<int64_t>(b->nv, 1) + kBlock - 1) / kBlock);
@@ -1487,6 +1491,7 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
         ga.work = d_bfs_work.p;
         ga.nmax = b->nmax;
         ga.nnzmax = nnzmax;
+        ga.list_words = bfs_list;
         GILA_TRY(run_batch_bfs(ga, bfs_lds, bfs_bs, dev, s));
         GILA_HIP(hipStreamSynchronize(s));
     } else if (b->nv > 0) {

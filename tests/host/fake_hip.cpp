@@ -37,6 +37,7 @@ std::set<Stream*> g_streams;
 std::set<Event*> g_events;
 std::set<void*> g_graphs;
 std::map<const void*, std::string> g_kernels;
+std::map<std::string, unsigned> g_block;  // threads per workgroup at each kernel's last launch
 Stream g_null;
 thread_local dim3_ t_grid, t_block;
 thread_local size_t t_shm;
@@ -137,6 +138,18 @@ void fake_hip_watch(const void* positions) {
     g_watched = positions;
     g_touched = false;
 }
+// Threads per workgroup at the last launch of a kernel whose name holds this (0: none), and
+// forgotten.
+unsigned fake_hip_block_of(const char* name) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    for (auto it = g_block.begin(); it != g_block.end(); ++it)
+        if (it->first.find(name) != std::string::npos) {
+            const unsigned b = it->second;
+            g_block.erase(it);
+            return b;
+        }
+    return 0;
+}
 int fake_hip_touched() { return g_touched ? 1 : 0; }
 
 void** __hipRegisterFatBinary(const void*) { return new void*(nullptr); }
@@ -165,6 +178,7 @@ hipError_t hipLaunchKernel(const void* f, dim3_ grid, dim3_ block, void** args, 
     {
         std::lock_guard<std::mutex> lk(g_mu);
         capturing = stream_of(s, "hipLaunchKernel")->capturing;
+        g_block[g_kernels[f]] = block.x;
     }
     if (grid.x == 0 || grid.y == 0 || block.x == 0 || block.x > 1024)
         violation(g_kernels[f].c_str(), "launch shape");

@@ -1,6 +1,7 @@
 // Over the stand-in runtime (fake_hip.cpp), by the argument: "streams", bursts of layout
 // jobs on servers that come and go, and calls on streams of the caller that come and go
-// too; "memory", a components' layout at every allocation that can fail.
+// too; "memory", a components' layout at every allocation that can fail; "batch", the route
+// of batches whose largest graph just fits a workgroup's LDS.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -17,6 +18,7 @@ extern "C" int hipFree(void*);
 extern "C" void fake_hip_fail_malloc_after(int64_t);
 extern "C" void fake_hip_watch(const void*);
 extern "C" int fake_hip_touched();
+extern "C" unsigned fake_hip_block_of(const char*);
 
 static void need(bool ok, const char* what) {
     if (!ok) {
@@ -67,6 +69,34 @@ static void memory(const gila_csr& g, gila_params p) {
     need(failed > 20 && fake_hip_touched(), "allocations that fail, and one call that does not");
 }
 
+// Complete graphs of n vertices: in 64 KB beside the CSR of 4 (n + 1) + 2 n (n - 1) bytes
+// and 1 KB of other state, three bitmaps for each of 16 wavefronts fit up to n = 177, for
+// each of 8 up to 178.
+static void batch() {
+    for (int32_t n : {100, 170, 175, 176, 177, 178, 179}) {
+        std::vector<int64_t> rp(1, 0);
+        std::vector<int32_t> ci;
+        for (int32_t v = 0; v < n; ++v) {
+            for (int32_t u = 0; u < n; ++u)
+                if (u != v) ci.push_back(u);
+            rp.push_back((int64_t)ci.size());
+        }
+        gila_csr g{};
+        g.n = n;
+        g.nnz = (int64_t)ci.size();
+        g.row_ptr = rp.data();
+        g.col_idx = ci.data();
+        const int32_t k = 2;
+        gila_batch* b = nullptr;
+        need(gila_batch_build(&g, 1, &k, nullptr, &b) == GILA_OK, "batch");
+        gila_batch_free(b);
+        const unsigned graph = fake_hip_block_of("batch_khop_kernel"), source = fake_hip_block_of("khop_bfs_kernel");
+        const unsigned want = n <= 177 ? 1024 : n <= 178 ? 512 : 0;
+        std::printf("n %d: %u threads per graph's workgroup, %u per source's\n", n, graph, source);
+        need(graph == want && (source == 0) == (want != 0), "route");
+    }
+}
+
 int main(int argc, char** argv) {
     setenv("GILA_PATH", "direct", 1);  // (segments are planned from counts that kernels make)
     std::vector<double> temps(70, 1.0);
@@ -80,6 +110,11 @@ int main(int argc, char** argv) {
     for (int32_t n : {100, 137, 400, 1024, 1025, 3000, 7000, 20000}) ring.emplace_back(n);
     if (argc > 1 && !std::strcmp(argv[1], "memory")) {
         memory(ring[0].csr, p);
+        std::printf("OK\n");
+        return 0;
+    }
+    if (argc > 1 && !std::strcmp(argv[1], "batch")) {
+        batch();
         std::printf("OK\n");
         return 0;
     }

@@ -31,3 +31,22 @@ def test_units_and_frontier_lists(k):
         assert np.array_equal(ptr, optr), (g.name, k)
         assert np.array_equal(idx, oidx), (g.name, k)
     b.free()
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 5])
+@pytest.mark.parametrize("largest", [100, 279, 280, 281, 283, 284, 285])
+def test_graphs_that_just_fit_in_lds(k, largest):
+    """Beside a complete graph that just fits (the LDS of a workgroup then holds lists of 18 ids
+    instead of 128): levels of one id, of a few and of nearly all; bit-exact again."""
+    require_gpu()
+    from paper_1606_02162_amd import gila
+    print(f"batch lds {largest} k={k}", flush=True)
+    graphs = [inputs.complete_graph(largest), inputs.star_graph(90), inputs.path_graph(99),
+              inputs.grid_graph(9, 10), inputs.barabasi_albert(95, 3, 2), inputs.path_graph(2)]
+    b = gila.Batch([gila.to_device_csr(g) for g in graphs], [k] * len(graphs))
+    for i, g in enumerate(graphs):
+        ptr, idx = b.export(i, g.n)
+        optr, oidx = oracle_rows(g, k)
+        assert np.array_equal(ptr, optr), (g.name, k)
+        assert np.array_equal(idx, oidx), (g.name, k)
+    b.free()

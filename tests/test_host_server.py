@@ -3,7 +3,8 @@
 kernels do nothing and whose streams, events and graphs are watched, so that a call naming a
 destroyed one, or asking about an event whose stream was destroyed, is an error.  The driver
 (tests/host/server_driver.cpp) sends bursts of jobs to servers that come and go, makes calls
-on streams of its own that come and go, and lets every allocation of a call fail."""
+on streams of its own that come and go, lets every allocation of a call fail, and looks at
+the route of batches near the LDS limit."""
 import concurrent.futures as cf
 import glob
 import os
@@ -61,4 +62,11 @@ def test_positions_stay_when_memory_runs_out(driver):
     """gila_layout_components with the i-th device allocation and all after it failing, for
     every i: ENOMEM, and no kernel that writes the caller's positions was launched."""
     rc, out = _run([driver, "memory"], timeout=240)
+    assert rc == 0 and out.strip().endswith("OK"), out
+
+
+def test_batch_route_near_the_lds_limit(driver):
+    """A batch takes one workgroup of 1024 threads, or of 512, per unit of a graph as long as
+    the graph and three bitmaps per wavefront fit in LDS."""
+    rc, out = _run([driver, "batch"], timeout=240)
     assert rc == 0 and out.strip().endswith("OK"), out
