@@ -194,13 +194,16 @@ __global__ void gather_bounds_kernel(const int64_t* __restrict__ kptr,
 // the graph's CSR is copied into LDS with local ids, then each wavefront takes one
 // source at a time and runs a level-synchronous BFS to depth k on a visited bitmap of
 // its own in LDS, deduplicating with LDS atomic ORs, and writes the row ascending by
-// scanning that bitmap.  A level's new vertices are listed (in up to list_cap entries)
-// and their rows walked one after another, an entry per lane: with a lane per frontier
-// vertex the longest row of each level was waited for, and with whole graphs for units the
-// largest graph (1000 random trees of 50 to 5000 vertices, k = 3: 2275 -> 1351 us).
-// A level that outgrows the list is followed by one that expands every vertex visited
-// so far, from a copy of the bitmap: the same set.  Used when every graph of the batch
-// fits.
+// scanning that bitmap.  A level's new vertices are listed (up to list_cap ids of all
+// levels) and their rows walked one after another, an entry per lane: with a lane per
+// frontier vertex the longest row of each level was waited for, and with whole graphs for
+// units the largest graph (1000 random trees of 50 to 5000 vertices, k = 3: 2275 -> 690
+// us with units of 512 sources, the walk and lane exchanges in the vector ALU).  The ids
+// that no longer fit the list go to a bitmap, and from then on each level's frontier is
+// one, its vertices taken 64 at a time, one per half word, the next level's in the list's
+// place.  (Expanding every vertex visited so far instead cost 300 Barabasi-Albert graphs
+// of 200 to 900, k = 6, 8.6 ms a build; 2.6 so, 4.7 with whole rows by one lane
+// throughout.)  Used when every graph of the batch fits.
 // Workgroups of 1024 threads (16 wavefronts share one graph, so that the
 // largest graphs, taken first, do not leave a long tail) when the per-wave
 // bitmaps fit beside the graph in LDS, else 512.
@@ -224,6 +227,10 @@ struct BatchBfsArgs {
 };
 
 constexpr int kUnitSources = 512;
+// Where no row of the 64 in hand is longer, a lane of a bitmap's frontier walks its own
+// (100 Barabasi-Albert graphs of 2000 to 4000, k = 6, ms a build: 9.3 without, 8.6, 7.9, 7.8
+// and 11.9 with 4, 8, 16 and any length; 300 small worlds 2.7, 2.8, 2.3, 2.2 and 2.3).
+constexpr int kOwnRow = 16;
 size_t batch_bfs_lds_bytes(int32_t nmax, int64_t nnzmax, int waves, int list_words) {
     const size_t nwords = (size_t)(nmax + 31) / 32;
     return 4 * ((size_t)nmax + 1) + 2 * (((size_t)nnzmax + 1) & ~(size_t)1) +
@@ -251,6 +258,7 @@ __global__ __launch_bounds__(BS) void batch_khop_kernel(BatchBfsArgs a) {
     uint32_t* vis = s_bm + (size_t)w * (2 * nwords_max + list_words);
     uint32_t* cur = vis + nwords_max;
     uint16_t* list = reinterpret_cast<uint16_t*>(cur + nwords_max);
+    for (int i = lane; i < nwords_max; i += 64) cur[i] = 0u;
     for (;;) {
         if (threadIdx.x == 0) s_unit = atomicAdd(a.work, 1);
         __syncthreads();
@@ -281,28 +289,37 @@ __global__ __launch_bounds__(BS) void batch_khop_kernel(BatchBfsArgs a) {
             for (int i = lane; i < nw; i += 64) vis[i] = i == (src >> 5) ? 1u << (src & 31) : 0u;
             if (lane == 0) list[0] = (uint16_t)src;
             wave_lds_fence();
-            int found = 0;         // ids of the levels before this one
-            int from = 0, to = 1;  // the frontier in the list
+            // take(valid, x) for every entry x of the rows that the lanes hold, one after
+            // another, an entry per lane; by the whole wavefront
+            const auto walk = [&](int start, int deg, bool one, auto&& take) {
+                const int inc = wave_inclusive_scan(deg);
+                const int total = __shfl(inc, 63, 64);
+                const int first = start - (inc - deg);  // entry t of the run: s_ci[first + t]
+                for (int t0 = 0; t0 < total; t0 += 64) {
+                    const int t = t0 + lane;
+                    int o = 0;  // the row of entry t: the first with inc > t
+                    if (!one) {
+#pragma unroll
+                        for (int h = 32; h >= 1; h >>= 1)
+                            if (__shfl(inc, o + h - 1, 64) <= t) o += h;
+                    }
+                    const int e = __shfl(first, o & 63, 64) + t;
+                    take(t < total, t < total ? s_ci[e] : 0);
+                }
+            };
+            // marks x as visited: whether it was not
+            const auto mark = [&](int x) {
+                const uint32_t m = 1u << (x & 31);
+                return !(atomicOr(&vis[x >> 5], m) & m);
+            };
+            int found = 0;         // ids of the levels so far
+            int from = 0, to = 1;  // the frontier in the list ...
             bool listed = true;
+            uint32_t *front = cur, *next = reinterpret_cast<uint32_t*>(list);  // ... or as a bitmap
             for (int level = 1; level <= k; ++level) {
-                int added = 0, at = 0;
-                // marks x (where take), listing it if a level follows
-                auto visit = [&](bool take, int x) {
-                    bool fresh = false;
-                    if (take) {
-                        const uint32_t m = 1u << (x & 31);
-                        fresh = !(atomicOr(&vis[x >> 5], m) & m);
-                    }
-                    const uint64_t b = __ballot(fresh);
-                    if (level < k && fresh) {
-                        const int slot = at + __popcll(b & ((1ull << lane) - 1));
-                        if (slot < list_cap) list[slot] = (uint16_t)x;
-                    }
-                    added += __popcll(b);
-                    at += __popcll(b);
-                };
+                int added = 0;
                 if (listed) {
-                    at = to;  // behind the frontier
+                    int at = to;  // behind the frontier
                     for (int c = from; c < to; c += 64) {
                         int start = 0, deg = 0;
                         if (c + lane < to) {
@@ -310,41 +327,58 @@ __global__ __launch_bounds__(BS) void batch_khop_kernel(BatchBfsArgs a) {
                             start = s_rp[u];
                             deg = s_rp[u + 1] - start;
                         }
-                        const int inc = wave_inclusive_scan(deg);
-                        const int total = __shfl(inc, 63, 64);
-                        const int first = start - (inc - deg);  // entry t of the run: s_ci[first + t]
-                        for (int t0 = 0; t0 < total; t0 += 64) {
-                            const int t = t0 + lane;
-                            int o = 0;  // the row of entry t: the first with inc > t
-                            if (to - from > 1) {
-#pragma unroll
-                                for (int h = 32; h >= 1; h >>= 1)
-                                    if (__shfl(inc, o + h - 1, 64) <= t) o += h;
+                        walk(start, deg, to - from == 1, [&](bool valid, int x) {
+                            const bool fresh = valid && mark(x);
+                            const uint64_t b = __ballot(fresh);
+                            if (level < k && fresh) {
+                                const int slot = __builtin_amdgcn_mbcnt_hi(
+                                    (uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, at));
+                                if (at + 64 <= list_cap || slot < list_cap) list[slot] = (uint16_t)x;
+                                else atomicOr(&cur[x >> 5], 1u << (x & 31));
                             }
-                            const int e = __shfl(first, o & 63, 64) + t;
-                            visit(t < total, t < total ? s_ci[e] : 0);
-                        }
+                            at += __popcll(b);
+                        });
                     }
-                } else {
-                    for (int i = lane; i < nw; i += 64) cur[i] = vis[i];
+                    added = at - to;
                     wave_lds_fence();
-                    for (int i0 = 0; i0 < nw; i0 += 64) {
-                        uint32_t bits = i0 + lane < nw ? cur[i0 + lane] : 0u;
+                    if (level < k && at > list_cap) {  // the rest of the level joins those in cur
+                        for (int t = to + lane; t < list_cap; t += 64)
+                            atomicOr(&cur[list[t] >> 5], 1u << (list[t] & 31));
+                        listed = false;
+                        wave_lds_fence();
+                    }
+                    from = to;
+                    to = at;
+                } else {
+                    for (int i = lane; i < nw; i += 64) next[i] = 0u;
+                    wave_lds_fence();
+                    const uint16_t* half = reinterpret_cast<const uint16_t*>(front);
+                    for (int i0 = 0; i0 < 2 * nw; i0 += 64) {
+                        uint32_t bits = i0 + lane < 2 * nw ? half[i0 + lane] : 0u;
                         while (__ballot(bits != 0u)) {
-                            const int u = (i0 + lane) * 32 + (bits ? __builtin_ctz(bits) : 0);
-                            const int e0 = bits ? s_rp[u] : 0, e1 = bits ? s_rp[u + 1] : 0;
+                            const int u = (i0 + lane) * 16 + (bits ? __builtin_ctz(bits) : 0);
+                            const int start = bits ? s_rp[u] : 0, deg = bits ? s_rp[u + 1] - start : 0;
                             bits &= bits - 1u;
-                            for (int e = e0; __ballot(e < e1); ++e) visit(e < e1, e < e1 ? s_ci[e] : 0);
+                            const auto reach = [&](bool valid, int x) {
+                                if (!valid || !mark(x)) return;
+                                ++added;
+                                atomicOr(&next[x >> 5], 1u << (x & 31));
+                            };
+                            if (__ballot(deg > kOwnRow)) walk(start, deg, false, reach);
+                            else for (int e = 0; e < deg; ++e) reach(true, s_ci[start + e]);
                         }
                     }
+                    added = wave_sum(added);
+                    wave_lds_fence();
+                    uint32_t* t = front;
+                    front = next;
+                    next = t;
                 }
                 found += added;
                 if (added == 0) break;
-                from = listed ? to : 0;
-                to = at;
-                listed = at <= list_cap;
-                // (after a level that expanded the whole bitmap the list holds just the
-                // new ids, from its start; when it overflows it is begun again there)
+            }
+            if (!listed) {  // cur is clear for the next source
+                for (int i = lane; i < nw; i += 64) cur[i] = 0u;
                 wave_lds_fence();
             }
             // the row's place: |N_v(k)| padded to quads, from the unit's cursor
@@ -1418,8 +1452,7 @@ int batch_build(const gila_csr* graphs, int32_t count, const int32_t* k, hipStre
     // graphs whose CSR and three bitmaps per wavefront (the third as the
     // frontier list) fit in LDS: one workgroup per unit, one pass; otherwise
     // one workgroup per source, count then fill.  The list takes 64 words
-    // where a bitmap is shorter and LDS allows: a level of more ids than it
-    // holds expands every vertex visited so far once more.
+    // where a bitmap is shorter and LDS allows.
     int64_t nnzmax = 0;
     for (int32_t i = 0; i < count; ++i) nnzmax = std::max(nnzmax, b->ebase[i + 1] - b->ebase[i]);
     const size_t max_lds = device_info(dev).max_lds_per_block;
