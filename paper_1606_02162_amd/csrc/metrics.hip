@@ -68,8 +68,24 @@ int mgrid(int64_t items) {
 }
 }  // namespace
 
-constexpr int kGabrielLanes = 8;          // lanes that share one point's search
-constexpr int64_t kGabrielBudget = 512;   // cells and points one of them visits for a point
+// Lanes that share one point's search, and the cells and points that one of them visits
+// before the point gets a wavefront of its own, by the number of points.  A lane more
+// shortens the walks, which is the time while the device has lanes to spare (it holds 2^18
+// of these), but the lanes of a group repeat each other's work between rings and wait for
+// the one with the fullest cell.  Similarity in ms with 1 / 2 / 8 lanes (budgets 2048, 1280,
+// 4096): 10k points at random 3.0 / 1.7 / 0.9, smoothed 9.7 / 10 / 5.0; 65k 4.1 / 3.1 / 2.1
+// and 7.8 / 5.8 / 5.5; 131k 5.2 / 3.9 / 3.3 and 9.8 / 7.0 / 11, in clusters of 50
+// 38 / 41 / 43, on a lattice 1.3 / 1.3 / 1.8; 262k at random 6.3 / 6.6 / 5.8, in clusters
+// 126 / 139 / 187, on a lattice 1.7 / 1.9 / 2.5.
+struct GabrielPlan {
+    int lanes;
+    int64_t budget;
+};
+inline GabrielPlan gabriel_plan(int32_t n) {
+    if (n <= 65536) return {8, 4096};
+    if (n <= 131072) return {2, 1280};
+    return {1, 2048};
+}
 
 // ------------------------------------------------------------------ points and edges
 template <class V>
@@ -892,11 +908,10 @@ __device__ int32_t gabriel_degree_of(int32_t iu, const Grid& g, const int64_t* _
     return over ? -1 : group_sum<G>(deg);
 }
 
-// kGabrielLanes lanes per point (in cell order: a wavefront's points are
-// neighbours); a point whose search exceeds the budget is listed in hard[] for
-// gabriel_wave_kernel instead.  The walks are latency-bound: with one lane per
-// point 131072 points are two wavefronts per SIMD, whose lanes also wait for
-// the longest of 64 walks (9.3 ms against 3.8 ms with eight).
+// L lanes per point (in cell order: a wavefront's points are neighbours); a point
+// whose search exceeds the budget is listed in hard[] for gabriel_wave_kernel
+// instead (gabriel_plan).
+template <int L>
 __global__ __launch_bounds__(kBlock, 4) void gabriel_degree_kernel(int32_t n, Grid g,
                                                                 const int64_t* __restrict__ start,
                                                                 const int32_t* __restrict__ pts,
@@ -905,7 +920,6 @@ __global__ __launch_bounds__(kBlock, 4) void gabriel_degree_kernel(int32_t n, Gr
                                                                 int32_t* __restrict__ gdeg,
                                                                 int32_t* __restrict__ hard,
                                                                 int32_t* __restrict__ hard_count) {
-    constexpr int L = kGabrielLanes;
     for (int64_t t = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / L; t < n;
          t += (int64_t)gridDim.x * (kBlock / L)) {
         const int32_t iu = pts[t];
@@ -1148,19 +1162,24 @@ static int drawing_metrics(const gila_csr* g, const V* pos, int32_t what, hipStr
                                             ws2.as<int64_t>(), s));
         hipLaunchKernelGGL(cell_fill_kernel, dim3(mgrid(n)), dim3(kBlock), 0, s, n, cellof.as<int32_t>(),
                            cstart.as<int64_t>(), cur.as<unsigned long long>(), pts.as<int32_t>());
-        // a point whose search visits more cells and points than this goes
-        // to a wavefront of its own (GILA_GABRIEL_BUDGET overrides; 0 sends
-        // every point there)
-        int64_t budget = kGabrielBudget;
+        // (GILA_GABRIEL_BUDGET overrides the budget; 0 sends every point to a
+        // wavefront of its own)
+        const GabrielPlan plan = gabriel_plan(n);
+        int64_t budget = plan.budget;
         if (const char* e = getenv("GILA_GABRIEL_BUDGET")) budget = std::max<int64_t>(0, std::atoll(e));
         MBuf hard(s), hcount(s);
         GILA_TRY(hard.alloc<int32_t>((size_t)n));
         GILA_TRY(hcount.alloc<int32_t>(1));
         GILA_HIP(hipMemsetAsync(hcount.p, 0, sizeof(int32_t), s));
         const float4 fbox = make_float4(xmin, xmax, ymin, ymax);
-        hipLaunchKernelGGL(gabriel_degree_kernel, dim3(mgrid((int64_t)n * kGabrielLanes)), dim3(kBlock), 0, s, n, gr,
-                           cstart.as<int64_t>(), pts.as<int32_t>(), pf.as<float2>(), (float)cell, fbox,
-                           budget, gdeg.as<int32_t>(), hard.as<int32_t>(), hcount.as<int32_t>());
+        const auto degrees = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(mgrid((int64_t)n * plan.lanes)), dim3(kBlock), 0, s, n, gr,
+                               cstart.as<int64_t>(), pts.as<int32_t>(), pf.as<float2>(), (float)cell, fbox,
+                               budget, gdeg.as<int32_t>(), hard.as<int32_t>(), hcount.as<int32_t>());
+        };
+        if (plan.lanes == 8) degrees(gabriel_degree_kernel<8>);
+        else if (plan.lanes == 2) degrees(gabriel_degree_kernel<2>);
+        else degrees(gabriel_degree_kernel<1>);
         hipLaunchKernelGGL(gabriel_wave_kernel, dim3(mgrid((int64_t)n * 64)), dim3(kBlock), 0, s, gr,
                            cstart.as<int64_t>(), pts.as<int32_t>(), pf.as<float2>(), (float)cell, fbox,
                            hard.as<int32_t>(), hcount.as<int32_t>(), gdeg.as<int32_t>());

@@ -225,3 +225,31 @@ def test_crossings_at_kernel_edges(G, i):
     both = G.drawing_metrics(rp, ci, G.FP32, pos, G.METRIC_CROSSINGS, edge_crossings=per).crossings
     assert np.array_equal(per.cpu().numpy(), want)
     assert total == both == int(want.sum()) // 2
+
+
+@pytest.mark.parametrize("n", [65536, 65537, 131072, 131073])
+def test_similarity_by_eight_two_and_one_lanes(G, n, monkeypatch):
+    """Where the number of lanes per point changes: the neighbours found by eight, two or one
+    lane of each point, and by a wavefront of its own for every point
+    (GILA_GABRIEL_BUDGET=0), are the same, at random, in clusters and on a lattice."""
+    import torch
+    g = inputs.erdos_renyi(n, 2 * n, seed=n)
+    rp, ci = G.to_device_csr(g)
+    rng = np.random.default_rng(n)
+    at = {"random": rng.random((n, 2)) * 1000.0,
+          "clusters": rng.integers(0, 200, (n, 2)) * 40.0 + rng.standard_normal((n, 2)),
+          "lattice": np.stack([np.arange(n) % 300, np.arange(n) // 300], 1)}
+    for name, x in at.items():
+        print(f"similarity {name} n={n}", flush=True)
+        pos = torch.from_numpy(x).float().cuda()
+        found = []
+        for budget in (None, "0"):
+            if budget is None:
+                monkeypatch.delenv("GILA_GABRIEL_BUDGET", raising=False)
+            else:
+                monkeypatch.setenv("GILA_GABRIEL_BUDGET", budget)
+            jac = torch.zeros(n, dtype=torch.float64, device="cuda")
+            m = G.drawing_metrics(rp, ci, G.FP32, pos, 4, None, jac)
+            found.append((m.gabriel_edges, m.similarity, jac.cpu().numpy()))
+        assert found[0][0] == found[1][0] > 0
+        assert found[0][1] == found[1][1] and np.array_equal(found[0][2], found[1][2])
