@@ -97,3 +97,35 @@ def test_stops_with_more_workgroups_than_the_device_holds(G, precision, H, stop,
     assert (st.energy, st.max_disp, st.moved, st.coincident) == \
         (last.energy, last.max_disp, last.moved, last.coincident)
     assert torch.equal(pos, ref)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_coincident_pairs_are_counted_for_their_own_iteration(G, path, precision):
+    """Twins (four leaves of each vertex of a path, in one place) stay coincident: every
+    iteration counts the same pairs while it reduces the one before.  In one range, in
+    replayed chunks and in single steps."""
+    import torch
+    print(f"coincident {path} {precision}", flush=True)
+    hubs, H = 2000, 110
+    i = np.arange(hubs)
+    leaf = hubs + 4 * i[:, None] + np.arange(4)[None, :]
+    u = np.concatenate([i[:-1], np.repeat(i, 4)])
+    v = np.concatenate([i[1:], leaf.ravel()])
+    g = inputs.to_csr(5 * hubs, u, v, "twins")
+    x = inputs.uniform_positions(g.n, 3)
+    x[leaf] = x[leaf[:, :1]]
+    rp, ci = G.to_device_csr(g)
+    prec = G.PRECISIONS[precision]
+    params = G.LayoutParams(temperature=np.full(H, 0.5), precision=prec)
+    x = torch.from_numpy(x).to(dtype=G.position_dtype(prec), device="cuda")
+    kh = G.build_khop(rp, ci, 2)
+    pairs = 12 * hubs  # ordered pairs of four twins
+    for end in (3, 20, H):
+        kh.enable_history(H)
+        pos = x.clone()
+        st = G.run(kh, params, pos, 0, end)
+        assert st.iterations_run == end and st.coincident == pairs
+        assert (kh.history(0, end)[:, 3] == pairs).all()
+    ref = x.clone()
+    for h in range(5):
+        assert G.step(kh, params, h, ref).coincident == pairs
