@@ -1,4 +1,5 @@
 // Error reporting, device helpers and small ABI functions of libgila.
+#include <atomic>
 #include <chrono>
 #include <cstdio>
 #include <cstdlib>
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(kBlock) void count_tiles_kernel(int64_t T, int64_t 
 // digit bit; an element's place is its digit's next one plus its rank among
 // the lower lanes.  Latency-bound (a tile is a chain of steps): one wavefront
 // per tile with a 64-step readlane ranking took 126 us a pass on 262144
-// elements (64 tiles), this 8 us (128 tiles of four wavefronts, 11 ballots
+// elements (64 tiles), this 12.5 us (128 tiles of four wavefronts, 11 ballots
 // for 2048 digits).  W = 1 where W histograms of nkeys words do not fit in LDS.
 template <int W>
 __global__ __launch_bounds__(64 * W) void scatter_tiles_kernel(int64_t T, int64_t tj, int64_t ntiles,
@@ -345,6 +346,7 @@ std::multimap<std::pair<int, size_t>, CachedBlock> g_cache;
 std::map<void*, LiveBlock> g_live;
 size_t g_cached_bytes = 0;
 uint64_t g_seq = 0;
+std::atomic<int64_t> g_events{0};  // cached blocks with an event (changed with the lock held)
 constexpr size_t kCacheLimit = (size_t)16 << 30;
 
 size_t size_class(size_t b) {
@@ -364,6 +366,13 @@ bool block_ready(const CachedBlock& c) {
     return quiet(hipEventQuery(c.ev)) == hipSuccess;
 }
 
+void drop_event(CachedBlock& c) {
+    if (!c.ev) return;
+    (void)quiet(hipEventDestroy(c.ev));
+    c.ev = nullptr;
+    --g_events;
+}
+
 // Returns ready cached blocks to the device until at most `keep` bytes stay
 // cached (all ready blocks for keep = 0).  Lock held.
 void trim_locked(size_t keep) {
@@ -376,7 +385,7 @@ void trim_locked(size_t keep) {
         if (!block_ready(it->second)) continue;
         DeviceGuard dg(it->first.first);
         if (quiet(hipFree(it->second.p)) != hipSuccess) continue;  // kept for a later trim
-        if (it->second.ev) (void)quiet(hipEventDestroy(it->second.ev));
+        drop_event(it->second);
         g_cached_bytes -= it->second.bytes;
         g_cache.erase(it);
     }
@@ -394,7 +403,7 @@ int dalloc(void** p, size_t bytes) {
         for (auto it = range.first; it != range.second; ++it) {
             if (!block_ready(it->second)) continue;
             *p = it->second.p;
-            if (it->second.ev) (void)quiet(hipEventDestroy(it->second.ev));
+            drop_event(it->second);
             g_cached_bytes -= rb;
             g_cache.erase(it);
             g_live[*p] = LiveBlock{dev, rb};
@@ -447,6 +456,7 @@ void dfree_on(void* p, hipStream_t s, bool idle) {
             c.ev = nullptr;
             (void)quiet(hipStreamSynchronize(s));
         }
+        if (c.ev) ++g_events;
     }
     g_cache.insert({{it->second.device, c.bytes}, c});
     g_cached_bytes += c.bytes;
@@ -455,7 +465,7 @@ void dfree_on(void* p, hipStream_t s, bool idle) {
 }
 
 void settle_released(hipStream_t s) {
-    if (!s) return;  // (the null stream stays)
+    if (!s || g_events == 0) return;  // (the null stream stays)
     uint64_t upto = 0;
     {
         std::lock_guard<std::mutex> lk(g_mem_mu);
@@ -469,9 +479,7 @@ void settle_released(hipStream_t s) {
     std::lock_guard<std::mutex> lk(g_mem_mu);
     for (auto& kv : g_cache) {
         CachedBlock& c = kv.second;
-        if (!c.ev || c.stream != s || c.seq > upto) continue;
-        (void)quiet(hipEventDestroy(c.ev));
-        c.ev = nullptr;
+        if (c.ev && c.stream == s && c.seq <= upto) drop_event(c);
     }
 }
 
