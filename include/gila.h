@@ -356,7 +356,7 @@ int gila_components(const gila_csr* g_dev, int32_t* label_dev, int32_t* count_ou
  * the same labels (label_dev as gila_components writes it, bit for bit) and
  * count, with no hipMalloc, hipFree or other allocating call.  The graph is
  * validated on the device (EINVAL as for gila_build_khop).  Its scratch (CSR
- * flags, the per-pass hooked flag, per-workgroup root counts) is a fixed
+ * checks, a sampled label, per-workgroup root counts) is a fixed
  * 16 KiB array of device memory inside the library, one copy per device,
  * held until the process ends; no graph needs more, so no size is refused
  * for it.  Every call on a device uses that device's copy: calls that

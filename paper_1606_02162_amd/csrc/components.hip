@@ -9,7 +9,9 @@
 // exactly: the ends' roots are joined with a compare-and-swap, retried from
 // the value found there when another link came first.  An edge with one end
 // outside is linked from that end, one inside joins nothing, so the trees are
-// then the components.  (Exact links of the first neighbours of all vertices
+// then the components: the scheme of M. Sutton, T. Ben-Nun and A. Barak,
+// "Optimizing Parallel Graph Connectivity Computation via Subgraph Sampling"
+// (2018), with atomic minima for hooks in the rounds.  (Exact links of the first neighbours of all vertices
 // at once took 0.64 ms on R-MAT 18: each retry climbs one hop of a long chain
 // of fresh hooks.)
 //

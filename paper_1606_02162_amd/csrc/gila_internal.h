@@ -135,8 +135,11 @@ constexpr int64_t kHubMin = 8192; // rows at least this long get a workgroup of 
 constexpr int kWaves = kBlock / 64;
 
 // ------------------------------------------------------------------ device control block
-// Written by the statistics kernel that ends each iteration; read by the host
-// at the end of a call and by the next iteration's kernels (stopped flag).
+// Statistics and the stopped flag are written by iteration_stats: in workgroup 0 of
+// the next iteration's force kernel, while the other workgroups of that launch run, or
+// in the statistics kernel that ends a sequence.  In the launch that sets `stopped` a
+// workgroup may see either value (it reads it once, for all its wavefronts); every
+// later launch, and the host at the end of a call, sees the new one.
 struct Ctl {
     int32_t stopped;
     int32_t iters_run;
@@ -317,7 +320,9 @@ struct gila_khop {
     gila::SegWg* seg_wg = nullptr;        // [seg_grid]
     int32_t seg_grid = 0;
     int32_t comb_grid = 0;
-    double2* part = nullptr;        // [T] partial force of each slice, row-major
+    // [T] partial force of each slice, row-major; with one segment [2 T]: two sets of
+    // per-vertex records (StepArgs::recs), by the iteration's parity
+    double2* part = nullptr;
     int32_t seg_precision = -1;     // precision the segments were built for
     bool seg_weighted = false;      // segment size chosen with a weight per staged vertex
     bool seg_large = false;         // force kernel shape: 1024 threads (else 512)
@@ -407,8 +412,8 @@ bool segment_path_enabled();
 int seg_size_for(const gila_khop* kh, int precision);
 // the segment layout is built for `precision` and the iteration uses it
 bool segment_ready_for(const gila_khop* kh, int precision);
-// implemented in layout.hip: publishes an iteration's statistics from the
-// per-workgroup partials (launched after each per-vertex kernel)
+// implemented in layout.hip: publishes an iteration's statistics (after each
+// iteration of the direct path, and after the last of a sequence on segments)
 int launch_iteration_stats(const StepArgs& a, hipStream_t s);
 // implemented in layout.hip: one iteration of a sequence on whichever path the
 // handle is ready for (has_prev as in launch_segment_step), and, after the
@@ -435,7 +440,7 @@ int enqueue_run(gila_khop* kh, const gila_params* p, int32_t start_h, int32_t en
 // Enqueues iterations [h, h + count) like enqueue_run, with the same bits;
 // when count == graph_len they replay one captured graph per handle (built on
 // first use, the caps read from a device copy of the schedule), so a tick of
-// the server costs two launches instead of three per iteration.
+// the server costs two launches and not one or two per iteration.
 int enqueue_tick(gila_khop* kh, const gila_params* p, int32_t h, int32_t count,
                  int32_t graph_len, void* pos_dev, hipStream_t s);
 // implemented in batch.hip
