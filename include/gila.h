@@ -351,9 +351,9 @@ int gila_layout_pruned(const gila_csr* g_dev, int32_t k, const gila_params* para
  * The graph is validated as for gila_build_khop.  Synchronises `stream`. */
 int gila_components(const gila_csr* g_dev, int32_t* label_dev, int32_t* count_out, void* stream);
 
-/* gila_components for callers that cannot allocate device memory (code under
- * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same labels (label_dev as gila_components writes it, bit for bit) and
+/* gila_components for callers that cannot allocate device memory (tight
+ * serving loops, harnesses that forbid hipMalloc; not a stream under capture,
+ * whose work it would wait for): the same labels (label_dev as gila_components writes it, bit for bit) and
  * count, with no hipMalloc, hipFree or other allocating call.  The graph is
  * validated on the device (EINVAL as for gila_build_khop).  Its scratch (CSR
  * checks, a sampled label, per-workgroup root counts) is a fixed
